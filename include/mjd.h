@@ -434,10 +434,12 @@ int mjd_entropy_decode(const uint8_t* h_jpg, size_t len, const mjd_scan* scan, c
 /* ---------------------------------------------------------------------
  * GPU entropy decoding of many baseline scans.  Restart intervals restart
  * the bit stream and the DC predictions (ITU-T T.81 restart markers), so
- * each one decodes on its own: one GPU lane decodes one interval.  This
- * moves the part the paper leaves on the CPU (Sec. 1: variable-length code
- * words) onto the device whenever a stream has restart markers.  A stream
- * without them is one interval and decodes on one lane (correct but slow).
+ * each one decodes on its own: one GPU lane decodes one interval.  Where a
+ * batch has few and long intervals (a stream without markers is one), they
+ * are cut into chunks whose block boundaries are found first, from several
+ * guesses each, and many lanes decode one interval.  This moves the part the
+ * paper leaves on the CPU (Sec. 1: variable-length code words) onto the
+ * device.
  * ------------------------------------------------------------------- */
 
 /* One scan to decode on the device. */
@@ -466,8 +468,8 @@ typedef struct mjd_entropy_batch mjd_entropy_batch;
  * are only recorded, not accessed. */
 int mjd_entropy_batch_create(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entropy_batch** out);
 
-/* Enqueue the decoding of every job on `stream`: one persistent kernel whose
- * workgroups take up to 256 intervals of one job at a time.  Launches of one
+/* Enqueue the decoding of every job on `stream`: two kernels, or up to seven
+ * where intervals are cut into chunks.  Launches of one
  * batch must be serialised (one stream).  Reads only the first len bytes of
  * each job's stream, rounded up to 16, and writes only its coefficient
  * blocks. */

@@ -1,50 +1,133 @@
-// GPU entropy decoding of many baseline scans: one lane per restart interval.
+// GPU entropy decoding of many baseline scans.
 //
-// The host plans the work:
-// - it checks every job;
-// - it builds each job's Huffman tables in the layout the kernel copies to
-//   LDS;
-// - it lists the restart intervals, sorts each job's list by length, and
-//   cuts it into items of at most 256 intervals, so an item never spans two
-//   jobs; items go longest first.
-// A persistent kernel pops items from a device counter. A workgroup loads
-// the tables of the item's job into LDS (only when the job changes). Each
-// lane then decodes one interval with the bit reader and block decoder of
-// entropy_lane.h. Blocks are scattered into a per-lane LDS buffer and stored
-// whole (128 B) in MCU order, the layout mjd_decode reads. Each interval's
-// status goes to a device array; the last workgroup out rearms the counter.
+// The host plans the work: it checks every job, builds its Huffman tables in
+// the layouts that the kernels copy to LDS, lists the restart intervals
+// (sorted by length within a job) and chooses which of them are split.  A
+// launch then runs, on one stream:
+//   entropy_destuff         the intervals' bytes without stuffed zeros, into
+//                           the batch's own memory (entropy_destuff_count
+//                           first, where an interval takes several waves);
+//   entropy_guess, _follow, where intervals are split: the block boundaries,
+//   _resolve                block counts and DC predictions at which their
+//                           parts begin;
+//   entropy_decode<true>    the parts of split intervals, a lane each;
+//   entropy_decode<false>   the other intervals, a lane each.
+// Both decoding kernels write whole blocks in MCU order, the layout that
+// mjd_decode reads.  Each interval's status goes to a device array.
 #include <stdio.h>
 #include <string.h>
 
 #include <algorithm>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
-#include "entropy_lane.h"
+#include "entropy_walk.h"
 #include "host_jpeg.h"
 #include "mjd_internal.h"
 
 namespace mjd {
 namespace gent {
 
+constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / 64;
+constexpr uint64_t kMaxStream = 0xFFFFFF00u;  // stream offsets are 32-bit
+constexpr uint32_t kTile = 4096;              // raw bytes that one wave destuffs
+constexpr uint32_t kLongSplit = 512;          // chunks above which a workgroup resolves an interval
+constexpr uint32_t kTail = 8192;              // bytes past the chunks that a workgroup may copy
+constexpr uint32_t kPad = 48;                 // bytes past an interval's raw length in its region
+constexpr uint32_t kStatusOk = 0xFFFFFFFFu;   // else (block in the interval) << 2 | kBadCode, kBadRun or kOverrun
+
 struct GJob {
   const uint8_t* jpg;
   int16_t* coef;
-  const GTables* tables;
-  uint32_t lim;        // stream bytes, rounded up to 16 (chunk loads stay below)
-  int32_t bpm;         // blocks per MCU
+  const FastTables* tables;
+  const GHuff* codes;  // the same tables' canonical codes
+  uint16_t* skip;      // kTableSlots skip tables, where the job has split intervals
+  uint32_t bpm;        // blocks per MCU
   uint32_t comp_bits;  // component of block b of an MCU in bits 2b..2b+1
-  uint32_t tsel;       // table slots of each component (plan_gtables)
+  uint32_t dc_slots;   // its DC and AC table slots, likewise
+  uint32_t ac_slots;
 };
 
+// One restart interval: its entropy-coded bytes [start, end) of the stream
+// (end: the marker that closes it), where its destuffed bytes go (16-byte
+// units), and its blocks among the job's.
+struct GInterval {
+  uint32_t start, end;
+  uint32_t dst;
+  uint32_t block0, n_blocks;
+  uint32_t job;
+};
+
+// A tile of an interval longer than kTile; first: the interval's first tile.
+struct GTile {
+  uint32_t iv, index, first;
+};
+
+// An interval decoded by chunks of destuffed bytes.  Chunks are numbered over
+// the batch, a job's one after the other, and lie in that order in memory.
+// 128 bytes: the 12-image corpus of 4:2:0 files takes 500 us, 625 with 256
+// and 1050 with 512; shorter ones leave more boundaries unguessed.
+constexpr uint32_t kChunk = 128, kChunkWords = kChunk / 4;
+struct GSplit {
+  uint32_t iv, chunk0, n_chunks;
+};
+// A workgroup's share of the chunks, of one job.
+struct GGroup {
+  uint32_t job, first, count;
+};
+
+// The part of the decoding that begins in one half of a chunk.
+constexpr uint32_t kParts = 2, kPart = kChunk / kParts;
+struct GTask {
+  uint32_t iv;
+  uint32_t word, bit_b;  // where it starts: word, bit | first block of the MCU << 8
+  uint32_t block0, n_blocks;
+  uint16_t dc[3];
+  uint16_t pad[3];
+};
+static_assert(sizeof(GTask) == 32, "two 16-byte loads");
+
+// What a lane found from the start of a part to the first block boundary in
+// the next: blocks and DC differences, and that boundary.
+struct GHop {
+  uint16_t blocks;
+  uint16_t dc[3];
+  uint32_t state;
+  uint32_t pad;
+};
+static_assert(sizeof(GHop) == 16, "one 16-byte store");
+
+// Tasks, or intervals, of one job that a workgroup decodes.
 struct GItem {
   uint32_t job, first, count;
-  uint32_t bytes;  // stream bytes of its longest interval
+  uint32_t bytes;  // of its longest lane
 };
 
-constexpr int kThreads = 256;
-constexpr uint64_t kMaxStream = 0xFFFFFF00u;  // stream offsets are 32-bit
+// Device tables of a batch (one allocation).
+struct GPlan {
+  const GJob* jobs;
+  const GInterval* ivs;
+  const GTile* tiles;
+  const GSplit* splits;
+  const GGroup* groups;
+  const uint32_t* split_of;  // per chunk
+  const GItem* items;
+  const uint32_t* skip_jobs;  // the jobs that have split intervals
+  uint32_t n_skip;
+  uint32_t n_iv, n_tiles, n_groups, n_more_groups, n_splits, n_long, n_items, n_split_items;
+  uint8_t* data;      // destuffed bytes
+  uint32_t* bytes;    // destuffed bytes per interval
+  uint32_t* kept;     // per tile: bytes kept, bit 31 where the data ends in it
+  uint32_t* status;   // per interval
+  uint32_t* states;   // kSlots per chunk
+  uint8_t* links;     // kSlots per chunk
+  GHop* hops;         // kParts per slot
+  GTask* tasks;       // kParts per chunk
+  unsigned* counters;
+};
 
 static int tables_for(const mjd_scan& scan, GTables* g, uint32_t* tsel) {
   switch (plan_gtables(scan, g, tsel)) {
@@ -64,117 +147,913 @@ static int tables_for(const mjd_scan& scan, GTables* g, uint32_t* tsel) {
 
 typedef __attribute__((address_space(3))) uint8_t lds8;
 typedef __attribute__((address_space(3))) uint16_t lds16;
+typedef __attribute__((address_space(3))) int16_t ldsi16;
 typedef __attribute__((address_space(3))) uint32_t lds32;
-typedef __attribute__((address_space(1))) const uint8_t gin8;
-typedef __attribute__((address_space(1))) const uint32_t gin32;
+typedef __attribute__((address_space(3))) uint64_t lds64;
 typedef int v4i_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(1))) v4i_t gout128;
-typedef __attribute__((address_space(1))) const v4i_t gin128;
+typedef uint32_t v4u_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i_t lds128;
+typedef __attribute__((address_space(1))) const uint8_t gin8;
+typedef __attribute__((address_space(1))) const v4u_t gin128;
+typedef __attribute__((address_space(1))) v4i_t gout128;
+typedef __attribute__((address_space(1))) uint8_t gout8;
+typedef __attribute__((address_space(1), aligned(1))) uint32_t gout32u;  // any byte address
+typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef __attribute__((address_space(1))) v4u_any gout128u;
 
-// Tables and the zig-zag map, in LDS.
-struct DevTab {
-  const __attribute__((address_space(3))) GHuff* tab;
-  const lds8* natural;
-  __device__ uint32_t fast(int t, int i) const { return tab[t].fast[i]; }
-  __device__ int lim(int t, int l) const { return tab[t].lim[l]; }
-  __device__ int valoff(int t, int l) const { return tab[t].valoff[l]; }
-  __device__ int val(int t, int i) const { return tab[t].vals[i]; }
-  __device__ int nat(int k) const { return natural[k]; }
-};
-
-// Per-lane LDS buffers (128-byte blocks, kRing-byte rings) sit one buffer
-// apart, so their 16-byte chunks are rotated by the lane number: the lanes
-// of a wave then spread a 16-byte access at the same offset over the banks.
-template <uint32_t kBytes>
-__device__ inline uint32_t swz(uint32_t off, uint32_t rot) {
-  static_assert(kBytes >= 16 && (kBytes & (kBytes - 1)) == 0, "buffers of a power-of-two number of chunks");
-  return (((off >> 4) + rot) & (kBytes / 16 - 1)) << 4 | (off & 15u);
+__device__ __forceinline__ uint32_t uniform(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
+}
+__device__ __forceinline__ uint32_t swap_bytes(uint32_t v) { return __builtin_amdgcn_perm(0, v, 0x00010203u); }
+__device__ __forceinline__ uint32_t lane_of() { return threadIdx.x & 63u; }
+// Lanes of `mask` below this one.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
 }
 
-// The block being decoded: 128 bytes of LDS per lane, stored whole (eight
-// 16-byte stores) to the next block of the interval and cleared.  The
-// stores are non-temporal: the coefficients are not read again by this
-// kernel, and written lines that stayed in the L2 would evict the lines of
-// the lanes' streams, which are then fetched again for every 16-byte chunk
-// (about 5 times the entropy-coded bytes instead of about 1.3).
-struct DevBlk {
-  lds8* buf;
-  gout128* dst;
-  uint32_t rot;
-  __device__ void put(int idx, int v) {
-    *reinterpret_cast<lds16*>(buf + swz<128>(static_cast<uint32_t>(idx) * 2, rot)) = static_cast<uint16_t>(v);
+// Makes a wave's LDS stores visible to its other lanes.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ---- destuffing -----------------------------------------------------------------
+// The zero that follows each 0xFF of a scan is dropped into a copy of the
+// interval, so that the decoding lanes, which then take plain words, neither
+// test every byte nor run the byte-wise path that one lane in six of a wave
+// needs in every step.  One wave takes kTile raw bytes, 16 a lane, and leaves
+// them by 16-byte stores at any address; bound by memory (15 us for the 17 MB
+// of the 12-image corpus, of 500).  Data ends at the first 0xFF that no zero
+// follows, as at the interval's end.
+
+// Bits 0..3: the bytes of x that are zero.
+__device__ __forceinline__ uint32_t zero_bytes(uint32_t x) {
+  const uint32_t t = ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu);  // 0x80 in each zero byte
+  return ((t >> 7) * 0x10204080u) >> 28 & 15u;
+}
+
+// Walks tile [a, b) of interval [start, end) of jpg; returns the bytes kept
+// and whether the data ends in it.  STORE: also writes them from dst on.
+template <bool STORE>
+__device__ __forceinline__ uint32_t destuff_tile(gin8* jpg, uint32_t start, uint32_t end, uint32_t a, uint32_t b,
+                                                 gout8* dst, bool* ends) {
+  const uint32_t lane = lane_of();
+  uint32_t total = 0;
+  *ends = false;
+  uint32_t p0 = a & ~15u;
+  for (uint32_t left = b - p0;; left -= 1024, p0 += 1024) {  // counts down: b may lie within 1024 bytes of 2^32
+    v4u_t v = {0, 0, 0, 0};
+    uint32_t prev_ff = 0, next_zero = 0, in_iv = 0, in_tile = 0;
+    if (16 * lane < left) {
+      const uint32_t p = p0 + 16 * lane;
+      v = *reinterpret_cast<gin128*>(jpg + p);
+      if (p > start) prev_ff = jpg[p - 1] == 0xFFu;
+      if (end - p > 16) next_zero = jpg[p + 16] == 0;
+      const uint32_t lo_i = p < start ? start - p : 0, hi_i = end - p < 16 ? end - p : 16;
+      const uint32_t lo_t = p < a ? a - p : 0, hi_t = b - p < 16 ? b - p : 16;
+      in_iv = ((1u << hi_i) - 1u) & ~((1u << lo_i) - 1u);
+      in_tile = ((1u << hi_t) - 1u) & ~((1u << lo_t) - 1u);
+    }
+    uint32_t ff = 0, zero = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      ff |= zero_bytes(~v[i]) << (4 * i);
+      zero |= zero_bytes(v[i]) << (4 * i);
+    }
+    ff &= in_iv;
+    zero &= in_iv;
+    const uint32_t stop = ff & ~(zero >> 1 | next_zero << 15) & in_tile;
+    uint32_t keep = in_tile & ~(zero & (ff << 1 | prev_ff));
+    const uint64_t stops = __ballot(stop != 0);
+    if (stops) {
+      const uint32_t first = static_cast<uint32_t>(__builtin_ctzll(stops));
+      keep = lane < first ? keep : (lane == first ? keep & ((stop & (0u - stop)) - 1u) : 0u);
+    }
+    const uint32_t n = static_cast<uint32_t>(__builtin_popcount(keep));
+    uint32_t before = 0, all = 0;  // kept by the lanes below, and by the wave
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      const uint64_t m = __ballot((n >> i & 1u) != 0);
+      before += lanes_below(m) << i;
+      all += static_cast<uint32_t>(__builtin_popcountll(m)) << i;
+    }
+    if constexpr (STORE) {
+      gout8* to = dst + total + before;
+      if (keep == 0xFFFFu) {
+        *reinterpret_cast<gout128u*>(to) = v;
+      } else if (keep) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (keep >> i & 1u) *to++ = static_cast<uint8_t>(v[i >> 2] >> (8 * (i & 3)));
+      }
+    }
+    total += all;
+    *ends = stops != 0;
+    if (stops || left <= 1024) return total;
   }
-  __device__ void finish() {
+}
+
+__global__ __launch_bounds__(kThreads) void entropy_destuff_count(const GPlan pl) {
+  const uint32_t w = uniform(blockIdx.x * kWaves + (threadIdx.x >> 6));
+  if (w >= pl.n_tiles) return;
+  const GTile t = pl.tiles[w];
+  const GInterval iv = pl.ivs[t.iv];
+  const uint32_t a = iv.start + t.index * kTile;
+  const uint32_t b = iv.end - a < kTile ? iv.end : a + kTile;
+  bool ends;
+  const uint32_t n = destuff_tile<false>((gin8*)pl.jobs[iv.job].jpg, iv.start, iv.end, a, b, nullptr, &ends);
+  if (lane_of() == 0) pl.kept[w] = n | (ends ? 0x80000000u : 0u);
+}
+
+// One entry per lane of a job's skip tables.
+__device__ __forceinline__ void fill_skip_tables(const GPlan& pl, uint32_t i) {
+  constexpr uint32_t kAll = kTableSlots * kSkipEntries;
+  if (i >= pl.n_skip * kAll) return;
+  const GJob& jb = pl.jobs[pl.skip_jobs[i / kAll]];
+  const uint32_t at = i % kAll, t = at / kSkipEntries;
+  bool ac = false;
+  for (uint32_t b = 0; b < jb.bpm; ++b) ac = ac || (jb.ac_slots >> (2 * b) & 3u) == t;
+  const FastTable& ft = jb.tables->t[t];
+  jb.skip[at] = static_cast<uint16_t>(skip_entry(at % kSkipEntries, ac, [&](uint32_t top) {
+    const uint32_t e = ft.fast[top >> (32 - kGLook)];
+    return e & 31u ? e : more_entry(e, top, ac, [&](uint32_t k) { return static_cast<uint32_t>(ft.more[k]); },
+                                    PlainTab{jb.codes}, static_cast<int>(t));
+  }));
+}
+
+// One wave per interval of at most kTile bytes, then one per tile of the
+// longer ones, after the bytes that entropy_destuff_count found in the tiles before;
+// the workgroups after those fill the skip tables that entropy_guess and
+// entropy_follow read.
+__global__ __launch_bounds__(kThreads) void entropy_destuff(const GPlan pl) {
+  const uint32_t groups = (pl.n_iv + pl.n_tiles + kWaves - 1) / kWaves;
+  if (blockIdx.x >= groups) return fill_skip_tables(pl, (blockIdx.x - groups) * kThreads + threadIdx.x);
+  const uint32_t w = uniform(blockIdx.x * kWaves + (threadIdx.x >> 6));
+  if (w >= pl.n_iv + pl.n_tiles) return;
+  const uint32_t lane = lane_of();
+  uint32_t which = w, tile = 0, at = 0;
+  if (w >= pl.n_iv) {
+    const GTile t = pl.tiles[w - pl.n_iv];
+    which = t.iv;
+    tile = t.index;
+    bool ended = false;
+    for (uint32_t i = lane; i < tile; i += 64) {
+      const uint32_t k = pl.kept[t.first + i];
+      at += k & 0x7FFFFFFFu;
+      ended = ended || (k >> 31);
+    }
+    for (int d = 32; d; d >>= 1) at += static_cast<uint32_t>(__shfl_xor(static_cast<int>(at), d));
+    at = uniform(at);
+    if (__ballot(ended)) return;
+  }
+  const GInterval iv = pl.ivs[which];
+  if (w < pl.n_iv) {
+    if (lane == 0) pl.status[which] = kStatusOk;
+    if (iv.end - iv.start > kTile) return;
+  }
+  const uint32_t a = iv.start + tile * kTile;
+  const uint32_t b = iv.end - a < kTile ? iv.end : a + kTile;
+  gout8* dst = (gout8*)(pl.data + static_cast<uint64_t>(iv.dst) * 16);
+  bool ends;
+  at += destuff_tile<true>((gin8*)pl.jobs[iv.job].jpg, iv.start, iv.end, a, b, dst + at, &ends);
+  if (ends || b == iv.end) {  // zeros up to the end of the chunk after the last
+    if (lane == 0) pl.bytes[which] = at;
+    if (lane < 8) *reinterpret_cast<gout32u*>(dst + at + 4 * lane) = 0;
+  }
+}
+
+// ---- tables and words in LDS -------------------------------------------------------
+
+typedef __attribute__((address_space(3))) FastTables lds_tables;
+
+__device__ __forceinline__ void load_tables(const FastTables* from, lds_tables* to) {
+  gin128* src = (gin128*)from;
+  __attribute__((address_space(3))) v4u_t* dst = (__attribute__((address_space(3))) v4u_t*)to;
+  for (uint32_t i = threadIdx.x; i < sizeof(FastTables) / 16; i += kThreads) dst[i] = src[i];
+}
+
+// The `fast` entry at the front of `top` in the table at byte offset t, and
+// the whole one where that uses no bits.
+__device__ __forceinline__ uint32_t fast_entry(const lds_tables* tabs, uint32_t t, uint32_t top) {
+  return *reinterpret_cast<const lds16*>((const lds8*)tabs + t + (top >> 21 & 0x7FEu));
+}
+__device__ __forceinline__ uint32_t long_code(const lds_tables* tabs, const GHuff* codes, uint32_t t, uint32_t top,
+                                              uint32_t e, bool ac) {
+  const lds16* more = reinterpret_cast<const lds16*>((const lds8*)tabs + t + sizeof(FastTable::fast));
+  return more_entry(e, top, ac, [more](uint32_t i) { return static_cast<uint32_t>(more[i]); }, PlainTab{codes},
+                    static_cast<int>(t / sizeof(FastTable)));
+}
+// Byte offset of the table that two bits of `slots` name for block b.
+__device__ __forceinline__ uint32_t table_of(uint32_t slots, uint32_t b) {
+  return (slots >> (2 * b) & 3u) * static_cast<uint32_t>(sizeof(FastTable));
+}
+
+// Words of consecutive chunks, which a workgroup or a wave copies to LDS
+// before it decodes them: a lane then waits for no load.  One word in 33 is
+// left free, so that lanes at the same place of different chunks meet in no
+// bank.  A lane's words are counted from the start of its interval and end
+// with a zero word past the data.
+constexpr uint32_t staged_size(uint32_t words) { return words + words / 32 + 1; }
+// Words that a block needs past the word of its first bit, the window's
+// included: a DC symbol of at most 27 bits and 63 of at most 31.
+constexpr uint32_t kBlockWords = (63 * 31 + 27 + 31) / 32 + 2;
+
+// Copies n words (a multiple of 4) from `src` on, by `lanes` lanes.
+__device__ __forceinline__ void stage_words(lds32* base, gin128* src, uint32_t n, uint32_t lane, uint32_t lanes) {
+  for (uint32_t i = lane; i < n / 4; i += lanes) {
+    const v4u_t v = src[i];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) __builtin_nontemporal_store(*reinterpret_cast<lds128*>(buf + swz<128>(16u * i, rot)), &dst[i]);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) reinterpret_cast<lds128*>(buf)[i] = v4i_t{0, 0, 0, 0};
-    dst += 8;
+    for (uint32_t j = 0; j < 4; ++j) base[4 * i + j + i / 8] = swap_bytes(v[j]);
+  }
+}
+
+struct StagedWords {
+  lds32* base;
+  gin128* src;    // the interval's data
+  uint32_t off;   // place of its first word in the copy (modulo 2^32)
+  uint32_t n;     // words of the copy
+  uint32_t zero;  // its zero word
+
+  __device__ uint32_t staged(uint32_t w) const {
+    const uint32_t i = (w < zero ? w : zero) + off;
+    return base[i + i / 32];
+  }
+  __device__ uint32_t word(uint32_t w) const {
+    const uint32_t v = w < zero ? w : zero, i = v + off;
+    if (__builtin_expect(i < n, 1)) return base[i + i / 32];
+    return swap_bytes(((__attribute__((address_space(1))) const uint32_t*)src)[v]);
+  }
+  __device__ BitWindow open(uint32_t at, uint32_t bit) const {
+    const uint32_t q = window_word(at, bit);
+    return window_at(at, bit, word(q ? q - 1 : 0), word(q));
   }
 };
 
-// The lane's stream: 16-byte chunk loads from global memory, held in two
-// register slots until the next refill writes them to the lane's 128-byte
-// LDS ring, from which every stream byte is read.
-struct DevMem {
-  gin8* jpg;
-  lds8* ring;
-  uint32_t rot;
-  v4i_t c0, c1;
-  __device__ void g_chunk(uint32_t p, int slot) {
-    const v4i_t v = *reinterpret_cast<gin128*>(jpg + p);
-    if (slot) c1 = v;
-    else c0 = v;
+// Eight words per lane in LDS (word w at [w & 7][lane], so that lanes at
+// different words meet no bank twice), filled from 16-byte chunks.  A chunk
+// is loaded at one refill and put in place at the next, so its latency
+// passes while the lane decodes; chunks past the data are the zero chunk
+// that destuffing leaves there.
+constexpr uint32_t kRingWords = 8;
+struct WordRing {
+  lds32* base;
+  gin128* src;
+  uint32_t last;  // the zero chunk
+  uint32_t have;  // words below are in place
+  v4u_t chunk;
+  bool loading;
+
+  __device__ void put(uint32_t at, v4u_t c) {
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) base[((at & 4u) + i) * kThreads] = swap_bytes(c[i]);  // at: a multiple of 4
   }
-  __device__ void commit(int slot, uint32_t off) { *reinterpret_cast<lds128*>(ring + swz<kRing>(off, rot)) = slot ? c1 : c0; }
-  __device__ uint32_t r_dword(uint32_t off) const { return *reinterpret_cast<const lds32*>(ring + swz<kRing>(off, rot)); }
+  __device__ uint32_t word(uint32_t w) const { return base[(w & (kRingWords - 1)) * kThreads]; }
+  // A window at the start.
+  __device__ BitWindow open(uint32_t bytes) {
+    last = bytes / 16 + 1;
+    const v4u_t c0 = src[0], c1 = src[1];  // there is always the zero chunk
+    put(0, c0);
+    put(4, c1);
+    have = 8;
+    loading = false;
+    return window_at(0, 0, 0, word(0));
+  }
+  __device__ void refill(bool active, uint32_t wi) {
+    if (loading) {
+      put(have, chunk);
+      have += 4;
+    }
+    loading = active && have - (wi & ~3u) <= 4;
+    if (loading) chunk = src[(have >> 2) < last ? have >> 2 : last];
+  }
+  __device__ bool ready(uint32_t wi) const { return wi < have; }
 };
 
-__global__ __launch_bounds__(kThreads) void entropy_kernel(const GJob* __restrict__ jobs,
-                                                           const Interval* __restrict__ ivs,
-                                                           const GItem* __restrict__ items, int n_items,
-                                                           uint32_t* __restrict__ status, unsigned* counters) {
-  __shared__ __align__(16) GTables tabs;
-  __shared__ __align__(16) uint32_t blocks[kThreads * 32];
-  __shared__ __align__(16) uint8_t rings[kThreads * kRing];
+// ---- finding the block boundaries of a split interval -----------------------------
+// A Huffman-coded stream read from a wrong bit falls into step with the code
+// words within a few tens of bytes, but its blocks may then be counted in the
+// wrong place of the MCU, and the tables of luma and chroma differ, so the
+// step is lost and found again until the place is right too: about 130 bytes
+// on average for 4:2:0, over 500 for one start in a hundred.  With one lane
+// per possible first block, one of them is right within 20 bytes for 19
+// starts of 20 (measured over qualities 50 to 95).
+//   guess    one lane per chunk and first block reads the chunk from its first
+//            bit and leaves the block boundary at which it enters the next;
+//   follow   one lane per distinct boundary reads on through that chunk,
+//            counts blocks and sums DC differences, and links the boundary to
+//            the one of the next chunk that it arrives at.  A lane that
+//            arrives elsewhere takes a free slot there and goes on;
+//   resolve  chains the links from the interval's start (a scan over maps of
+//            slots), and turns counts and sums into each chunk's task.
+// An interval whose chain breaks (no free slot, or not within kMaxHops
+// chunks, as textures that repeat can make it) is decoded by one lane from
+// that chunk on.
+// A lane's steps are one chain of dependent operations, about 550 cycles each
+// with a table look-up in LDS on it, so both kernels take several symbols a
+// step (skip tables, 12 to 11 bits of look-up cost 2% and leave room for four
+// workgroups a CU) and are bound by that chain where lanes are few and by
+// instruction issue where they are many: a 4000x3000 4:2:0 file with a marker
+// per MCU row takes 47 + 98 us in them, the 12-image corpus 142 + 183 us.
+constexpr uint32_t kMaxHops = 32;
+
+// The tables of a job for guess and follow.
+struct SkipLds {
+  __align__(16) FastTables fast;
+  __align__(16) uint16_t skip[kTableSlots * kSkipEntries];
+};
+typedef __attribute__((address_space(3))) SkipLds lds_skip;
+
+__device__ __forceinline__ void load_skip_tables(const GJob& jb, lds_skip* to) {
+  load_tables(jb.tables, (lds_tables*)&to->fast);
+  gin128* src = (gin128*)jb.skip;
+  __attribute__((address_space(3))) v4u_t* dst = (__attribute__((address_space(3))) v4u_t*)to->skip;
+  for (uint32_t i = threadIdx.x; i < kTableSlots * kSkipEntries / 8; i += kThreads) dst[i] = src[i];
+}
+
+// A lane on its way from a block boundary to another.
+struct Walker {
+  const lds_skip* tabs;
+  const GHuff* codes;
+  uint32_t bpm, slots_dc, slots_ac, comp_bits;
+  BitWindow w;
+  uint32_t b, k;
+  uint32_t t, ac;  // slots of the next symbol's table and of the block's AC table
+  uint32_t comp;
+  uint32_t blocks, dc0, dc1, dc2;  // since start_counts()
+
+  __device__ Walker(const GJob& jb, const lds_skip* tabs_)
+      : tabs(tabs_), codes(jb.codes), bpm(jb.bpm), slots_dc(jb.dc_slots), slots_ac(jb.ac_slots), comp_bits(jb.comp_bits) {
+    start_counts();
+  }
+  __device__ void start_counts() { blocks = dc0 = dc1 = dc2 = 0; }
+  __device__ void block(uint32_t b_) {
+    b = b_;
+    k = 0;
+    t = slots_dc >> (2 * b) & 3u;
+    ac = slots_ac >> (2 * b) & 3u;
+    comp = comp_bits >> (2 * b) & 3u;
+  }
+  // Whether the lane is at a block boundary at or past bit `target`.
+  __device__ bool reached(uint32_t target) const { return k == 0 && static_cast<int32_t>(w.pos() - target) >= 0; }
+  // One step of one or more symbols; `next` is word w.wi.  Where no code
+  // begins, the block ends (the decoding lane will find the error in it) and
+  // the lane goes on a bit later with a new first block.
+  template <bool COUNT>
+  __device__ __forceinline__ void step(uint32_t next) {
+    const uint32_t top = w.top();
+    const uint32_t m = tabs->skip[t << kSkipLook | top >> (32 - kSkipLook)];
+    uint32_t bits = m & 31u, to = k + (m >> 5 & 63u), size = m >> 11 & 15u;
+    bool end = m >> 15, bad = false;
+    if (bits == 0 || to > 63) {
+      const uint32_t ft = t * static_cast<uint32_t>(sizeof(FastTable));
+      const lds_tables* fast = (const lds_tables*)&tabs->fast;
+      uint32_t e = fast_entry(fast, ft, top);
+      if ((e & 31u) == 0) e = long_code(fast, codes, ft, top, e, k != 0);
+      bad = e == kBadEntry;
+      bits = bad ? 1u : e & 31u;
+      size = k || bad ? 0u : e >> 5 & 15u;
+      to = k + (e >> 9);
+      end = to > 63;
+    }
+    w.drop(bits, next);
+    if constexpr (COUNT) {
+      const uint32_t v = static_cast<uint32_t>(entry_value(top, bits, size));  // 0 for AC symbols
+      dc0 += comp == 0 ? v : 0u;
+      dc1 += comp == 1 ? v : 0u;
+      dc2 += comp == 2 ? v : 0u;
+    }
+    k = to;
+    t = ac;
+    if (end) {
+      if constexpr (COUNT) ++blocks;
+      block(bad || b + 1 == bpm ? 0u : b + 1);
+    }
+  }
+};
+
+// Words that a workgroup stages of its chunks and those after them, for a
+// block that begins in the last chunk and, in `follow`, for lanes that go on.
+constexpr uint32_t kGuessGroup = 85, kFollowGroup = 96;  // chunks: one lane per guess for three blocks an MCU
+constexpr uint32_t kFollowMore = 8;
+constexpr uint32_t kGuessWords = kGuessGroup * kChunkWords + kBlockWords;
+constexpr uint32_t kFollowWords = (kFollowGroup + kFollowMore) * kChunkWords;
+
+// A lane's chunk: its interval, its number there and the last one that holds
+// data, which hands over to none.
+struct ChunkOf {
+  GSplit sp;
+  uint32_t c, last;
+  StagedWords words;
+  __device__ ChunkOf(const GPlan& pl, const GGroup& g, uint32_t chunk, lds32* staged, uint32_t n) {
+    sp = pl.splits[pl.split_of[chunk]];
+    c = chunk - sp.chunk0;
+    const uint32_t bytes = pl.bytes[sp.iv];
+    last = bytes ? (bytes - 1) / kChunk : 0;
+    words.base = staged;
+    words.src = (gin128*)(pl.data + static_cast<uint64_t>(sp.chunk0) * kChunk);
+    words.off = (sp.chunk0 - g.first) * kChunkWords;
+    words.n = n;
+    words.zero = (bytes + 3) / 4;
+  }
+};
+
+__global__ __launch_bounds__(kThreads) void entropy_guess(const GPlan pl) {
+  __shared__ SkipLds tables;
+  __shared__ uint32_t staged[staged_size(kGuessWords)];
+  const GGroup g = pl.groups[blockIdx.x];
+  const GJob& jb = pl.jobs[g.job];
+  const uint32_t n = g.count * kChunkWords + kBlockWords;
+  stage_words((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, kThreads);
+  load_skip_tables(jb, (lds_skip*)&tables);
+  __syncthreads();
+  Walker walk(jb, (const lds_skip*)&tables);
+  const uint32_t mine = threadIdx.x / walk.bpm, first = threadIdx.x - mine * walk.bpm;
+  if (mine >= g.count) return;
+  const uint32_t chunk = g.first + mine;
+  const ChunkOf at(pl, g, chunk, (lds32*)staged, n);
+  uint32_t state = kNoState;
+  if (at.c < at.last && (at.c > 0 || first == 0)) {
+    const uint32_t target = (at.c + 1) * (kChunk * 8);
+    walk.w = at.words.open(at.c * kChunkWords, 0);
+    walk.block(first);
+    do walk.step<false>(at.words.staged(walk.w.wi));
+    while (!walk.reached(target));
+    state = make_state(walk.w.pos() - target, walk.b);
+  }
+  uint32_t* own = pl.states + static_cast<uint64_t>(chunk) * kSlots;
+  if (at.c == 0 && first == 0) {
+    own[0] = make_state(0, 0);
+    for (uint32_t i = 1; i < kSlots; ++i) own[i] = kNoState;
+  }
+  if (at.c + 1 < at.sp.n_chunks) {
+    own[kSlots + first] = state;
+    if (first == 0)
+      for (uint32_t i = walk.bpm; i < kSlots; ++i) own[kSlots + i] = kNoState;
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void entropy_follow(const GPlan pl) {
+  __shared__ SkipLds tables;
+  __shared__ uint32_t staged[staged_size(kFollowWords)];
+  __shared__ uint16_t list[kFollowGroup * kGuesses];  // chunk in the group << 3 | slot, without the empty and repeated ones
+  __shared__ uint32_t n_list;
+  const GGroup g = pl.groups[pl.n_groups + blockIdx.x];
+  const GJob& jb = pl.jobs[g.job];
+  const uint32_t n = (g.count + kFollowMore) * kChunkWords;
+  if (threadIdx.x == 0) n_list = 0;
+  stage_words((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, kThreads);
+  load_skip_tables(jb, (lds_skip*)&tables);
+  __syncthreads();
+  Walker walk(jb, (const lds_skip*)&tables);
+  for (uint32_t i0 = 0; i0 < g.count * walk.bpm; i0 += kThreads) {
+    const uint32_t i = i0 + threadIdx.x, mine = i / walk.bpm, slot = i - mine * walk.bpm;
+    bool use = mine < g.count;
+    if (use) {
+      const uint32_t* s = pl.states + static_cast<uint64_t>(g.first + mine) * kSlots;
+      const uint32_t own = s[slot];
+      use = own != kNoState;
+      for (uint32_t j = 0; j + 1 < kGuesses; ++j)
+        if (j < slot && s[j] == own) use = false;
+    }
+    const uint64_t m = __ballot(use);
+    uint32_t base = 0;
+    if (lane_of() == 0) base = atomicAdd(&n_list, static_cast<uint32_t>(__builtin_popcountll(m)));
+    base = uniform(base);
+    if (use) list[base + lanes_below(m)] = static_cast<uint16_t>(mine << 3 | slot);
+  }
+  __syncthreads();
+  const uint32_t n_work = n_list;
+  for (uint32_t i = threadIdx.x; i < n_work; i += kThreads) {
+    uint32_t chunk = g.first + (list[i] >> 3), slot = list[i] & 7u, hops = 0;
+    const ChunkOf at(pl, g, chunk, (lds32*)staged, n);
+    uint32_t c = at.c;
+    if (c >= at.last) continue;
+    const uint32_t from = pl.states[static_cast<uint64_t>(chunk) * kSlots + slot];
+    walk.w = at.words.open(c * kChunkWords + (from >> 8), (from >> 3) & 31u);
+    walk.block(from & 7u);
+    for (bool on = true; on;) {
+      uint32_t* to = pl.states + static_cast<uint64_t>(chunk + 1) * kSlots;
+      uint32_t guessed[kGuesses];  // asked for before the walk
+      for (uint32_t j = 0; j < kGuesses; ++j) guessed[j] = to[j];
+      const bool in_copy = (chunk + 1 - g.first) * kChunkWords + kBlockWords <= n;
+      GHop* hop = pl.hops + (static_cast<uint64_t>(chunk) * kSlots + slot) * kParts;
+      uint32_t state = 0, part = 0, target = c * (kChunk * 8) + kPart * 8;
+      walk.start_counts();
+      while (part < kParts) {
+        if (walk.reached(target)) {  // perhaps by a block longer than the part, without a step
+          state = make_state(walk.w.pos() - target, walk.b);
+          hop[part] = GHop{static_cast<uint16_t>(walk.blocks),
+                           {static_cast<uint16_t>(walk.dc0), static_cast<uint16_t>(walk.dc1), static_cast<uint16_t>(walk.dc2)},
+                           state, 0};
+          ++part;
+          target += kPart * 8;
+          walk.start_counts();
+        } else {
+          walk.step<true>(in_copy ? at.words.staged(walk.w.wi) : at.words.word(walk.w.wi));
+        }
+      }
+      uint32_t link = kNoLink;
+      for (uint32_t j = kGuesses; j-- > 0;)
+        if (guessed[j] == state) link = j;
+      on = false;  // unless this lane goes on from a slot of its own
+      if (link == kNoLink && ++hops < kMaxHops) {
+        for (uint32_t j = kGuesses; j < kSlots && link == kNoLink; ++j) {
+          const uint32_t was = atomicCAS(&to[j], kNoState, state);
+          if (was == kNoState || was == state) link = j;
+          on = was == kNoState;
+        }
+      }
+      pl.links[static_cast<uint64_t>(chunk) * kSlots + slot] = static_cast<uint8_t>(link);
+      on = on && c + 1 < at.last;
+      ++c;
+      ++chunk;
+      slot = link;
+    }
+  }
+}
+
+// Scans N values at once over a group of LANES lanes (64: a wave; more: the
+// workgroup): those of all lanes below go to `below`, those of the whole group
+// to `all`.
+template <int LANES, int N, class Then>
+__device__ __forceinline__ void scan(const uint32_t (&v)[N], uint32_t none, Then then, uint32_t* lds,
+                                     uint32_t (&below)[N], uint32_t (&all)[N]) {
+  const uint32_t lane = lane_of();
+  const auto wave_scan = [&](uint32_t (&x)[N], uint32_t width) {
+    for (uint32_t d = 1; d < width; d <<= 1)
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const uint32_t y = static_cast<uint32_t>(__shfl_up(static_cast<int>(x[i]), d));
+        x[i] = lane >= d ? then(y, x[i]) : x[i];
+      }
+  };
+  uint32_t x[N];
+  for (int i = 0; i < N; ++i) x[i] = v[i];
+  wave_scan(x, 64);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const uint32_t y = static_cast<uint32_t>(__shfl_up(static_cast<int>(x[i]), 1));
+    below[i] = lane ? y : none;
+    all[i] = static_cast<uint32_t>(__shfl(static_cast<int>(x[i]), 63));
+  }
+  if constexpr (LANES > 64) {
+    constexpr uint32_t kGroupWaves = LANES / 64;
+    const uint32_t wave = uniform(threadIdx.x >> 6);
+    if (lane == 0)
+      for (int i = 0; i < N; ++i) lds[i * kGroupWaves + wave] = all[i];
+    __syncthreads();
+    uint32_t y[N];  // each wave scans the waves' values
+#pragma unroll
+    for (int i = 0; i < N; ++i) y[i] = lds[i * kGroupWaves + lane % kGroupWaves];
+    wave_scan(y, kGroupWaves);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const uint32_t before = wave ? static_cast<uint32_t>(__shfl(static_cast<int>(y[i]), static_cast<int>(wave) - 1)) : none;
+      below[i] = then(before, below[i]);
+      all[i] = static_cast<uint32_t>(__shfl(static_cast<int>(y[i]), kGroupWaves - 1));
+    }
+  }
+}
+
+// One group of LANES lanes per split interval: a wave for most, a workgroup
+// for those of many chunks (pl.n_long of them, first in the list).  A lane
+// takes a run of chunks, kRun at a time so that their loads overlap.
+constexpr uint32_t kRun = 4;
+template <int LANES>
+__global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve(const GPlan pl) {
+  __shared__ uint32_t lds[LANES > 64 ? 4 * (LANES / 64) : 1];
+  __shared__ uint32_t broken_lds;
+  const uint32_t which = LANES > 64 ? blockIdx.x : pl.n_long + uniform(blockIdx.x * kWaves + (threadIdx.x >> 6));
+  if (which >= pl.n_splits) return;
+  const uint32_t id = LANES > 64 ? threadIdx.x : lane_of();
+  const GSplit sp = pl.splits[which];
+  const GInterval iv = pl.ivs[sp.iv];
+  const uint32_t bytes = pl.bytes[sp.iv];
+  const uint32_t last = bytes ? (bytes - 1) / kChunk : 0;
+  const uint32_t per = (last + LANES - 1) / LANES;
+  const uint32_t c0 = id * per < last ? id * per : last, c1 = c0 + per < last ? c0 + per : last;
+  const uint64_t* links = reinterpret_cast<const uint64_t*>(pl.links) + sp.chunk0;
+  // the maps of a run of chunks from chunk c on
+  auto load_maps = [&](uint32_t c, uint32_t (&maps)[kRun]) {
+    uint64_t l[kRun];
+#pragma unroll
+    for (uint32_t i = 0; i < kRun; ++i) l[i] = links[c + i < c1 ? c + i : c];
+#pragma unroll
+    for (uint32_t i = 0; i < kRun; ++i) maps[i] = map_of_links(l[i]);
+  };
+  uint32_t maps[kRun];
+  uint32_t m[1] = {kSameSlots}, below[1], all_map[1];
+  for (uint32_t c = c0; c < c1; c += kRun) {
+    load_maps(c, maps);
+#pragma unroll
+    for (uint32_t i = 0; i < kRun; ++i)
+      if (c + i < c1) m[0] = map_then(m[0], maps[i]);
+  }
+  scan<LANES, 1>(m, kSameSlots, [](uint32_t a, uint32_t b) { return map_then(a, b); }, lds, below, all_map);
+  const uint32_t slot0 = below[0] & 15u;  // the slot of chunk c0 that the chain enters by
+  // a run's slots along the chain (kNoLink after a missing link) and hops
+  struct Run {
+    uint32_t slot[kRun];
+    GHop hop[kRun][kParts];
+  };
+  auto load_run = [&](uint32_t c, uint32_t slot, Run* r) {
+    if (per > kRun) load_maps(c, maps);  // else they are still there
+#pragma unroll
+    for (uint32_t i = 0; i < kRun; ++i) {
+      r->slot[i] = slot;
+      slot = slot < kSlots ? maps[i] >> (4 * slot) & 15u : kNoLink;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kRun; ++i) {
+      const uint32_t s = r->slot[i] < kSlots ? r->slot[i] : 0u;
+      const GHop* h = pl.hops + (static_cast<uint64_t>(sp.chunk0 + (c + i < c1 ? c + i : c)) * kSlots + s) * kParts;
+#pragma unroll
+      for (uint32_t j = 0; j < kParts; ++j) r->hop[i][j] = h[j];
+    }
+    return slot;
+  };
+  uint32_t s[4] = {0, 0, 0, 0};
+  uint32_t slot = slot0, broken = 0xFFFFFFFFu;  // the first chunk whose link is missing
+  Run run;
+  for (uint32_t c = c0; c < c1 && broken == 0xFFFFFFFFu; c += kRun) {
+    const uint32_t next = load_run(c, slot, &run);
+#pragma unroll
+    for (uint32_t i = 0; i < kRun; ++i) {
+      if (c + i >= c1 || run.slot[i] >= kSlots) continue;
+#pragma unroll
+      for (uint32_t j = 0; j < kParts; ++j) {
+        s[0] += run.hop[i][j].blocks;
+        for (int d = 0; d < 3; ++d) s[1 + d] += run.hop[i][j].dc[d];
+      }
+      const uint32_t after = i + 1 < kRun ? run.slot[i + 1] : next;
+      if (after >= kSlots) broken = c + i;
+    }
+    slot = next;
+  }
+  for (int d = 32; d; d >>= 1) {
+    const uint32_t o = static_cast<uint32_t>(__shfl_xor(static_cast<int>(broken), d));
+    broken = o < broken ? o : broken;
+  }
+  if constexpr (LANES > 64) {
+    if (threadIdx.x == 0) broken_lds = 0xFFFFFFFFu;
+    __syncthreads();
+    if (lane_of() == 0) atomicMin(&broken_lds, broken);
+    __syncthreads();
+    broken = broken_lds;
+  }
+  uint32_t at[4], all[4];
+  scan<LANES, 4>(s, 0u, [](uint32_t a, uint32_t b) { return a + b; }, lds, at, all);
+  // `state`: where part `part` of chunk c begins; n: its blocks
+  auto task = [&](uint32_t c, uint32_t part, uint32_t state, uint32_t n, const uint32_t before[4]) {
+    const uint32_t done = before[0] < iv.n_blocks ? before[0] : iv.n_blocks;
+    GTask k;
+    k.iv = sp.iv;
+    k.word = c * kChunkWords + part * (kPart / 4) + (state >> 8);
+    k.bit_b = ((state >> 3) & 31u) | (state & 7u) << 8;
+    k.block0 = iv.block0 + done;
+    k.n_blocks = n < iv.n_blocks - done ? n : iv.n_blocks - done;
+    for (int d = 0; d < 3; ++d) {
+      k.dc[d] = static_cast<uint16_t>(before[1 + d]);
+      k.pad[d] = 0;
+    }
+    pl.tasks[static_cast<uint64_t>(sp.chunk0 + c) * kParts + part] = k;
+  };
+  auto no_task = [&](uint32_t c, uint32_t part) { task(c, part, 0, 0, s); };
+  auto entry = [&](uint32_t c, uint32_t in) {
+    return in < kSlots ? pl.states[static_cast<uint64_t>(sp.chunk0 + c) * kSlots + in] : 0u;
+  };
+  // up to the broken chunk each part decodes its own blocks; the first of
+  // that chunk, or of the last, all that are left
+  const uint32_t stop = broken < last ? broken : last;
+  slot = slot0;
+  for (uint32_t c = c0; c < c1; c += kRun) {
+    if (per > kRun) slot = load_run(c, slot, &run);  // else it is still there
+    uint32_t state[kRun];
+#pragma unroll
+    for (uint32_t i = 0; i < kRun; ++i) state[i] = entry(c + i < c1 ? c + i : c, run.slot[i]);
+#pragma unroll
+    for (uint32_t i = 0; i < kRun; ++i) {
+      if (c + i >= c1) continue;
+      uint32_t st = state[i];
+#pragma unroll
+      for (uint32_t j = 0; j < kParts; ++j) {
+        if (c + i > stop || (c + i == stop && j > 0)) {
+          no_task(c + i, j);
+          continue;
+        }
+        task(c + i, j, st, c + i == stop ? iv.n_blocks : run.hop[i][j].blocks, at);
+        st = run.hop[i][j].state;
+        at[0] += run.hop[i][j].blocks;
+        for (int d = 0; d < 3; ++d) at[1 + d] += run.hop[i][j].dc[d];
+      }
+    }
+  }
+  for (uint32_t c = last + id; c < sp.n_chunks; c += LANES)
+    for (uint32_t j = 0; j < kParts; ++j) {
+      if (c == last && j == 0 && stop == last) task(c, 0, entry(c, all_map[0] & 15u), iv.n_blocks, all);
+      else no_task(c, j);
+    }
+}
+
+// ---- decoding ------------------------------------------------------------------------
+// One lane decodes one interval, or one part of a split one, one symbol per
+// step.  A block is built in 128 bytes of LDS (the value of a step is stored
+// in the next one, beside its table lookup, so that only that lookup's
+// latency is on the lane's chain); a lane whose block is complete waits for
+// the next of the points that come every four steps, where it adds the DC
+// prediction and the wave stores all complete blocks together, eight lanes a
+// block, in whole 128-byte lines that do not stay in the L2.  When every lane
+// stored its own blocks as they ended, three lanes of a wave did so in each
+// step and all 64 waited for their 24 memory instructions.
+// Bound by a lane's chain of steps where intervals are few, by issue and LDS
+// (three workgroups a CU) where they are many: 153,904 intervals of 267 MB
+// take 1.6 ms (3.4 with stuffed bytes and stores by lane), 1.3 million of 274
+// MB 1.7 ms (2.5).
+
+// Per-lane block buffers sit 128 bytes apart; their 16-byte parts are rotated
+// by the lane, which spreads the lanes' stores over the banks.
+struct BlockBuf {
+  uint32_t base, rot;  // byte offset of the lane's buffer, 16 * (lane & 7)
+  __device__ uint32_t at(uint32_t byte) const { return base | ((byte + rot) & 127u); }
+};
+
+constexpr int kDecodeSteps = 4;  // between two points; every second one refills
+
+template <bool SPLIT>
+__global__ __launch_bounds__(kThreads, SPLIT ? 2 : 3) void entropy_decode(const GPlan pl) {
+  __shared__ __align__(16) FastTables tables;
+  __shared__ __align__(16) uint8_t block_bytes[kThreads * 128];
+  constexpr uint32_t kWaveLds = staged_size(64 * (kPart / 4) + kBlockWords);  // of a wave's parts
+  __shared__ uint32_t words_mem[SPLIT ? kWaves * kWaveLds : kRingWords * kThreads];
+  __shared__ uint32_t list_mem[kThreads];  // block | lane << 28 (its low four bits) of the wave's complete blocks
   __shared__ int s_next;
-  const int tid = static_cast<int>(threadIdx.x);
-  {
-    lds128* b = reinterpret_cast<lds128*>((lds8*)blocks + tid * 128);
+  const uint32_t tid = threadIdx.x, lane = lane_of();
+  const uint32_t wave = uniform(tid >> 6), wave0 = wave * 64;
+  lds_tables* tabs = (lds_tables*)&tables;
+  lds8* blocks = (lds8*)block_bytes;
+  lds32* list = (lds32*)list_mem + wave0;
+  const lds8* nat2 = (const lds8*)tables.nat2;  // indexed by the position after the coefficient
+  const BlockBuf buf{tid * 128, (lane & 7u) * 16};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) b[i] = v4i_t{0, 0, 0, 0};
-  }
-  int cur_job = -1;
+  for (uint32_t i = 0; i < 8; ++i) *reinterpret_cast<lds128*>(blocks + buf.base + 16 * i) = v4i_t{0, 0, 0, 0};
+  uint32_t cur_job = 0xFFFFFFFFu;
+  const uint32_t n_items = SPLIT ? pl.n_split_items : pl.n_items - pl.n_split_items;
+  const GItem* items = pl.items + (SPLIT ? 0 : pl.n_split_items);
+  unsigned* counters = pl.counters + (SPLIT ? 0 : 2);
   for (;;) {
     if (tid == 0) s_next = static_cast<int>(atomicAdd(&counters[0], 1u));
     __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(s_next);
+    const uint32_t it = uniform(static_cast<uint32_t>(s_next));
     __syncthreads();  // every lane has read s_next (and finished the last item)
     if (it >= n_items) break;
     const GItem item = items[it];
-    const int job = __builtin_amdgcn_readfirstlane(static_cast<int>(item.job));
+    const uint32_t job = uniform(item.job);
+    const GJob& jb = pl.jobs[job];
     if (job != cur_job) {
-      gin128* src = (gin128*)jobs[job].tables;
-      lds128* dst = (lds128*)&tabs;
-      for (int i = tid; i < static_cast<int>(sizeof(GTables) / 16); i += kThreads) dst[i] = src[i];
+      load_tables(jb.tables, tabs);
       __syncthreads();
       cur_job = job;
     }
-    if (tid < static_cast<int>(item.count)) {
-      const GJob& jb = jobs[job];
-      const Interval iv = ivs[item.first + static_cast<uint32_t>(tid)];
-      DevTab tab{(const __attribute__((address_space(3))) GHuff*)tabs.t, (const lds8*)tabs.nat};
-      const uint32_t rot = static_cast<uint32_t>(tid) & 7u;
-      DevBlk blk{(lds8*)blocks + tid * 128, (gout128*)(jb.coef + iv.mcu0 * static_cast<uint64_t>(jb.bpm) * 64), rot};
-      DevMem mem{(gin8*)jb.jpg, (lds8*)rings + tid * kRing, rot, v4i_t{0, 0, 0, 0}, v4i_t{0, 0, 0, 0}};
-      const uint32_t st = decode_interval(tab, blk, mem, jb.lim, iv, jb.bpm, jb.comp_bits, jb.tsel);
-      if (st != kOk) {  // leave the block buffer clear for the next interval
-        lds128* b = reinterpret_cast<lds128*>(blk.buf);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) b[i] = v4i_t{0, 0, 0, 0};
+    const uint32_t bpm = jb.bpm, comp_bits = jb.comp_bits, slots_dc = jb.dc_slots, slots_ac = jb.ac_slots;
+    const GHuff* codes = jb.codes;
+    gout128* coef = (gout128*)jb.coef;
+    // the lane's task
+    uint32_t which = 0, b = 0, block = 0, left = 0, block0 = 0, bytes = 0;
+    uint32_t p0 = 0, p1 = 0, p2 = 0;
+    const bool have_task = tid < item.count;
+    typename std::conditional<SPLIT, StagedWords, WordRing>::type words;
+    BitWindow w{0, 0, 0, 0};
+    if constexpr (SPLIT) {
+      // the parts lie in order in memory
+      words.base = (lds32*)words_mem + wave * kWaveLds;
+      const uint64_t word0 = static_cast<uint64_t>(item.first + wave0) * (kPart / 4);
+      words.n = 64 * (kPart / 4) + kBlockWords;
+      if (wave0 < item.count) stage_words(words.base, (gin128*)(pl.data + word0 * 4), words.n, lane, 64);
+      wave_sync();
+      if (have_task) {
+        const GTask k = pl.tasks[item.first + tid];
+        which = k.iv;
+        b = k.bit_b >> 8;
+        block = k.block0;
+        left = k.n_blocks;
+        p0 = k.dc[0];
+        p1 = k.dc[1];
+        p2 = k.dc[2];
+        const GInterval iv = pl.ivs[which];
+        bytes = pl.bytes[which];
+        block0 = iv.block0;
+        words.src = (gin128*)(pl.data + static_cast<uint64_t>(iv.dst) * 16);
+        words.off = iv.dst * 4u - static_cast<uint32_t>(word0);
+        words.zero = (bytes + 3) / 4;
+        w = words.open(k.word, k.bit_b & 255u);
       }
-      status[item.first + static_cast<uint32_t>(tid)] = st;
+    } else {
+      words.base = (lds32*)words_mem + tid;
+      words.src = (gin128*)pl.data;
+      words.loading = false;
+      words.have = words.last = 0;
+      if (have_task) {
+        which = item.first + tid;
+        const GInterval iv = pl.ivs[which];
+        bytes = pl.bytes[which];
+        block = block0 = iv.block0;
+        left = iv.n_blocks;
+        words.src = (gin128*)(pl.data + static_cast<uint64_t>(iv.dst) * 16);
+        w = words.open(bytes);
+      }
+    }
+    // k is the position of the block's next coefficient, at least 64 once it
+    // is complete, kIdle in a lane that has nothing to do
+    constexpr uint32_t kIdle = 1u << 20;
+    uint32_t k = left > 0 ? 0u : kIdle, size = 0;
+    uint32_t t = table_of(slots_dc, b), ac = table_of(slots_ac, b);
+    uint32_t place = 126;  // where the last symbol's value goes: not yet stored
+    int32_t value = 0, dc_value = 0;
+    bool refill = true;
+    const auto step = [&](uint32_t next) {
+      const uint32_t top = w.top();
+      uint32_t e = fast_entry(tabs, t, top);
+      *reinterpret_cast<ldsi16*>(blocks + buf.at(place)) = static_cast<int16_t>(value);
+      if ((e & 31u) == 0) e = long_code(tabs, codes, t, top, e, k != 0);
+      size = e >> 5 & 15u;
+      value = entry_value(top, e & 31u, size);
+      dc_value = k == 0 ? value : dc_value;
+      k += e >> 9;
+      place = nat2[k];
+      t = ac;
+      w.drop(e & 31u, next);
+    };
+    while (__ballot(k < kIdle)) {
+      if constexpr (SPLIT) {
+        // a lane near the end of the copy (one that decodes what a broken
+        // chain left) reads from memory
+        const uint32_t i = (w.wi < words.zero ? w.wi : words.zero) + words.off;
+        if (__ballot(k < 64 && i + kDecodeSteps >= words.n)) {
+          const uint32_t at = w.wi;
+          uint32_t q[kDecodeSteps];  // the words that the steps can come to
+          for (uint32_t s = 0; s < kDecodeSteps; ++s) q[s] = words.word(at + s);
+#pragma unroll 1
+          for (int s = 0; s < kDecodeSteps; ++s) {
+            const uint32_t d = w.wi - at;
+            if (k < 64) step(d == 0 ? q[0] : d == 1 ? q[1] : d == 2 ? q[2] : q[3]);
+          }
+        } else {
+#pragma unroll
+          for (int s = 0; s < kDecodeSteps; ++s)
+            if (k < 64) step(words.staged(w.wi));
+        }
+      } else {
+        if (refill) words.refill(k < kIdle, w.wi);
+        refill = !refill;
+#pragma unroll
+        for (int s = 0; s < kDecodeSteps; ++s)
+          if (k < 64 && words.ready(w.wi)) step(words.word(w.wi));
+      }
+      const bool full = k >= 64 && k < kIdle;
+      const uint64_t m = __ballot(full);
+      if (m == 0) continue;
+      if (full) {
+        *reinterpret_cast<ldsi16*>(blocks + buf.at(place)) = static_cast<int16_t>(value);
+        const uint32_t comp = comp_bits >> (2 * b) & 3u;
+        const uint32_t p = (comp == 0 ? p0 : comp == 1 ? p1 : p2) + static_cast<uint32_t>(dc_value);
+        *reinterpret_cast<ldsi16*>(blocks + buf.at(0)) = static_cast<int16_t>(p);
+        p0 = comp == 0 ? p : p0;
+        p1 = comp == 1 ? p : p1;
+        p2 = comp == 2 ? p : p2;
+        list[lanes_below(m)] = block | lane << 28;
+        // a size with a position past the block's end: no code began, or a
+        // run left the block
+        uint32_t error = k > 64 && size ? (k >= kBadStep ? kBadCode : kBadRun) : kOk;
+        b = b + 1 < bpm ? b + 1 : 0;
+        if (b == 0 && error == kOk && static_cast<int64_t>(w.wi - 1u) * 32 - w.sh > static_cast<int64_t>(bytes) * 8)
+          error = kOverrun;
+        if (error) atomicMin(&pl.status[which], (block - block0) << 2 | error);
+        ++block;
+        --left;
+        k = left > 0 && error == kOk ? 0u : kIdle;
+        t = table_of(slots_dc, b);
+        ac = table_of(slots_ac, b);
+        place = 126;
+        value = 0;
+      }
+      wave_sync();
+      // the lanes are listed in order: how many lie in each 16 gives the
+      // other two bits of a listed lane
+      const uint32_t n = static_cast<uint32_t>(__builtin_popcountll(m));
+      const uint32_t n1 = static_cast<uint32_t>(__builtin_popcountll(m & 0xFFFFull)),
+                     n2 = static_cast<uint32_t>(__builtin_popcountll(m & 0xFFFFFFFFull)),
+                     n3 = static_cast<uint32_t>(__builtin_popcountll(m & 0xFFFFFFFFFFFFull));
+      for (uint32_t i = lane >> 3; i < n; i += 8) {
+        const uint32_t x = list[i];
+        const uint32_t from = x >> 28 | (i >= n2 ? 32u + (i >= n3 ? 16u : 0u) : i >= n1 ? 16u : 0u), part = lane & 7u;
+        lds128* src = reinterpret_cast<lds128*>(blocks + ((wave0 + from) * 128 | ((16 * part + 16 * (from & 7u)) & 127u)));
+        __builtin_nontemporal_store(*src, &coef[static_cast<uint64_t>(x & 0xFFFFFFFu) * 8 + part]);
+        *src = v4i_t{0, 0, 0, 0};
+      }
+      wave_sync();
     }
   }
   // the last workgroup out rearms the queue for the next launch
@@ -193,31 +1072,68 @@ __global__ __launch_bounds__(kThreads) void entropy_kernel(const GJob* __restric
 
 struct mjd_entropy_batch {
   mjd_ctx* ctx = nullptr;
-  uint32_t n_jobs = 0;
-  uint32_t n_intervals = 0;
-  uint32_t n_items = 0;
-  int grid = 0;
-  mjd::gent::GJob* d_jobs = nullptr;
-  mjd::gent::GTables* d_tables = nullptr;
-  mjd::gent::Interval* d_ivs = nullptr;
-  mjd::gent::GItem* d_items = nullptr;
-  uint32_t* d_status = nullptr;
-  unsigned* d_counters = nullptr;
+  mjd::gent::GPlan plan{};
+  int grid = 0, split_grid = 0;
+  uint8_t* d_mem = nullptr;              // every table and buffer of the plan
   std::vector<uint32_t> first_interval;  // per job, into the interval list
   std::vector<uint32_t> iv_index;        // per listed interval, its number in its scan
-  uint64_t pixels = 0, bytes = 0;
+  uint64_t bytes = 0;
 };
 
 namespace mjd {
 namespace gent {
 
-static void free_batch(mjd_entropy_batch* b) {
-  if (b->d_jobs) (void)hipFree(b->d_jobs);
-  if (b->d_tables) (void)hipFree(b->d_tables);
-  if (b->d_ivs) (void)hipFree(b->d_ivs);
-  if (b->d_items) (void)hipFree(b->d_items);
-  if (b->d_status) (void)hipFree(b->d_status);
-  if (b->d_counters) (void)hipFree(b->d_counters);
+// The parts of one device allocation, in order; offsets are multiples of 256.
+struct Layout {
+  uint64_t size = 0;
+  uint64_t add(uint64_t bytes) {
+    const uint64_t at = size;
+    size = (size + bytes + 255) & ~uint64_t{255};
+    return at;
+  }
+};
+
+// The length above which intervals are split: the power of two (or none)
+// that gives the batch the least time by these rates, all measured on 4:2:0
+// files of quality 85 (us, with B and MB the entropy-coded bytes):
+// - a lane that decodes a whole interval takes 0.41 us a byte, however few
+//   there are (188 intervals of 14 KB: 7780 us, 9619 of 1.8 KB: 1000 us), and
+//   a batch of them at least 5.5 us a MB (1.3 million intervals of 0.2 KB:
+//   1740 us for 274 MB);
+// - a split batch takes 100 us more than 22 us a MB (2.5 MB: 226 us, 381 MB:
+//   7880 us).
+// Splitting is for what fits kSplitMost, which bounds its tables (2.8 bytes
+// per byte).
+constexpr uint64_t kSplitMost = uint64_t{256} << 20;
+static uint32_t split_threshold(const std::vector<GInterval>& ivs) {
+  uint64_t bytes[33] = {};  // of the intervals of 2^(i-1) < length <= 2^i
+  uint64_t count[33] = {};
+  uint32_t longest[33] = {};
+  for (const GInterval& iv : ivs) {
+    const uint32_t len = iv.end - iv.start;
+    int i = 0;
+    while (i < 32 && (uint64_t{1} << i) < len) ++i;
+    bytes[i] += len;
+    ++count[i];
+    longest[i] = std::max(longest[i], len);
+  }
+  double best = 0;
+  uint32_t over = 0xFFFFFFFFu;
+  uint64_t split = 0, rest = 0;
+  for (int i = 0; i <= 32; ++i) rest += bytes[i];
+  for (int i = 32; i >= 7; --i) {  // all above 2^i are split
+    uint32_t most = 0;
+    for (int j = 0; j <= i; ++j) most = std::max(most, longest[j]);
+    const double t = (split ? 100.0 + 22e-6 * static_cast<double>(split) : 0.0) +
+                     std::max(0.41 * most, 5.5e-6 * static_cast<double>(rest));
+    if (split <= kSplitMost && (i == 32 || t < best)) {
+      best = t;
+      over = i == 32 ? 0xFFFFFFFFu : 1u << i;
+    }
+    split += bytes[i] + count[i] * 2 * kChunk;
+    rest -= bytes[i];
+  }
+  return over;
 }
 
 static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entropy_batch* b) {
@@ -225,8 +1141,13 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   if (n > (1u << 24)) return fail(MJD_EINVAL, "entropy batch of %zu jobs too large", n);
   std::vector<GJob> gj(n);
   std::vector<GTables> gt(n);
-  std::vector<Interval> ivs;
+  std::vector<FastTables> ft(n);
+  std::vector<GInterval> ivs;
+  std::vector<GTile> tiles;
+  std::vector<GSplit> splits;
+  std::vector<GGroup> groups;
   std::vector<GItem> items;
+  uint64_t chunks = 0;  // of split intervals
   b->first_interval.resize(n);
   for (size_t j = 0; j < n; ++j) {
     const mjd_entropy_job& J = jobs[j];
@@ -242,78 +1163,217 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
       const std::string why = mjd_last_error();
       return fail(rc, "job %zu: %s", j, why.c_str());
     }
-    if (L.bpm > 8) return fail(MJD_EINVAL, "job %zu: %d blocks per MCU", j, L.bpm);
-    rc = tables_for(*J.scan, &gt[j], &gj[j].tsel);
+    if (L.bpm > static_cast<int>(kGuesses)) return fail(MJD_EINVAL, "job %zu: %d blocks per MCU", j, L.bpm);
+    uint32_t tsel;
+    rc = tables_for(*J.scan, &gt[j], &tsel);
     if (rc != MJD_OK) {
       const std::string why = mjd_last_error();
       return fail(rc, "job %zu: %s", j, why.c_str());
     }
-    memcpy(gt[j].nat, host::zigzag_to_natural(), 64);
-    gj[j].jpg = J.d_jpg;
-    gj[j].coef = J.d_coef;
-    gj[j].lim = static_cast<uint32_t>((J.len + 15) & ~uint64_t{15});
-    gj[j].bpm = L.bpm;
-    gj[j].comp_bits = 0;
-    for (int i = 0; i < L.bpm; ++i) gj[j].comp_bits |= static_cast<uint32_t>(L.comp_of[i]) << (2 * i);
+    gj[j] = GJob{J.d_jpg, J.d_coef, nullptr, nullptr, nullptr, static_cast<uint32_t>(L.bpm), 0, 0, 0};
+    uint32_t ac_used = 0;
+    for (int c = 0; c < 3; ++c) ac_used |= 1u << (tsel >> (4 * c + 2) & 3u);
+    for (int t = 0; t < kTableSlots; ++t) build_fast_table(gt[j].t[t], ac_used >> t & 1u, &ft[j].t[t]);
+    build_places(host::zigzag_to_natural(), ft[j].nat2);
+    for (int i = 0; i < L.bpm; ++i) {
+      const uint32_t c = static_cast<uint32_t>(L.comp_of[i]);
+      gj[j].comp_bits |= c << (2 * i);
+      gj[j].dc_slots |= (tsel >> (4 * c) & 3u) << (2 * i);
+      gj[j].ac_slots |= (tsel >> (4 * c + 2) & 3u) << (2 * i);
+    }
     // the intervals: byte ranges from the restart index, checked against the stream
     const uint32_t ni = J.scan->n_intervals;
     const uint64_t ri = J.scan->restart_interval ? J.scan->restart_interval : L.n_mcus;
     const uint64_t* off = J.h_offsets;
     if (off[ni] > J.len) return fail(MJD_EINVAL, "job %zu: restart index past the stream end", j);
-    b->first_interval[j] = static_cast<uint32_t>(ivs.size());
+    const size_t first = ivs.size();
+    b->first_interval[j] = static_cast<uint32_t>(first);
+    if (first + ni > 0x7FFFFFF0u) return fail(MJD_EINVAL, "entropy batch holds too many intervals");
     for (uint32_t s = 0; s < ni; ++s) {
       if (off[s + 1] < off[s] + 2) return fail(MJD_EINVAL, "job %zu: restart index not increasing", j);
-      Interval iv;
+      GInterval iv;
       iv.start = static_cast<uint32_t>(off[s]);
       iv.end = static_cast<uint32_t>(off[s + 1] - 2);
-      iv.index = s;
-      iv.mcu0 = s * ri;
-      iv.n_mcus = static_cast<uint32_t>(std::min<uint64_t>(ri, L.n_mcus - iv.mcu0));
+      iv.dst = s;  // its number in the scan, until the list is sorted
+      iv.block0 = static_cast<uint32_t>(s * ri * L.bpm);
+      iv.n_blocks = static_cast<uint32_t>(std::min<uint64_t>(ri, L.n_mcus - s * ri) * L.bpm);
+      iv.job = static_cast<uint32_t>(j);
       ivs.push_back(iv);
     }
     // A lane's decode time follows its interval's length, and a wave (and a
     // workgroup) lasts as long as its longest interval: sort the job's
     // intervals longest first so that each item holds intervals of similar
     // length.
-    const auto first = ivs.begin() + b->first_interval[j];
-    std::stable_sort(first, ivs.end(),
-                     [](const Interval& x, const Interval& y) { return x.end - x.start > y.end - y.start; });
-    for (uint32_t s = 0; s < ni; s += kThreads) {
-      const Interval& lead = ivs[b->first_interval[j] + s];
-      items.push_back(GItem{static_cast<uint32_t>(j), b->first_interval[j] + s, std::min<uint32_t>(kThreads, ni - s),
-                            lead.end - lead.start});
-    }
-    b->pixels += static_cast<uint64_t>(J.scan->frame.width) * J.scan->frame.height;
+    std::stable_sort(ivs.begin() + first, ivs.end(), [](const GInterval& x, const GInterval& y) {
+      return x.end - x.start > y.end - y.start;
+    });
     b->bytes += J.len;
-    if (ivs.size() > 0x7FFFFFF0u) return fail(MJD_EINVAL, "entropy batch holds too many intervals");
+  }
+  const size_t n_iv = ivs.size();
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, entropy_decode<false>, kThreads, 0) != hipSuccess || per_cu < 1)
+    per_cu = 1;
+  const int cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
+  const uint32_t split_over = split_threshold(ivs);
+  b->iv_index.resize(n_iv);
+  // Split intervals lie in whole chunks, so that chunk i of the batch is at
+  // byte i * kChunk of the data; the others follow them.
+  for (const GInterval& iv : ivs)
+    if (iv.end - iv.start > split_over) chunks += (static_cast<uint64_t>(iv.end - iv.start) + kPad) / kChunk + 1;
+  uint64_t units = chunks ? (chunks * kChunk + kTail) / 16 : 0;  // 16-byte units taken
+  uint32_t n_chunks = 0;
+  std::vector<uint32_t> skip_jobs, split_of;
+  split_of.reserve(chunks);
+  std::vector<GItem> split_items;
+  std::vector<GGroup> more_groups;
+  for (size_t j = 0; j < n; ++j) {
+    const size_t end = j + 1 < n ? b->first_interval[j + 1] : n_iv;
+    const uint32_t job = static_cast<uint32_t>(j), first_chunk = n_chunks;
+    size_t i = b->first_interval[j];
+    for (size_t k = i; k < end; ++k) {
+      GInterval& iv = ivs[k];
+      const uint32_t len = iv.end - iv.start;
+      b->iv_index[k] = iv.dst;
+      if (len > kTile) {
+        const uint32_t first = static_cast<uint32_t>(tiles.size());
+        for (uint32_t t = 0; t <= (len - 1) / kTile; ++t) tiles.push_back(GTile{static_cast<uint32_t>(k), t, first});
+      }
+      if (len > split_over) {
+        const uint32_t c = static_cast<uint32_t>((static_cast<uint64_t>(len) + kPad) / kChunk + 1);
+        iv.dst = n_chunks * (kChunk / 16);
+        split_of.insert(split_of.end(), c, static_cast<uint32_t>(splits.size()));
+        splits.push_back(GSplit{static_cast<uint32_t>(k), n_chunks, c});
+        n_chunks += c;
+        i = k + 1;  // the longest come first
+      } else {
+        iv.dst = static_cast<uint32_t>(units);
+        units += (static_cast<uint64_t>(len) + kPad + 15) / 16;
+        if (units > 0xFFFFFFFFu) return fail(MJD_ENOMEM, "entropy batch holds too many stream bytes");
+      }
+    }
+    if (n_chunks > first_chunk) {
+      skip_jobs.push_back(job);
+      const uint32_t parts = n_chunks * kParts;
+      uint32_t per = std::min(kThreads / gj[j].bpm, kGuessGroup);
+      for (uint32_t f = first_chunk; f < n_chunks; f += per) groups.push_back(GGroup{job, f, std::min(per, n_chunks - f)});
+      per = kFollowGroup;
+      for (uint32_t f = first_chunk; f < n_chunks; f += per) more_groups.push_back(GGroup{job, f, std::min(per, n_chunks - f)});
+      for (uint32_t f = first_chunk * kParts; f < parts; f += kThreads)
+        split_items.push_back(GItem{job, f, std::min<uint32_t>(kThreads, parts - f), kPart});
+    }
+    for (; i < end; i += kThreads)
+      items.push_back(GItem{job, static_cast<uint32_t>(i), static_cast<uint32_t>(std::min<size_t>(kThreads, end - i)),
+                            ivs[i].end - ivs[i].start});
   }
   // longest items first, so that the last ones to start are short
   std::stable_sort(items.begin(), items.end(), [](const GItem& x, const GItem& y) { return x.bytes > y.bytes; });
-  b->iv_index.resize(ivs.size());
-  for (size_t i = 0; i < ivs.size(); ++i) b->iv_index[i] = ivs[i].index;
-  b->n_jobs = static_cast<uint32_t>(n);
-  b->n_intervals = static_cast<uint32_t>(ivs.size());
-  b->n_items = static_cast<uint32_t>(items.size());
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, entropy_kernel, kThreads, 0) != hipSuccess || per_cu < 1)
-    per_cu = 1;
-  b->grid = std::min<int>(static_cast<int>(items.size()), per_cu * (ctx->cu_count > 0 ? ctx->cu_count : 256));
-  if (hipMalloc(&b->d_tables, n * sizeof(GTables)) != hipSuccess ||
-      hipMalloc(&b->d_jobs, n * sizeof(GJob)) != hipSuccess ||
-      hipMalloc(&b->d_ivs, ivs.size() * sizeof(Interval)) != hipSuccess ||
-      hipMalloc(&b->d_items, items.size() * sizeof(GItem)) != hipSuccess ||
-      hipMalloc(&b->d_status, ivs.size() * sizeof(uint32_t)) != hipSuccess ||
-      hipMalloc(&b->d_counters, 2 * sizeof(unsigned)) != hipSuccess)
-    return fail(MJD_ENOMEM, "device allocation for the entropy batch tables failed");
-  for (size_t j = 0; j < n; ++j) gj[j].tables = b->d_tables + j;
-  if (hipMemcpy(b->d_tables, gt.data(), n * sizeof(GTables), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(b->d_jobs, gj.data(), n * sizeof(GJob), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(b->d_ivs, ivs.data(), ivs.size() * sizeof(Interval), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(b->d_items, items.data(), items.size() * sizeof(GItem), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemset(b->d_status, 0, ivs.size() * sizeof(uint32_t)) != hipSuccess ||
-      hipMemset(b->d_counters, 0, 2 * sizeof(unsigned)) != hipSuccess)
+  const size_t n_split_items = split_items.size(), n_guess_groups = groups.size();
+  groups.insert(groups.end(), more_groups.begin(), more_groups.end());
+  items.insert(items.begin(), split_items.begin(), split_items.end());
+  // a workgroup of its own resolves each long split interval, so these come first
+  std::vector<uint32_t> order(splits.size()), place(splits.size());
+  for (size_t k = 0; k < order.size(); ++k) order[k] = static_cast<uint32_t>(k);
+  const auto is_long = [&](uint32_t k) { return splits[k].n_chunks > kLongSplit; };
+  const uint32_t n_long = static_cast<uint32_t>(std::stable_partition(order.begin(), order.end(), is_long) - order.begin());
+  if (n_long && n_long < splits.size()) {
+    std::vector<GSplit> sorted(splits.size());
+    for (size_t k = 0; k < order.size(); ++k) {
+      sorted[k] = splits[order[k]];
+      place[order[k]] = static_cast<uint32_t>(k);
+    }
+    splits.swap(sorted);
+    for (uint32_t& k : split_of) k = place[k];
+  }
+  b->grid = std::min<int>(static_cast<int>(items.size() - n_split_items), per_cu * cus);
+  b->split_grid = std::min<int>(static_cast<int>(n_split_items), 2 * cus);
+  // one allocation: what the host fills first, then what the kernels write
+  Layout mem;
+  const uint64_t o_jobs = mem.add(n * sizeof(GJob)), o_tables = mem.add(n * sizeof(FastTables)), o_codes = mem.add(n * sizeof(GTables)),
+                 o_ivs = mem.add(n_iv * sizeof(GInterval)), o_tiles = mem.add(tiles.size() * sizeof(GTile)),
+                 o_splits = mem.add(splits.size() * sizeof(GSplit)), o_groups = mem.add(groups.size() * sizeof(GGroup)),
+                 o_split_of = mem.add(split_of.size() * sizeof(uint32_t)),
+                 o_items = mem.add(items.size() * sizeof(GItem)),
+                 o_skip_jobs = mem.add(skip_jobs.size() * sizeof(uint32_t)), o_counters = mem.add(4 * sizeof(unsigned)),
+                 o_status = mem.add(n_iv * sizeof(uint32_t));
+  const uint64_t upload = mem.size;
+  const uint64_t o_bytes = mem.add(n_iv * sizeof(uint32_t)), o_kept = mem.add(tiles.size() * sizeof(uint32_t)),
+                 o_states = mem.add(chunks * kSlots * sizeof(uint32_t)),
+                 o_links = mem.add(chunks * kSlots), o_hops = mem.add(chunks * kSlots * kParts * sizeof(GHop)),
+                 o_tasks = mem.add(chunks * kParts * sizeof(GTask)),
+                 o_skip = mem.add(skip_jobs.size() * kTableSlots * kSkipEntries * sizeof(uint16_t)),
+                 o_data = mem.add(units * 16);
+  if (hipMalloc(&b->d_mem, mem.size) != hipSuccess)
+    return fail(MJD_ENOMEM, "device allocation for the entropy batch failed");
+  uint8_t* d = b->d_mem;
+  for (size_t j = 0; j < n; ++j) {
+    gj[j].tables = reinterpret_cast<const FastTables*>(d + o_tables) + j;
+    gj[j].codes = (reinterpret_cast<const GTables*>(d + o_codes) + j)->t;
+  }
+  for (size_t i = 0; i < skip_jobs.size(); ++i)
+    gj[skip_jobs[i]].skip = reinterpret_cast<uint16_t*>(d + o_skip) + i * kTableSlots * kSkipEntries;
+  std::vector<uint8_t> host(upload);
+  auto fill = [&](uint64_t at, const void* from, size_t bytes) {
+    if (bytes) memcpy(host.data() + at, from, bytes);
+  };
+  fill(o_jobs, gj.data(), n * sizeof(GJob));
+  fill(o_tables, ft.data(), n * sizeof(FastTables));
+  fill(o_codes, gt.data(), n * sizeof(GTables));
+  fill(o_ivs, ivs.data(), n_iv * sizeof(GInterval));
+  fill(o_tiles, tiles.data(), tiles.size() * sizeof(GTile));
+  fill(o_splits, splits.data(), splits.size() * sizeof(GSplit));
+  fill(o_groups, groups.data(), groups.size() * sizeof(GGroup));
+  fill(o_split_of, split_of.data(), split_of.size() * sizeof(uint32_t));
+  fill(o_items, items.data(), items.size() * sizeof(GItem));
+  fill(o_skip_jobs, skip_jobs.data(), skip_jobs.size() * sizeof(uint32_t));
+  memset(host.data() + o_status, 0xFF, n_iv * sizeof(uint32_t));  // kStatusOk; the counters are zero
+  if (hipMemcpy(d, host.data(), upload, hipMemcpyHostToDevice) != hipSuccess)
     return fail(MJD_EDEVICE, "uploading the entropy batch tables failed");
+  GPlan& p = b->plan;
+  p.jobs = reinterpret_cast<const GJob*>(d + o_jobs);
+  p.ivs = reinterpret_cast<const GInterval*>(d + o_ivs);
+  p.tiles = reinterpret_cast<const GTile*>(d + o_tiles);
+  p.splits = reinterpret_cast<const GSplit*>(d + o_splits);
+  p.groups = reinterpret_cast<const GGroup*>(d + o_groups);
+  p.split_of = reinterpret_cast<const uint32_t*>(d + o_split_of);
+  p.items = reinterpret_cast<const GItem*>(d + o_items);
+  p.skip_jobs = reinterpret_cast<const uint32_t*>(d + o_skip_jobs);
+  p.n_skip = static_cast<uint32_t>(skip_jobs.size());
+  p.n_iv = static_cast<uint32_t>(n_iv);
+  p.n_tiles = static_cast<uint32_t>(tiles.size());
+  p.n_groups = static_cast<uint32_t>(n_guess_groups);
+  p.n_more_groups = static_cast<uint32_t>(more_groups.size());
+  p.n_splits = static_cast<uint32_t>(splits.size());
+  p.n_long = n_long;
+  p.n_items = static_cast<uint32_t>(items.size());
+  p.n_split_items = static_cast<uint32_t>(n_split_items);
+  p.data = d + o_data;
+  p.bytes = reinterpret_cast<uint32_t*>(d + o_bytes);
+  p.kept = reinterpret_cast<uint32_t*>(d + o_kept);
+  p.status = reinterpret_cast<uint32_t*>(d + o_status);
+  p.states = reinterpret_cast<uint32_t*>(d + o_states);
+  p.links = d + o_links;
+  p.hops = reinterpret_cast<GHop*>(d + o_hops);
+  p.tasks = reinterpret_cast<GTask*>(d + o_tasks);
+  p.counters = reinterpret_cast<unsigned*>(d + o_counters);
   return MJD_OK;
+}
+
+static hipError_t enqueue(const mjd_entropy_batch* b, hipStream_t s) {
+  const GPlan& p = b->plan;
+  const dim3 block(kThreads);
+  if (p.n_tiles) hipLaunchKernelGGL(entropy_destuff_count, dim3((p.n_tiles + kWaves - 1) / kWaves), block, 0, s, p);
+  const uint32_t skip_groups = p.n_skip * (kTableSlots * kSkipEntries / kThreads);
+  hipLaunchKernelGGL(entropy_destuff, dim3((p.n_iv + p.n_tiles + kWaves - 1) / kWaves + skip_groups), block, 0, s, p);
+  if (p.n_splits) {
+    hipLaunchKernelGGL(entropy_guess, dim3(p.n_groups), block, 0, s, p);
+    hipLaunchKernelGGL(entropy_follow, dim3(p.n_more_groups), block, 0, s, p);
+    if (p.n_long) hipLaunchKernelGGL(entropy_resolve<1024>, dim3(p.n_long), dim3(1024), 0, s, p);
+    const uint32_t rest = p.n_splits - p.n_long;
+    if (rest) hipLaunchKernelGGL(entropy_resolve<64>, dim3((rest + kWaves - 1) / kWaves), block, 0, s, p);
+    hipLaunchKernelGGL(entropy_decode<true>, dim3(b->split_grid), block, 0, s, p);
+  }
+  if (b->grid) hipLaunchKernelGGL(entropy_decode<false>, dim3(b->grid), block, 0, s, p);
+  return hipGetLastError();
 }
 
 }  // namespace gent
@@ -335,7 +1395,7 @@ int mjd_entropy_batch_create(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n
   int rc = mjd::gent::build(ctx, jobs, n, b);
   if (cur != ctx->device) (void)hipSetDevice(cur);
   if (rc != MJD_OK) {
-    mjd::gent::free_batch(b);
+    if (b->d_mem) (void)hipFree(b->d_mem);
     delete b;
     return rc;
   }
@@ -349,10 +1409,7 @@ int mjd_entropy_batch_launch(mjd_entropy_batch* b, void* stream) {
   (void)hipGetDevice(&cur);
   if (cur != b->ctx->device && hipSetDevice(b->ctx->device) != hipSuccess)
     return mjd::fail(MJD_EDEVICE, "hipSetDevice(%d) failed", b->ctx->device);
-  hipLaunchKernelGGL(mjd::gent::entropy_kernel, dim3(b->grid), dim3(mjd::gent::kThreads), 0,
-                     static_cast<hipStream_t>(stream), b->d_jobs, b->d_ivs, b->d_items, static_cast<int>(b->n_items),
-                     b->d_status, b->d_counters);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = mjd::gent::enqueue(b, static_cast<hipStream_t>(stream));
   if (cur != b->ctx->device) (void)hipSetDevice(cur);
   if (e != hipSuccess) return mjd::fail(MJD_EDEVICE, "entropy kernel launch failed: %s", hipGetErrorString(e));
   return MJD_OK;
@@ -365,28 +1422,28 @@ int mjd_entropy_batch_status(mjd_entropy_batch* b, int64_t* bad_job) {
   (void)hipGetDevice(&cur);
   if (cur != b->ctx->device && hipSetDevice(b->ctx->device) != hipSuccess)
     return mjd::fail(MJD_EDEVICE, "hipSetDevice(%d) failed", b->ctx->device);
-  std::vector<uint32_t> st(b->n_intervals);
+  std::vector<uint32_t> st(b->plan.n_iv);
   hipError_t e = hipDeviceSynchronize();
-  if (e == hipSuccess) e = hipMemcpy(st.data(), b->d_status, st.size() * sizeof(uint32_t), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = hipMemcpy(st.data(), b->plan.status, st.size() * sizeof(uint32_t), hipMemcpyDeviceToHost);
   if (cur != b->ctx->device) (void)hipSetDevice(cur);
   if (e != hipSuccess) return mjd::fail(MJD_EDEVICE, "reading the entropy status failed: %s", hipGetErrorString(e));
-  for (uint32_t i = 0; i < b->n_intervals; ++i) {
-    if (!st[i]) continue;
+  for (uint32_t i = 0; i < b->plan.n_iv; ++i) {
+    if (st[i] == mjd::gent::kStatusOk) continue;
     const auto it = std::upper_bound(b->first_interval.begin(), b->first_interval.end(), i);
     const int64_t job = static_cast<int64_t>(it - b->first_interval.begin()) - 1;
     if (bad_job) *bad_job = job;
     static const char* what[] = {"", "an invalid Huffman code", "a coefficient run past the end of a block",
                                  "an interval that ends before its last MCU"};
     return mjd::fail(MJD_ECORRUPT, "job %lld, restart interval %u: %s", static_cast<long long>(job),
-                     b->iv_index[i], what[st[i] < 4 ? st[i] : 1]);
+                     b->iv_index[i], what[st[i] & 3u]);
   }
   return MJD_OK;
 }
 
 int mjd_entropy_batch_info(const mjd_entropy_batch* b, uint32_t* intervals, uint32_t* workgroups, uint64_t* bytes) {
   if (!b) return mjd::fail(MJD_EINVAL, "null entropy batch");
-  if (intervals) *intervals = b->n_intervals;
-  if (workgroups) *workgroups = static_cast<uint32_t>(b->grid);
+  if (intervals) *intervals = b->plan.n_iv;
+  if (workgroups) *workgroups = static_cast<uint32_t>(b->grid + b->split_grid);
   if (bytes) *bytes = b->bytes;
   return MJD_OK;
 }
@@ -397,7 +1454,7 @@ void mjd_entropy_batch_destroy(mjd_entropy_batch* b) {
   (void)hipGetDevice(&cur);
   if (cur != b->ctx->device) (void)hipSetDevice(b->ctx->device);
   (void)hipDeviceSynchronize();
-  mjd::gent::free_batch(b);
+  if (b->d_mem) (void)hipFree(b->d_mem);
   if (cur != b->ctx->device) (void)hipSetDevice(cur);
   delete b;
 }

@@ -48,13 +48,21 @@ struct Interval {
 };
 
 // Entry of the first-level table (index: the next kGLook bits):
-//   0                no code of at most kGLook bits starts there
-//   bits 0-4         code length
+//   0                no code of at most kGLook bits starts there, or a DC
+//                    symbol above 11
+//   bits 0-4         bits of the code and the magnitude together
 //   bits 5-8         magnitude size (AC: low nibble of the symbol; DC: the
-//                    symbol); size 0 in an AC table is EOB, or ZRL with run 15
-//   bits 9-12        zero run (AC: high nibble of the symbol)
-//   kBadSym          a DC symbol above 11
-constexpr uint32_t kBadSym = 1u << 13;
+//                    symbol); size 0 in an AC table is EOB or ZRL
+//   bits 9-15        how far the symbol moves the zig-zag position: the AC
+//                    zero run + 1, 16 for ZRL, kEobStep for EOB, 1 for DC
+constexpr uint32_t kEobStep = 64;
+
+MJD_HD inline uint32_t table_entry(uint32_t length, uint32_t sym, bool ac) {
+  const uint32_t size = sym & 15u;
+  if (!ac) return sym > 11 ? 0u : (length + size) | size << 5 | 1u << 9;
+  const uint32_t step = sym == 0 || (size == 0 && sym < 0xF0) ? kEobStep : (sym >> 4) + 1;
+  return (length + size) | size << 5 | step << 9;
+}
 
 struct GHuff {
   uint16_t fast[1 << kGLook];
@@ -95,9 +103,7 @@ inline int build_gtable(const mjd_huffman& h, bool ac, GHuff* t) {
     for (int i = 0; i < h.bits[l - 1]; ++i) {
       if (code >= (1 << l)) return kTableOverfull;
       if (l <= kGLook) {
-        const uint32_t sym = h.vals[k];
-        const uint32_t e = ac ? static_cast<uint32_t>(l) | (sym & 15u) << 5 | (sym >> 4) << 9
-                              : static_cast<uint32_t>(l) | (sym & 15u) << 5 | (sym > 11 ? kBadSym : 0u);
+        const uint32_t e = table_entry(static_cast<uint32_t>(l), h.vals[k], ac);
         const int lo = code << (kGLook - l), hi = (code + 1) << (kGLook - l);
         for (int p = lo; p < hi; ++p) t->fast[p] = static_cast<uint16_t>(e);
       }
@@ -298,6 +304,20 @@ struct LaneState {
   int pred0 = 0, pred1 = 0, pred2 = 0;
 };
 
+// The table entry of a code longer than kGLook bits at the front of `top`
+// (0: no code there, or a DC symbol above 11): its length is one more than
+// the number of left-aligned limits that the next 16 bits reach.
+template <class Tab>
+MJD_HD inline uint32_t long_entry(const Tab& tab, int t, uint32_t top, bool ac) {
+  const int w = static_cast<int>(top >> 16);
+  int l = kGLook + 1;
+  for (int j = kGLook + 1; j <= 16; ++j) l += w >= tab.lim(t, j) ? 1 : 0;
+  const int lc = l > 16 ? 16 : l;
+  const int idx = (w >> (16 - lc)) + tab.valoff(t, lc);
+  if (l > 16 || idx < 0 || idx > 255) return 0;
+  return table_entry(static_cast<uint32_t>(lc), static_cast<uint32_t>(tab.val(t, idx)), ac);
+}
+
 // One symbol of the lane's interval.  Tab supplies
 //   uint32_t fast(int t, int i), int lim(int t, int l), int valoff(int t, int l),
 //   int val(int t, int i), int nat(int k)
@@ -319,30 +339,15 @@ MJD_HD inline uint32_t lane_step(const Tab& tab, Blk& blk, LaneBits<Ring>& br, L
   uint32_t d0, d1, d2;
   br.fetch(d0, d1, d2);
   const uint32_t top = br.peek32();
-  const uint32_t e = tab.fast(t, static_cast<int>(top >> (32 - kGLook)));
-  uint32_t len = e & 31u, sz = (e >> 5) & 15u, run = (e >> 9) & 15u;
-  bool bad = (e & kBadSym) != 0;
-  if (e == 0) {
-    // a code longer than kGLook bits: its length is one more than the
-    // number of left-aligned limits the next 16 bits reach
-    const int w = static_cast<int>(top >> 16);
-    int l = kGLook + 1;
-    for (int j = kGLook + 1; j <= 16; ++j) l += w >= tab.lim(t, j) ? 1 : 0;
-    const int lc = l > 16 ? 16 : l;
-    const int idx = (w >> (16 - lc)) + tab.valoff(t, lc);
-    const bool ok = l <= 16 && idx >= 0 && idx <= 255;
-    const uint32_t sym = ok ? static_cast<uint32_t>(tab.val(t, idx)) : 0u;
-    bad = !ok || (dc && sym > 11);
-    len = static_cast<uint32_t>(lc);
-    sz = sym & 15u;
-    run = dc ? 0u : sym >> 4;
-    if (dc && sym > 15) sz = 0;
-  }
+  uint32_t e = tab.fast(t, static_cast<int>(top >> (32 - kGLook)));
+  if (e == 0) e = long_entry(tab, t, top, !dc);
+  const bool bad = e == 0;
+  const uint32_t total = e & 31u, sz = (e >> 5) & 15u, step = e >> 9;
   // the magnitude bits follow the code inside the 32-bit window
-  const int raw = sz ? static_cast<int>((top << len) >> (32 - sz)) : 0;
+  const int raw = sz ? static_cast<int>((top << (total - sz)) >> (32 - sz)) : 0;
   const int half = static_cast<int>((1u << sz) >> 1);
   int val = raw < half ? raw - 2 * half + 1 : raw;  // EXTEND (T.81 F.2.2.1)
-  br.consume(len + sz, d0, d1, d2);
+  br.consume(total, d0, d1, d2);
   if (dc) {
     // DC prediction per component (T.81 F.2.1.3), kept in three registers
     // and chosen by masks (a select would become an indexed stack load)
@@ -353,15 +358,14 @@ MJD_HD inline uint32_t lane_step(const Tab& tab, Blk& blk, LaneBits<Ring>& br, L
     st.pred2 = (p & m2) | (st.pred2 & ~m2);
     val = p;
   }
-  // A coefficient lands at k + run.  EOB (size 0, run below 15) and ZRL
-  // (size 0, run 15) write a zero at a position not yet reached, which is
-  // still zero, so the store stays unconditional.
+  // A coefficient lands at k + run.  EOB and ZRL (size 0) write a zero at a
+  // position not yet reached, which is still zero, so the store stays
+  // unconditional.
   const bool skip = !dc && sz == 0;
-  const int kk = st.k + static_cast<int>(run);
-  blk.put(tab.nat(kk < 63 ? kk : 63), skip ? 0 : val);
-  const bool eob = skip && run != 15;
+  const int kk = st.k + static_cast<int>(step) - 1;
+  blk.put(tab.nat(kk < 0 ? 0 : kk < 63 ? kk : 63), skip ? 0 : val);
   uint32_t status = bad ? kBadCode : (!skip && kk > 63) ? kBadRun : kRunning;
-  st.k = eob ? 64 : kk + 1;
+  st.k = kk + 1;
   if (status == kRunning && st.k >= 64) {
     blk.finish();
     st.k = 0;

@@ -1,0 +1,202 @@
+// Pieces of the GPU entropy decoder that work on destuffed data: the zero
+// byte that follows each 0xFF of a scan is dropped beforehand, so a lane
+// takes its bits from plain words and one refill is one word.  Written for
+// one lane, through a table interface, so that a CPU caller can run them too.
+#pragma once
+
+#include "entropy_lane.h"
+
+namespace mjd {
+namespace gent {
+
+// A window of two words (most significant bit first) over a word stream.
+// sh is the number of unread bits of w1's word that the 32-bit view leaves
+// out, 0..31; wi is the word that follows w1.
+struct BitWindow {
+  uint32_t w0, w1, wi;
+  int32_t sh;
+
+  // The next 32 bits.
+  MJD_HD uint32_t top() const {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_alignbit(w0, w1, static_cast<uint32_t>(sh));
+#else
+    return static_cast<uint32_t>((static_cast<uint64_t>(w0) << 32 | w1) >> sh);
+#endif
+  }
+  // Drops n <= 31 bits; `next` is word wi.
+  MJD_HD void drop(uint32_t n, uint32_t next) {
+    sh -= static_cast<int32_t>(n);
+    const bool over = sh < 0;
+    sh &= 31;
+    w0 = over ? w1 : w0;
+    w1 = over ? next : w1;
+    wi += over ? 1u : 0u;
+  }
+  // Position of the next unread bit, modulo 2^32 (callers compare positions
+  // that lie close together).
+  MJD_HD uint32_t pos() const { return 32u * (wi - 1u) - static_cast<uint32_t>(sh); }
+};
+
+// First word that a window at bit position 32 * word + bit needs, and the
+// window itself from words q - 1 and q (q = word, or word + 1 where bit > 0).
+MJD_HD inline uint32_t window_word(uint32_t word, uint32_t bit) { return word + (bit ? 1u : 0u); }
+MJD_HD inline BitWindow window_at(uint32_t word, uint32_t bit, uint32_t before, uint32_t at) {
+  const uint32_t q = window_word(word, bit);
+  return BitWindow{before, at, q + 1u, static_cast<int32_t>(32u * (q - word) - bit)};
+}
+
+// A Huffman table as the kernels keep it in LDS: one look-up by the next
+// kGLook bits, and one more where the code is longer.  An entry of `fast`
+// whose low five bits (the bits used) are zero leads to `more`:
+//   bits 5-7    further bits of the code to look at, n
+//   bits 8-15   half the index of the 2^n entries of that prefix
+// so a prefix takes as many entries as its longest code needs.  Entry 0 of
+// `more` is 0 and stands for a prefix that found no entries left: the
+// canonical code's limits then decide (long_entry).  Where no code begins,
+// the entry is kBadEntry: a magnitude size and a step that no valid entry has
+// together, so that a lane needs no test of its own for it.
+constexpr uint32_t kMore = 320;
+constexpr uint32_t kBadStep = 127;
+constexpr uint32_t kBadEntry = 16u | 15u << 5 | kBadStep << 9;
+constexpr uint32_t kBadPrefix = 1u << 8;  // n = 0 at entry 2, kBadEntry
+struct FastTable {
+  uint16_t fast[1 << kGLook];
+  uint16_t more[kMore];
+};
+// Positions past 63 (an EOB, or data that leaves the block) write to
+// coefficient 63.
+constexpr uint32_t kPlaces = 64 + kBadStep + 1;
+struct FastTables {
+  FastTable t[kTableSlots];
+  uint8_t nat2[kPlaces];  // byte offset in a block (twice the natural index) of zig-zag position k - 1
+};
+static_assert(sizeof(FastTables) % 16 == 0, "tables copy as 16-byte chunks");
+
+struct PlainTab {
+  const GHuff* tab;
+  MJD_HD uint32_t fast(int t, int i) const { return tab[t].fast[i]; }
+  MJD_HD int lim(int t, int l) const { return tab[t].lim[l]; }
+  MJD_HD int valoff(int t, int l) const { return tab[t].valoff[l]; }
+  MJD_HD int val(int t, int i) const { return tab[t].vals[i]; }
+};
+
+inline void build_fast_table(const GHuff& h, bool ac, FastTable* f) {
+  memset(f->more, 0, sizeof(f->more));
+  f->more[2] = kBadEntry;
+  for (uint32_t p = 0; p < 1u << kGLook; ++p) f->fast[p] = h.fast[p] ? h.fast[p] : static_cast<uint16_t>(kBadPrefix);
+  const PlainTab tab{&h};
+  uint32_t used = 3;
+  const uint32_t last = (static_cast<uint32_t>(h.lim[16]) + 63u) >> 6;
+  for (uint32_t p = static_cast<uint32_t>(h.lim[kGLook]) >> 6; p < last; ++p) {
+    uint32_t n = 0;  // bits past the prefix of its longest code
+    for (uint32_t v = 0; v < 64; ++v) {
+      const uint32_t e = long_entry(tab, 0, (p << 6 | v) << 16, ac);
+      const uint32_t len = (e & 31u) - ((e >> 5) & 15u);
+      if (e && len - kGLook > n) n = len - kGLook;
+    }
+    if (n == 0) continue;
+    const uint32_t at = (used + 1u) & ~1u;
+    if (at + (1u << n) > kMore) {
+      f->fast[p] = 0;
+      continue;
+    }
+    for (uint32_t v = 0; v < 1u << n; ++v) {
+      const uint32_t e = long_entry(tab, 0, (p << 6 | v << (6 - n)) << 16, ac);
+      f->more[at + v] = static_cast<uint16_t>(e ? e : kBadEntry);
+    }
+    f->fast[p] = static_cast<uint16_t>(n << 5 | at >> 1 << 8);
+    used = at + (1u << n);
+  }
+}
+
+inline void build_places(const uint8_t* natural, uint8_t nat2[kPlaces]) {
+  for (uint32_t k = 0; k < kPlaces; ++k) nat2[k] = static_cast<uint8_t>(2 * natural[k == 0 ? 0 : k < 64 ? k - 1 : 63]);
+}
+
+// The whole entry at the front of `top`, from its `fast` entry e, which uses
+// no bits; more(i) reads entry i of `more`.
+template <class More, class Tab>
+MJD_HD inline uint32_t more_entry(uint32_t e, uint32_t top, bool ac, const More& more, const Tab& tab, int t) {
+  const uint32_t n = e >> 5 & 7u;
+  const uint32_t m = more((e >> 8) * 2 + (static_cast<uint32_t>(static_cast<uint64_t>(top << kGLook) << n >> 32)));
+  if (m) return m;
+  const uint32_t l = long_entry(tab, t, top, ac);
+  return l ? l : kBadEntry;
+}
+
+// Several symbols at once, for lanes that only look for block boundaries:
+// what the next kSkipLook bits determine.
+//   0            not even one symbol
+//   bits 0-4     bits of all its symbols
+//   bits 5-10    how far they move the zig-zag position, an EOB left out
+//   bits 11-14   DC: the magnitude size of its one symbol
+//   bit 15       the last symbol is EOB
+// A lane whose position would leave the block by bits 5-10 takes one symbol.
+constexpr uint32_t kSkipLook = 11;
+constexpr uint32_t kSkipEntries = 1u << kSkipLook;
+
+template <class Entry>
+MJD_HD inline uint32_t skip_entry(uint32_t index, bool ac, const Entry& entry) {
+  const uint32_t top = index << (32 - kSkipLook);
+  uint32_t bits = 0, step = 0;
+  for (;;) {
+    const uint32_t e = entry(top << bits);
+    const uint32_t size = e >> 5 & 15u;
+    if (e == kBadEntry || bits + (e & 31u) - size > kSkipLook) break;  // no code among the known bits
+    if (!ac) return (e & 31u) | 1u << 5 | size << 11;
+    if (e >> 9 == kEobStep) return (bits + (e & 31u)) | step << 5 | 1u << 15;
+    if (step + (e >> 9) > 63) break;
+    bits += e & 31u;
+    step += e >> 9;
+    if (bits >= kSkipLook) break;
+  }
+  return bits | step << 5;
+}
+
+// The value whose `size` magnitude bits end `total` bits into `top` (T.81
+// F.2.2.1 EXTEND); 0 for size 0.
+MJD_HD inline int32_t entry_value(uint32_t top, uint32_t total, uint32_t size) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const int32_t raw = static_cast<int32_t>(__builtin_amdgcn_ubfe(top, 32u - total, size));
+#else
+  const int32_t raw = size ? static_cast<int32_t>((top >> (32u - total)) & ((1u << size) - 1u)) : 0;
+#endif
+  const int32_t mask = static_cast<int32_t>((1u << size) - 1u);
+  return raw > (mask >> 1) ? raw : raw - mask;
+}
+
+// A split interval is cut into chunks of destuffed bytes.  A state names a
+// block boundary at or after a byte of it: the bits from there, and the block
+// of the MCU that begins at the boundary.
+constexpr uint32_t kNoState = 0xFFFFFFFFu;
+MJD_HD inline uint32_t make_state(uint32_t bits, uint32_t b) { return bits << 3 | b; }
+
+// Slots of a chunk: the exits of the chunk before it for each first block
+// that is tried there, and two for boundaries that none of them reached.
+constexpr uint32_t kGuesses = 6, kSlots = 8;
+constexpr uint32_t kNoLink = 15;
+
+// Maps of a chunk's slots to the next chunk's, four bits a slot; anything
+// above 7 is no slot.
+constexpr uint32_t kSameSlots = 0x76543210u;
+MJD_HD inline uint32_t map_of_links(uint64_t links) {
+  uint32_t m = 0;
+  for (uint32_t i = 0; i < kSlots; ++i) {
+    const uint32_t v = static_cast<uint32_t>(links >> (8 * i)) & 0xFFu;
+    m |= (v < kSlots ? v : kNoLink) << (4 * i);
+  }
+  return m;
+}
+// First `a`, then `b`.
+MJD_HD inline uint32_t map_then(uint32_t a, uint32_t b) {
+  uint32_t m = 0;
+  for (uint32_t i = 0; i < kSlots; ++i) {
+    const uint32_t j = (a >> (4 * i)) & 15u;
+    m |= (j < kSlots ? (b >> (4 * j)) & 15u : kNoLink) << (4 * i);
+  }
+  return m;
+}
+
+}  // namespace gent
+}  // namespace mjd
