@@ -4,6 +4,7 @@ chroma upsampling -> YCbCr->RGB as one fused HIP kernel behind a C ABI
 """
 from __future__ import annotations
 
+from ._binding import _geometry, _variant_geometry
 from ._binding import (MJD_IDCT_FLOAT, MJD_IDCT_IFAST, MJD_IDCT_ISLOW, MJD_PART_OVERLAP, MJD_PART_PPS, MJD_PART_SPS, MJD_SERVE_CONTINUOUS, MJD_SERVE_SYNC,  # noqa: F401
                        MJD_UPSAMPLE_FANCY, MJD_UPSAMPLE_SIMPLE,
                        Batch, Context, EntropyBatch, Hetero, MjdError, Pipeline, Server, make_variant, mjd_decode_variant, mjd_partition_rows,
@@ -29,8 +30,9 @@ def decode(ctx: Context, frame, coef, qt, mode: str = "fancy", out=None, rows=No
 
     if frame.get("ncomp", 3) != 3:
         raise ValueError("grayscale frames decode with decode_variant(..., ncomp=1)")
-    g = mjd_geometry_of(frame)
-    if coef.numel() != g["n_blocks"] * 64 or coef.element_size() != 2 or not coef.is_cuda:
+    f = make_frame(frame)
+    g = _geometry(f)
+    if coef.numel() != g.n_blocks * 64 or coef.element_size() != 2 or not coef.is_cuda:
         raise ValueError("coef must be a CUDA int16 tensor of n_blocks*64 elements")
     if qt.numel() != 256 or qt.element_size() != 2 or not qt.is_cuda:
         raise ValueError("qt must be a CUDA 16-bit tensor of 4*64 entries")
@@ -41,8 +43,8 @@ def decode(ctx: Context, frame, coef, qt, mode: str = "fancy", out=None, rows=No
         out = torch.empty((h, w, 3), dtype=torch.uint8, device=coef.device)
     if out.shape != (h, w, 3) or out.dtype != torch.uint8 or not out.is_contiguous():
         raise ValueError("out must be a contiguous uint8 tensor [H, W, 3]")
-    r0, r1 = rows if rows is not None else (0, g["mcus_y"])
-    mjd_decode(ctx, frame, coef, qt, UPSAMPLE[mode], out, 3 * w, r0, r1, stream)
+    r0, r1 = rows if rows is not None else (0, g.mcus_y)
+    mjd_decode(ctx, f, coef, qt, UPSAMPLE[mode], out, 3 * w, r0, r1, stream)
     return out
 
 
@@ -56,8 +58,8 @@ def decode_variant(ctx: Context, frame, coef, qt, idct: str = "islow", mode: str
     import torch
 
     v = make_variant(frame, ncomp, idct, mode, scale)
-    g, wb = mjd_variant_geometry(v)
-    if coef.numel() != g["n_blocks"] * 64 or coef.element_size() != 2 or not coef.is_cuda:
+    g, wb = _variant_geometry(v)
+    if coef.numel() != g.n_blocks * 64 or coef.element_size() != 2 or not coef.is_cuda:
         raise ValueError("coef must be a CUDA int16 tensor of n_blocks*64 elements")
     if qt.numel() != 256 or qt.element_size() != 2 or not qt.is_cuda:
         raise ValueError("qt must be a CUDA 16-bit tensor of 4*64 entries")
@@ -67,7 +69,7 @@ def decode_variant(ctx: Context, frame, coef, qt, idct: str = "islow", mode: str
         out = torch.empty(shape, dtype=torch.uint8, device=coef.device)
     if tuple(out.shape) != shape or out.dtype != torch.uint8 or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous uint8 tensor {shape}")
-    work = torch.empty(max(wb, 16), dtype=torch.uint8, device=coef.device)
+    work = torch.empty(wb, dtype=torch.uint8, device=coef.device) if wb else None
     mjd_decode_variant(ctx, v, coef, qt, out, ncomp * w, work, wb, stream)
     return out
 

@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "_lib", "libmjd.so")
@@ -281,18 +282,26 @@ def _check(rc: int):
         raise MjdError(rc, mjd_last_error())
 
 
+_FRAME = struct.Struct("<II10B2x")
+assert _FRAME.size == ctypes.sizeof(mjd_frame)
+
+
 def make_frame(frame) -> mjd_frame:
     """dict {width, height, h, v, qsel} (or an mjd_frame) -> mjd_frame."""
     if isinstance(frame, mjd_frame):
         return frame
     f = mjd_frame()
-    f.width = int(frame["width"])
-    f.height = int(frame["height"])
-    for c in range(3):
-        f.h[c] = int(frame["h"][c])
-        f.v[c] = int(frame["v"][c])
-        f.qsel[c] = int(frame.get("qsel", (0, 1, 1))[c])
-    f.reserved = 0
+    h, v, q = frame["h"], frame["v"], frame.get("qsel", (0, 1, 1))
+    try:
+        _FRAME.pack_into(f, 0, frame["width"], frame["height"], h[0], h[1], h[2], v[0], v[1], v[2], q[0], q[1], q[2], 0)
+    except (struct.error, TypeError):  # other number types, values that C truncates
+        f.width = int(frame["width"])
+        f.height = int(frame["height"])
+        for c in range(3):
+            f.h[c] = int(h[c])
+            f.v[c] = int(v[c])
+            f.qsel[c] = int(q[c])
+        f.reserved = 0
     return f
 
 
@@ -302,23 +311,45 @@ def _ptr(x) -> int:
         return 0
     if isinstance(x, int):
         return x
-    if hasattr(x, "data_ptr"):
-        return int(x.data_ptr())
+    p = getattr(x, "data_ptr", None)
+    if p is not None:
+        return int(p())
     return int(x.ctypes.data)
+
+
+_torch = None
+
+
+def _current_stream() -> int:
+    """The current torch stream's handle, without the Stream object that
+    torch.cuda.current_stream() makes (2.9 us, as long as the rest of a call
+    on a small image) where this torch offers that."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    raw = getattr(_torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not _torch.cuda.is_initialized():
+        return int(_torch.cuda.current_stream().cuda_stream)
+    return int(raw(_torch._C._cuda_getDevice()))
 
 
 def _stream(s) -> int:
     if s is None:
-        import torch
-        return int(torch.cuda.current_stream().cuda_stream)
+        return _current_stream()
     if isinstance(s, int):
         return s
     return int(s.cuda_stream)
 
 
-def mjd_geometry_of(frame) -> dict:
+def _geometry(frame: mjd_frame) -> mjd_geometry:
     g = mjd_geometry()
-    _check(lib().mjd_geometry_of(ctypes.byref(make_frame(frame)), ctypes.byref(g)))
+    _check(lib().mjd_geometry_of(ctypes.byref(frame), ctypes.byref(g)))
+    return g
+
+
+def mjd_geometry_of(frame) -> dict:
+    g = _geometry(make_frame(frame))
     return {"mcu_w": g.mcu_w, "mcu_h": g.mcu_h, "mcus_x": g.mcus_x, "mcus_y": g.mcus_y,
             "blocks_per_mcu": g.blocks_per_mcu, "comp_w": list(g.comp_w), "comp_h": list(g.comp_h),
             "n_blocks": g.n_blocks}
@@ -394,14 +425,29 @@ def mjd_copy(ctx: Context, dst, src, nbytes: int, stream=None):
     _check(lib().mjd_copy(ctx.handle, _ptr(dst), _ptr(src), int(nbytes), _stream(stream)))
 
 
+# An mjd_job as bytes: width, height; h, v, qsel, reserved; four 64-bit words.
+_JOB = struct.Struct("<II10B6x4Q")
+assert _JOB.size == ctypes.sizeof(mjd_job)
+
+
 def _job_array(jobs):
+    """The jobs as a C array.  Ctypes takes 7 us a job field by field, the
+    packing 2, which is most of a call on small images (32 of them: 74 us with
+    the one, of which the kernel's 43); what it does not take as it is (other
+    number types, values that C truncates, an mjd_frame) goes field by field."""
     arr = (mjd_job * len(jobs))()
     for i, (frame, coef, qt, rgb, pitch) in enumerate(jobs):
-        arr[i].frame = make_frame(frame)
-        arr[i].d_coef = _ptr(coef)
-        arr[i].d_qt = _ptr(qt)
-        arr[i].d_rgb = _ptr(rgb)
-        arr[i].pitch = int(pitch)
+        try:
+            h, v = frame["h"], frame["v"]
+            q = frame.get("qsel", (0, 1, 1))
+            _JOB.pack_into(arr, i * 56, frame["width"], frame["height"], h[0], h[1], h[2], v[0], v[1], v[2],
+                           q[0], q[1], q[2], 0, _ptr(coef), _ptr(qt), _ptr(rgb), pitch)
+        except (struct.error, TypeError, AttributeError):
+            arr[i].frame = make_frame(frame)
+            arr[i].d_coef = _ptr(coef)
+            arr[i].d_qt = _ptr(qt)
+            arr[i].d_rgb = _ptr(rgb)
+            arr[i].pitch = int(pitch)
     return arr
 
 
@@ -636,14 +682,20 @@ def make_variant(frame, ncomp: int = 3, idct: str = "islow", mode: str = "fancy"
                        upsample=MJD_UPSAMPLE_FANCY if mode == "fancy" else MJD_UPSAMPLE_SIMPLE, scale=int(scale))
 
 
-def mjd_variant_geometry(variant: mjd_variant) -> tuple:
-    """-> (geometry dict, workspace bytes)."""
+def _variant_geometry(variant: mjd_variant) -> tuple:
+    """-> (mjd_geometry, workspace bytes)."""
     g = mjd_geometry()
     wb = ctypes.c_uint64()
     _check(lib().mjd_variant_geometry(ctypes.byref(variant), ctypes.byref(g), ctypes.byref(wb)))
+    return g, wb.value
+
+
+def mjd_variant_geometry(variant: mjd_variant) -> tuple:
+    """-> (geometry dict, workspace bytes)."""
+    g, work = _variant_geometry(variant)
     return ({"mcu_w": g.mcu_w, "mcu_h": g.mcu_h, "mcus_x": g.mcus_x, "mcus_y": g.mcus_y,
              "blocks_per_mcu": g.blocks_per_mcu, "comp_w": list(g.comp_w), "comp_h": list(g.comp_h),
-             "n_blocks": g.n_blocks}, wb.value)
+             "n_blocks": g.n_blocks}, work)
 
 
 def mjd_decode_variant(ctx: Context, variant: mjd_variant, coef, qt, out, pitch: int, work, work_bytes: int,
