@@ -39,12 +39,14 @@ __global__ __launch_bounds__(kBatchThreads, 2) void decode_batch(const ImageView
   __shared__ __align__(16) uint8_t lds[kBatchLds];
   __shared__ int s_next;
   const int tid = static_cast<int>(threadIdx.x);
-  for (;;) {
-    if (tid == 0) s_next = static_cast<int>(atomicAdd(&counters[0], 1u));
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(s_next);
-    __syncthreads();  // every lane has read s_next before it is overwritten
-    if (it >= n_items) break;
+  // The first segment is the workgroup's number; the counter deals those
+  // after the grid's.  The next one is asked for before a segment is decoded,
+  // so no segment waits for the counter (512 workgroups that ask at once wait
+  // 4 us for each other).
+  int it = static_cast<int>(blockIdx.x);
+  while (it < n_items) {
+    int next = 0;
+    if (tid == 0) next = static_cast<int>(gridDim.x + atomicAdd(&counters[0], 1u));
     const BatchItem bi = items[it];
     // a reference into the device table (scalar loads), not a local copy,
     // which would have to live in scratch memory behind the decoder's
@@ -81,10 +83,15 @@ __global__ __launch_bounds__(kBatchThreads, 2) void decode_batch(const ImageView
         break;
       }
     }
+    if (tid == 0) s_next = next;
+    __syncthreads();
+    it = __builtin_amdgcn_readfirstlane(s_next);  // the next run's first barrier comes before it changes again
   }
-  // the last workgroup out rearms the queue for the next launch
+  // The last workgroup out rearms the queue for the next launch.  No fence:
+  // each workgroup's own requests have returned before it reports, and a fence
+  // here writes back the whole L2 of its XCD, once a workgroup, while others
+  // still store (768 segments of one 4096x1536 image: 42 us with it).
   if (tid == 0) {
-    __threadfence();
     const unsigned done = atomicAdd(&counters[1], 1u);
     if (done == gridDim.x - 1) {
       atomicExch(&counters[0], 0u);
@@ -154,11 +161,14 @@ int batch_plan(mjd_ctx* ctx, const mjd_job* jobs, size_t n, int upsample, BatchP
   }
   const int slots = batch_slots(ctx);
   // Segment length: about 4 segments per resident workgroup over the whole
-  // batch, so the queue balances the tail; the tuning knob overrides it.
+  // batch, so the queue balances the tail, and at most 6 sub-tiles, past which
+  // the tail costs more than the segments' ends (48 mixed images of 252 MP:
+  // 530 us with 6, 541 with 12, 575 with 26, which 4 a workgroup gives); the
+  // tuning knob overrides it.
   int seg_sub = static_cast<int>(ctx->tuning.seg_subtiles);
   if (seg_sub <= 0) {
     const uint64_t want = static_cast<uint64_t>(slots) * 4;
-    seg_sub = static_cast<int>(std::max<uint64_t>(1, (subtiles + want - 1) / want));
+    seg_sub = static_cast<int>(std::min<uint64_t>(6, std::max<uint64_t>(1, (subtiles + want - 1) / want)));
   }
   for (size_t i = 0; i < n; ++i) {
     int sx, sy;

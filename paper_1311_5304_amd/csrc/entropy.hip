@@ -1056,9 +1056,11 @@ __global__ __launch_bounds__(kThreads, SPLIT ? 2 : 3) void entropy_decode(const 
       wave_sync();
     }
   }
-  // the last workgroup out rearms the queue for the next launch
+  // The last workgroup out rearms the queue for the next launch.  No fence:
+  // each workgroup's own requests have returned before it reports, and a fence
+  // here writes back the whole L2 of its XCD, once a workgroup, while others
+  // still store.
   if (tid == 0) {
-    __threadfence();
     const unsigned done = atomicAdd(&counters[1], 1u);
     if (done == gridDim.x - 1) {
       atomicExch(&counters[0], 0u);
