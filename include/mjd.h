@@ -193,10 +193,9 @@ int mjd_decode_host(const mjd_frame* frame, const int16_t* h_coef, const uint16_
  * integer-or-float IDCTs; Sec. 4.2 decodes samplings other than 4:4:4 and
  * 4:2:2 the same way).  Full-size colour images decode in one launch of
  * the fused segment kernel for their sampling and IDCT method (no sample
- * planes in memory, no workspace).  Grayscale decodes in one launch that
- * writes its rows directly; scaled decodes use two launches: dequantise +
- * reduced IDCT into per-component sample planes in a caller workspace,
- * then upsampling + colour conversion.
+ * planes in memory, no workspace), scaled images in one launch of a tile
+ * kernel that keeps the reduced samples in the LDS, and grayscale in one
+ * launch that writes its rows directly.
  * IDCT methods:
  *   MJD_IDCT_ISLOW  LL&M in 13-bit fixed point (mjd_decode's arithmetic);
  *   MJD_IDCT_IFAST  the AAN flowgraph (transposed forward graph) in fixed
@@ -227,7 +226,7 @@ typedef struct mjd_variant {
 /* Host only: validates `variant` and gives its geometry: the coefficient
  * layout (grayscale: 8x8 MCUs of one block), comp_w/comp_h at the output
  * scale (0 for absent components), and the workspace mjd_decode_variant
- * needs (0 for grayscale and for full-size colour images).  out and work_bytes
+ * asks for (0 for grayscale and for full-size colour images).  out and work_bytes
  * may be NULL.  MJD_EINVAL for bad fields, MJD_EUNSUPPORTED for other
  * samplings. */
 int mjd_variant_geometry(const mjd_variant* variant, mjd_geometry* out, uint64_t* work_bytes);
@@ -238,7 +237,7 @@ int mjd_variant_geometry(const mjd_variant* variant, mjd_geometry* out, uint64_t
  * scale), < 2^31; < 2^24 for full-size colour images), only each row's
  * first ncomp * ceil(W / scale) bytes written; d_work: device workspace of
  * at least the size mjd_variant_geometry gives, 16-byte aligned, owned by
- * the caller, overwritten (may be NULL when that size is 0).  A full-size
+ * the caller, contents undefined after the call (may be NULL when that size is 0).  A full-size
  * colour image runs with the context's tuning (segment length, workgroup
  * count; the shape index only where the sampling's islow kernel is
  * mjd_decode's), which changes speed only.  Asynchronous on `stream`.

@@ -52,8 +52,8 @@ def decode_variant(ctx: Context, frame, coef, qt, idct: str = "islow", mode: str
                    out=None, stream=None, scale: int = 1):
     """Decode one image through the variants path (IDCT method `idct`,
     samplings (1,1), (2,1), (1,2), (2,2), (4,1), or grayscale with ncomp=1;
-    output 1/scale of the image for scale 2, 4, 8).  Allocates the plane
-    workspace with torch.  Returns `out`: uint8 [H', W', 3], or [H', W'] for
+    output 1/scale of the image for scale 2, 4, 8).  Allocates the
+    call's workspace with torch.  Returns `out`: uint8 [H', W', 3], or [H', W'] for
     grayscale, H' = ceil(H / scale), W' = ceil(W / scale)."""
     import torch
 

@@ -50,9 +50,8 @@ int frame_geometry(const mjd_frame* f, mjd_geometry* g) {
   return MJD_OK;
 }
 
-// Geometry of a variant frame and the workspace its planes need.
-int variant_geometry(const mjd_variant* vr, mjd_geometry* g, uint64_t* work, uint32_t plane_pitch[3],
-                            uint64_t plane_off[3]) {
+// Geometry of a variant frame and the workspace its call is given.
+int variant_geometry(const mjd_variant* vr, mjd_geometry* g, uint64_t* work) {
   if (!vr || !g) return fail(MJD_EINVAL, "null variant or geometry pointer");
   const mjd_frame& f = vr->frame;
   if (f.reserved != 0) return fail(MJD_EINVAL, "reserved frame field must be 0");
@@ -87,8 +86,9 @@ int variant_geometry(const mjd_variant* vr, mjd_geometry* g, uint64_t* work, uin
   g->mcus_y = (f.height + g->mcu_h - 1) / g->mcu_h;
   g->blocks_per_mcu = nc == 1 ? 1 : hy * vy + 2;
   g->n_blocks = static_cast<uint64_t>(g->mcus_x) * g->mcus_y * g->blocks_per_mcu;
-  // component sizes at the output scale; planes of whole blocks of n
-  // samples, rows padded to 16 bytes
+  // component sizes at the output scale, and the workspace of a scaled colour
+  // image: planes of whole blocks of n samples, rows padded to 16 bytes (the
+  // size that the entry point has always asked for; its kernel needs none)
   const uint32_t n = 8 / scale;
   uint64_t total = 0;
   for (int c = 0; c < 3; ++c) {
@@ -96,10 +96,8 @@ int variant_geometry(const mjd_variant* vr, mjd_geometry* g, uint64_t* work, uin
     const uint32_t cw = (f.width * hc + hy - 1) / hy, ch = (f.height * vc + vy - 1) / vy;
     g->comp_w[c] = c < nc ? (cw + scale - 1) / scale : 0;
     g->comp_h[c] = c < nc ? (ch + scale - 1) / scale : 0;
-    plane_pitch[c] = (g->mcus_x * hc * n + 15) & ~15u;
-    plane_off[c] = total;
-    // full-size colour images decode in one fused pass: no planes
-    if (nc == 3 && scale > 1) total += (static_cast<uint64_t>(plane_pitch[c]) * g->mcus_y * vc * n + 255) & ~255ull;
+    const uint64_t plane_pitch = (g->mcus_x * hc * n + 15) & ~15u;
+    if (nc == 3 && scale > 1) total += (plane_pitch * g->mcus_y * vc * n + 255) & ~255ull;
   }
   *work = total;
   return MJD_OK;
@@ -118,10 +116,9 @@ int mjd_geometry_of(const mjd_frame* frame, mjd_geometry* out) {
 
 
 int mjd_variant_geometry(const mjd_variant* variant, mjd_geometry* out, uint64_t* work_bytes) {
-  uint32_t pp[3];
-  uint64_t po[3], wb = 0;
+  uint64_t wb = 0;
   mjd_geometry g;
-  const int rc = mjd::variant_geometry(variant, &g, &wb, pp, po);
+  const int rc = mjd::variant_geometry(variant, &g, &wb);
   if (rc != MJD_OK) return rc;
   if (out) *out = g;
   if (work_bytes) *work_bytes = wb;

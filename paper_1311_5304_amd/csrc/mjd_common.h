@@ -15,10 +15,9 @@ void clear_error();
 // Host-only frame validation + geometry (no HIP calls).
 int frame_geometry(const mjd_frame* f, mjd_geometry* g);
 
-// Geometry of a decoder-variant frame, the workspace its planes need, and
-// the planes' pitches and offsets in that workspace (no HIP calls).
-int variant_geometry(const mjd_variant* vr, mjd_geometry* g, uint64_t* work, uint32_t plane_pitch[3],
-                     uint64_t plane_off[3]);
+// Geometry of a decoder-variant frame and the workspace its call is given
+// (no HIP calls).
+int variant_geometry(const mjd_variant* vr, mjd_geometry* g, uint64_t* work);
 
 // HIP device of a context.
 int ctx_device(const mjd_ctx* ctx);

@@ -34,6 +34,10 @@ int shape_count(int hf, int vf, bool fancy);
 // whose islow kernel is the single-image kernel's shape list).
 hipError_t launch_variant(const ImageView& im, int hf, int vf, bool fancy, int idct, int cu_count,
                           const mjd_tuning& tu, hipStream_t stream);
+// Scaled decoding (scale 2, 4 or 8): the image of a validated variant, colour
+// or grayscale, in one launch.
+hipError_t launch_scaled(const mjd_variant& vr, const mjd_geometry& g, const int16_t* coef, const uint16_t* qt,
+                         uint8_t* out, uint32_t pitch, hipStream_t stream);
 hipError_t shape_info(int hf, int vf, bool fancy, int index, int* sx, int* sy, int* nt, int* lds_bytes, int* per_cu);
 
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);

@@ -303,3 +303,50 @@ def test_full_size_image(M, ctx, method):
     got = _run(M, ctx, frame, coef, qt, method, "fancy")
     exp = V.decode_variant(frame, coef, qt, method, "fancy")
     assert np.array_equal(got, exp), int((got != exp).sum())
+
+
+@pytest.mark.parametrize("scale", [2, 4, 8])
+@pytest.mark.parametrize("hy,vy,w,h", [(2, 2, 1031, 131), (2, 1, 1449, 67), (1, 2, 263, 227), (1, 1, 967, 65),
+                                       (4, 1, 1283, 66), (2, 2, 512, 128), (2, 1, 960, 64)])
+def test_scaled_tiles_meet_at_their_edges(M, ctx, scale, hy, vy, w, h):
+    # several tiles a side, the last ones of one MCU, and whole tiles; extreme
+    # coefficients on both sides of every tile edge; rows at odd addresses
+    fr = {"width": w, "height": h, "h": (hy, 1, 1), "v": (vy, 1, 1), "qsel": (2, 0, 1)}
+    coef, qt = _case(w + h + scale, fr)
+    cd = torch.from_numpy(coef.reshape(-1)).cuda()
+    qd = torch.from_numpy(qt.view(np.int16).reshape(-1)).cuda()
+    for mode in ("simple", "fancy"):
+        say(f"1/{scale} tiles {hy}x{vy} {w}x{h} {mode}")
+        v = M.make_variant(fr, 3, "islow", mode, scale)
+        _, wb = M.mjd_variant_geometry(v)
+        ow, oh = -(-w // scale), -(-h // scale)
+        pitch = 3 * ow + 7
+        buf = torch.full((oh * pitch + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        work = torch.empty(wb, dtype=torch.uint8, device="cuda")
+        M.mjd_decode_variant(ctx, v, cd, qd, buf.data_ptr() + 1, pitch, work, wb)
+        torch.cuda.synchronize()
+        b = buf.cpu().numpy()
+        rows = b[1:1 + oh * pitch].reshape(oh, pitch)
+        exp = V.decode_variant(fr, coef, qt, "islow", mode, scale)
+        assert np.array_equal(rows[:, :3 * ow].reshape(exp.shape), exp)
+        assert np.all(rows[:, 3 * ow:] == 0xA5) and b[0] == 0xA5 and np.all(b[1 + oh * pitch:] == 0xA5)
+
+
+@pytest.mark.parametrize("scale", [2, 4, 8])
+@pytest.mark.parametrize("top", [255, 256, 1155, 65535])
+def test_scaled_decoding_with_wide_quant_tables(M, ctx, scale, top):
+    # table entries on both sides of 8 bits, in one component's table alone
+    rng = np.random.default_rng(top + scale)
+    fr = {"width": 131, "height": 77, "h": (2, 1, 1), "v": (2, 1, 1), "qsel": (0, 1, 2)}
+    for table in range(3):
+        qt = rng.integers(1, 17, (4, 64)).astype(np.uint16)
+        qt[table, [0, 1, 8, 9, 11, 26]] = top
+        n = V.variant_geometry(fr)["n_blocks"]
+        lim = np.maximum(1155 // qt.max(axis=0).astype(np.int64), 1 if top <= 1155 else 0)
+        coef = rng.integers(-lim, lim + 1, (n, 64)).astype(np.int16)
+        say(f"1/{scale} table {table} entries up to {top}")
+        cd = torch.from_numpy(coef.reshape(-1)).cuda()
+        qd = torch.from_numpy(qt.view(np.int16).reshape(-1)).cuda()
+        for mode in ("simple", "fancy"):
+            got = M.decode_variant(ctx, fr, cd, qd, "islow", mode, scale=scale).cpu().numpy()
+            assert np.array_equal(got, V.decode_variant(fr, coef, qt, "islow", mode, scale))
