@@ -690,10 +690,11 @@ struct SegmentDecoder {
     constexpr int ITEMS = (C::CR / 2) * C::UX;
     static_assert(ITEMS % NT == 0, "the row pairs of a sub-tile fill the workgroup a whole number of times");
     const bool has_b = k >= 2;
-    // A segment of one sub-tile: its last pair takes the place of the tail
-    // pair there is none of, so the sub-tile's pairs are one round (as a
-    // second round, or as rows of its own after it, it doubled the phase).
-    const bool fold = K == 1;
+    // A segment of one sub-tile whose last pair is in this walk: the pair
+    // takes the place of the tail pair there is none of, so the sub-tile's
+    // pairs are one round, not two.  (Where the rows are spread over the
+    // waves instead, the test costs a 4096x3072 image 1% and gives nothing.)
+    const bool fold = LAST_IN_WALK && K == 1;
     const int n_items = ITEMS + (LAST_IN_WALK && k == K && !fold ? C::UX : 0);
     const SubInfo sa = uniform(sub_info(k - 1)), sb = uniform(sub_info(has_b ? k - 2 : 0));
     // every unit of the strip is whole: the plain store path alone
@@ -1216,7 +1217,7 @@ struct SegmentDecoder {
       // next step's barrier.
       if (k < K) phase1(k, h);
       if constexpr (HALO_Y && !LAST_IN_WALK)
-        if (k == K && K > 1) last_pair_rows();
+        if (k == K) last_pair_rows();
     }
   }
 };
