@@ -259,3 +259,28 @@ def test_launch_shapes_bit_exact(M, ctx, samp, mode):
                     assert np.all(got[:y0] == 5) and np.all(got[y1:] == 5)
     finally:
         M.mjd_ctx_set_tuning(ctx, 0, 0)
+
+
+@pytest.mark.parametrize("w,h", [(16, 8), (257, 190), (1921, 1081), (4096, 2048), (4096, 2208), (5000, 3000)])
+def test_422_fancy_default_shape_equals_every_shape(M, ctx, w, h):
+    # images on both sides of the rule that picks the shape by size, with the
+    # last segments and the last columns short
+    rng = np.random.default_rng(w)
+    frame = {"width": w, "height": h, "h": (2, 1, 1), "v": (1, 1, 1), "qsel": (0, 1, 1)}
+    n = M.mjd_geometry_of(frame)["n_blocks"]
+    coef = (rng.standard_normal((n, 64)) * (40 / (1 + np.arange(64)))).astype(np.int16)
+    qt = rng.integers(1, 17, (4, 64)).astype(np.uint16)
+    c, q = to_dev(coef, qt)
+    say(f"4:2:2 fancy {w}x{h}")
+    got = M.decode(ctx, frame, c, q, "fancy")
+    band = M.decode(ctx, frame, c, q, "fancy", rows=(0, (h + 7) // 8 // 2 + 1))
+    half = min(h, 8 * ((h + 7) // 8 // 2 + 1))
+    assert torch.equal(band[:half], got[:half])
+    if w * h < 100000:
+        assert_same(got.cpu().numpy(), oracle.decode(frame, coef, qt, "fancy"), f"{w}x{h}")
+    try:
+        for shape in range(M.mjd_shape_count(2, 1, M.MJD_UPSAMPLE_FANCY)):
+            M.mjd_ctx_set_tuning(ctx, 2, 0, shape)
+            assert torch.equal(M.decode(ctx, frame, c, q, "fancy"), got), shape
+    finally:
+        M.mjd_ctx_set_tuning(ctx, 0, 0, 0)
