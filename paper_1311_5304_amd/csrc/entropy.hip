@@ -80,7 +80,7 @@ struct GGroup {
 };
 
 // The part of the decoding that begins in one half of a chunk.
-constexpr uint32_t kParts = 2, kPart = kChunk / kParts;
+constexpr uint32_t kParts = 2, kPart = kChunk / kParts;  // entropy_follow counts two
 struct GTask {
   uint32_t iv;
   uint32_t word, bit_b;  // where it starts: word, bit | first block of the MCU << 8
@@ -351,24 +351,29 @@ __device__ __forceinline__ uint32_t table_of(uint32_t slots, uint32_t b) {
 }
 
 // Words of consecutive chunks, which a workgroup or a wave copies to LDS
-// before it decodes them: a lane then waits for no load.  One word in 33 is
-// left free, so that lanes at the same place of different chunks meet in no
-// bank.  A lane's words are counted from the start of its interval and end
-// with a zero word past the data.
+// before it decodes them: a lane then waits for no load.  A lane's words are
+// counted from the start of its interval and end with a zero word past the
+// data.  SPREAD leaves one word in 33 free, so that lanes at the same place
+// of different chunks meet in no bank; without it a word's address takes no
+// arithmetic.
+template <bool SPREAD>
+__host__ __device__ constexpr uint32_t staged_place(uint32_t i) { return SPREAD ? i + i / 32 : i; }
 constexpr uint32_t staged_size(uint32_t words) { return words + words / 32 + 1; }
 // Words that a block needs past the word of its first bit, the window's
 // included: a DC symbol of at most 27 bits and 63 of at most 31.
 constexpr uint32_t kBlockWords = (63 * 31 + 27 + 31) / 32 + 2;
 
 // Copies n words (a multiple of 4) from `src` on, by `lanes` lanes.
+template <bool SPREAD>
 __device__ __forceinline__ void stage_words(lds32* base, gin128* src, uint32_t n, uint32_t lane, uint32_t lanes) {
   for (uint32_t i = lane; i < n / 4; i += lanes) {
     const v4u_t v = src[i];
 #pragma unroll
-    for (uint32_t j = 0; j < 4; ++j) base[4 * i + j + i / 8] = swap_bytes(v[j]);
+    for (uint32_t j = 0; j < 4; ++j) base[staged_place<SPREAD>(4 * i + j)] = swap_bytes(v[j]);
   }
 }
 
+template <bool SPREAD>
 struct StagedWords {
   lds32* base;
   gin128* src;    // the interval's data
@@ -377,12 +382,11 @@ struct StagedWords {
   uint32_t zero;  // its zero word
 
   __device__ uint32_t staged(uint32_t w) const {
-    const uint32_t i = (w < zero ? w : zero) + off;
-    return base[i + i / 32];
+    return base[staged_place<SPREAD>((w < zero ? w : zero) + off)];
   }
   __device__ uint32_t word(uint32_t w) const {
     const uint32_t v = w < zero ? w : zero, i = v + off;
-    if (__builtin_expect(i < n, 1)) return base[i + i / 32];
+    if (__builtin_expect(i < n, 1)) return base[staged_place<SPREAD>(i)];
     return swap_bytes(((__attribute__((address_space(1))) const uint32_t*)src)[v]);
   }
   __device__ BitWindow open(uint32_t at, uint32_t bit) const {
@@ -472,63 +476,86 @@ __device__ __forceinline__ void load_skip_tables(const GJob& jb, lds_skip* to) {
   for (uint32_t i = threadIdx.x; i < kTableSlots * kSkipEntries / 8; i += kThreads) dst[i] = src[i];
 }
 
-// A lane on its way from a block boundary to another.
+// A lane on its way from a block boundary to another, over a copy of the
+// data.  A step's instructions are what it costs (a wave alone on its SIMD
+// issues one in five cycles, and a look-up's latency is that of twenty-five),
+// so whatever only a block's end needs waits for one: the position, the next
+// block's tables, the sum that its DC difference goes to.
 struct Walker {
   const lds_skip* tabs;
   const GHuff* codes;
-  uint32_t bpm, slots_dc, slots_ac, comp_bits;
-  BitWindow w;
-  uint32_t b, k;
-  uint32_t t, ac;  // slots of the next symbol's table and of the block's AC table
-  uint32_t comp;
-  uint32_t blocks, dc0, dc1, dc2;  // since start_counts()
+  uint32_t bpm2, slots_dc, slots_ac, comp_bits;
+  uint32_t w0, w1;  // the window, as in BitWindow
+  int32_t sh;
+  uint32_t at;      // byte offset in the copy of the word after w1's
+  uint32_t b2, k;   // twice the block of the MCU; the zig-zag position
+  uint32_t t, ac;   // slots of the next symbol's table and of the block's AC table
+  lds32* sums;      // of DC differences, a row of kThreads lanes for each component
+  uint32_t row;     // byte offset of the block's
+  uint32_t blocks;
 
-  __device__ Walker(const GJob& jb, const lds_skip* tabs_)
-      : tabs(tabs_), codes(jb.codes), bpm(jb.bpm), slots_dc(jb.dc_slots), slots_ac(jb.ac_slots), comp_bits(jb.comp_bits) {
-    start_counts();
+  __device__ Walker(const GJob& jb, const lds_skip* tabs_, lds32* sums_)
+      : tabs(tabs_), codes(jb.codes), bpm2(2 * jb.bpm), slots_dc(jb.dc_slots), slots_ac(jb.ac_slots),
+        comp_bits(jb.comp_bits), sums(sums_), blocks(0) {}
+  // The lane's window, from one over words counted from `off` words into the copy.
+  __device__ void open(const BitWindow& w, uint32_t off) {
+    w0 = w.w0;
+    w1 = w.w1;
+    sh = w.sh;
+    at = 4 * (w.wi + off);
   }
-  __device__ void start_counts() { blocks = dc0 = dc1 = dc2 = 0; }
-  __device__ void block(uint32_t b_) {
-    b = b_;
+  __device__ void block(uint32_t b2_) {
+    b2 = b2_;
     k = 0;
-    t = slots_dc >> (2 * b) & 3u;
-    ac = slots_ac >> (2 * b) & 3u;
-    comp = comp_bits >> (2 * b) & 3u;
+    t = slots_dc >> b2 & 3u;
+    ac = slots_ac >> b2 & 3u;
+    row = (comp_bits >> b2 & 3u) * (kThreads * 4);
   }
-  // Whether the lane is at a block boundary at or past bit `target`.
-  __device__ bool reached(uint32_t target) const { return k == 0 && static_cast<int32_t>(w.pos() - target) >= 0; }
-  // One step of one or more symbols; `next` is word w.wi.  Where no code
-  // begins, the block ends (the decoding lane will find the error in it) and
-  // the lane goes on a bit later with a new first block.
-  template <bool COUNT>
-  __device__ __forceinline__ void step(uint32_t next) {
-    const uint32_t top = w.top();
-    const uint32_t m = tabs->skip[t << kSkipLook | top >> (32 - kSkipLook)];
-    uint32_t bits = m & 31u, to = k + (m >> 5 & 63u), size = m >> 11 & 15u;
-    bool end = m >> 15, bad = false;
-    if (bits == 0 || to > 63) {
-      const uint32_t ft = t * static_cast<uint32_t>(sizeof(FastTable));
-      const lds_tables* fast = (const lds_tables*)&tabs->fast;
-      uint32_t e = fast_entry(fast, ft, top);
-      if ((e & 31u) == 0) e = long_code(fast, codes, ft, top, e, k != 0);
-      bad = e == kBadEntry;
-      bits = bad ? 1u : e & 31u;
-      size = k || bad ? 0u : e >> 5 & 15u;
-      to = k + (e >> 9);
-      end = to > 63;
-    }
-    w.drop(bits, next);
-    if constexpr (COUNT) {
-      const uint32_t v = static_cast<uint32_t>(entry_value(top, bits, size));  // 0 for AC symbols
-      dc0 += comp == 0 ? v : 0u;
-      dc1 += comp == 1 ? v : 0u;
-      dc2 += comp == 2 ? v : 0u;
-    }
-    k = to;
-    t = ac;
-    if (end) {
-      if constexpr (COUNT) ++blocks;
-      block(bad || b + 1 == bpm ? 0u : b + 1);
+  // Position of the next unread bit in the copy, modulo 2^32.
+  __device__ uint32_t pos() const { return 8 * at - 32u - static_cast<uint32_t>(sh); }
+  // Walks on from a block boundary until ended(its position) at one; next(at)
+  // reads the word at a byte offset.  Where no code begins, the block ends
+  // (the decoding lane will find the error in it) and the lane goes on a bit
+  // later with a new first block.
+  template <bool COUNT, class Next, class Ended>
+  __device__ __forceinline__ void walk(const Next& next, const Ended& ended) {
+    for (bool on = true; on;) {
+      const uint32_t top = __builtin_amdgcn_alignbit(w0, w1, static_cast<uint32_t>(sh));
+      const uint32_t m = tabs->skip[__builtin_amdgcn_alignbit(t, top, 32 - kSkipLook)];
+      const uint32_t word = next(at);
+      uint32_t bits = m & 31u, to = k + (m >> 5 & 127u), size = m >> 12;
+      lds32* sum = reinterpret_cast<lds32*>(reinterpret_cast<lds8*>(sums) + row);
+      t = ac;
+      bool ends = to > 63;
+      if (ends) {
+        bool bad = false;
+        if (skip_takes_one(m, to)) {
+          const uint32_t ft = (k ? ac : slots_dc >> b2 & 3u) * static_cast<uint32_t>(sizeof(FastTable));
+          const lds_tables* fast = (const lds_tables*)&tabs->fast;
+          uint32_t e = fast_entry(fast, ft, top);
+          if ((e & 31u) == 0) e = long_code(fast, codes, ft, top, e, k != 0);
+          bad = e == kBadEntry;
+          bits = bad ? 1u : e & 31u;
+          size = k || bad ? 0u : e >> 5 & 15u;
+          to = k + (e >> 9);
+          ends = to > 63;
+        }
+        if (ends) {
+          if constexpr (COUNT) ++blocks;
+          block(bad || b2 + 2 == bpm2 ? 0u : b2 + 2);
+          to = 0;
+          on = !ended(pos() + bits);
+        }
+      }
+      // 0 for AC symbols
+      if constexpr (COUNT) __hip_atomic_fetch_add(sum, static_cast<uint32_t>(entry_value(top, bits, size)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+      k = to;
+      sh -= static_cast<int32_t>(bits);
+      const bool over = sh < 0;
+      sh &= 31;
+      w0 = over ? w1 : w0;
+      w1 = over ? word : w1;
+      at += over ? 4u : 0u;
     }
   }
 };
@@ -545,7 +572,8 @@ constexpr uint32_t kFollowWords = (kFollowGroup + kFollowMore) * kChunkWords;
 struct ChunkOf {
   GSplit sp;
   uint32_t c, last;
-  StagedWords words;
+  StagedWords<false> words;
+  uint32_t limit;  // byte offset of the zero word in the copy
   __device__ ChunkOf(const GPlan& pl, const GGroup& g, uint32_t chunk, lds32* staged, uint32_t n) {
     sp = pl.splits[pl.split_of[chunk]];
     c = chunk - sp.chunk0;
@@ -556,31 +584,36 @@ struct ChunkOf {
     words.off = (sp.chunk0 - g.first) * kChunkWords;
     words.n = n;
     words.zero = (bytes + 3) / 4;
+    limit = 4 * (words.zero + words.off);
+  }
+  // A word that is known to lie in the copy, or past the data.
+  __device__ uint32_t staged(uint32_t at) const {
+    return *reinterpret_cast<const lds32*>(reinterpret_cast<const lds8*>(words.base) + (at < limit ? at : limit));
   }
 };
 
 __global__ __launch_bounds__(kThreads) void entropy_guess(const GPlan pl) {
   __shared__ SkipLds tables;
-  __shared__ uint32_t staged[staged_size(kGuessWords)];
+  __shared__ uint32_t staged[kGuessWords];
   const GGroup g = pl.groups[blockIdx.x];
   const GJob& jb = pl.jobs[g.job];
   const uint32_t n = g.count * kChunkWords + kBlockWords;
-  stage_words((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, kThreads);
+  stage_words<false>((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, kThreads);
   load_skip_tables(jb, (lds_skip*)&tables);
   __syncthreads();
-  Walker walk(jb, (const lds_skip*)&tables);
-  const uint32_t mine = threadIdx.x / walk.bpm, first = threadIdx.x - mine * walk.bpm;
+  Walker walk(jb, (const lds_skip*)&tables, nullptr);
+  const uint32_t bpm = jb.bpm, mine = threadIdx.x / bpm, first = threadIdx.x - mine * bpm;
   if (mine >= g.count) return;
   const uint32_t chunk = g.first + mine;
   const ChunkOf at(pl, g, chunk, (lds32*)staged, n);
   uint32_t state = kNoState;
   if (at.c < at.last && (at.c > 0 || first == 0)) {
-    const uint32_t target = (at.c + 1) * (kChunk * 8);
-    walk.w = at.words.open(at.c * kChunkWords, 0);
-    walk.block(first);
-    do walk.step<false>(at.words.staged(walk.w.wi));
-    while (!walk.reached(target));
-    state = make_state(walk.w.pos() - target, walk.b);
+    const uint32_t target = (mine + 1) * (kChunk * 8);
+    walk.open(at.words.open(at.c * kChunkWords, 0), at.words.off);
+    walk.block(2 * first);
+    walk.walk<false>([&](uint32_t i) { return at.staged(i); },
+                     [&](uint32_t pos) { return static_cast<int32_t>(pos - target) >= 0; });
+    state = make_state(walk.pos() - target, walk.b2 / 2);
   }
   uint32_t* own = pl.states + static_cast<uint64_t>(chunk) * kSlots;
   if (at.c == 0 && first == 0) {
@@ -590,25 +623,27 @@ __global__ __launch_bounds__(kThreads) void entropy_guess(const GPlan pl) {
   if (at.c + 1 < at.sp.n_chunks) {
     own[kSlots + first] = state;
     if (first == 0)
-      for (uint32_t i = walk.bpm; i < kSlots; ++i) own[kSlots + i] = kNoState;
+      for (uint32_t i = bpm; i < kSlots; ++i) own[kSlots + i] = kNoState;
   }
 }
 
 __global__ __launch_bounds__(kThreads) void entropy_follow(const GPlan pl) {
   __shared__ SkipLds tables;
-  __shared__ uint32_t staged[staged_size(kFollowWords)];
+  __shared__ uint32_t staged[kFollowWords];
+  __shared__ uint32_t sums[3 * kThreads];
   __shared__ uint16_t list[kFollowGroup * kGuesses];  // chunk in the group << 3 | slot, without the empty and repeated ones
   __shared__ uint32_t n_list;
   const GGroup g = pl.groups[pl.n_groups + blockIdx.x];
   const GJob& jb = pl.jobs[g.job];
   const uint32_t n = (g.count + kFollowMore) * kChunkWords;
   if (threadIdx.x == 0) n_list = 0;
-  stage_words((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, kThreads);
+  stage_words<false>((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, kThreads);
   load_skip_tables(jb, (lds_skip*)&tables);
   __syncthreads();
-  Walker walk(jb, (const lds_skip*)&tables);
-  for (uint32_t i0 = 0; i0 < g.count * walk.bpm; i0 += kThreads) {
-    const uint32_t i = i0 + threadIdx.x, mine = i / walk.bpm, slot = i - mine * walk.bpm;
+  Walker walk(jb, (const lds_skip*)&tables, (lds32*)sums + threadIdx.x);
+  const uint32_t bpm = jb.bpm;
+  for (uint32_t i0 = 0; i0 < g.count * bpm; i0 += kThreads) {
+    const uint32_t i = i0 + threadIdx.x, mine = i / bpm, slot = i - mine * bpm;
     bool use = mine < g.count;
     if (use) {
       const uint32_t* s = pl.states + static_cast<uint64_t>(g.first + mine) * kSlots;
@@ -631,29 +666,42 @@ __global__ __launch_bounds__(kThreads) void entropy_follow(const GPlan pl) {
     uint32_t c = at.c;
     if (c >= at.last) continue;
     const uint32_t from = pl.states[static_cast<uint64_t>(chunk) * kSlots + slot];
-    walk.w = at.words.open(c * kChunkWords + (from >> 8), (from >> 3) & 31u);
-    walk.block(from & 7u);
+    walk.open(at.words.open(c * kChunkWords + (from >> 8), (from >> 3) & 31u), at.words.off);
+    walk.block(2 * (from & 7u));
     for (bool on = true; on;) {
       uint32_t* to = pl.states + static_cast<uint64_t>(chunk + 1) * kSlots;
       uint32_t guessed[kGuesses];  // asked for before the walk
       for (uint32_t j = 0; j < kGuesses; ++j) guessed[j] = to[j];
       const bool in_copy = (chunk + 1 - g.first) * kChunkWords + kBlockWords <= n;
-      GHop* hop = pl.hops + (static_cast<uint64_t>(chunk) * kSlots + slot) * kParts;
-      uint32_t state = 0, part = 0, target = c * (kChunk * 8) + kPart * 8;
-      walk.start_counts();
-      while (part < kParts) {
-        if (walk.reached(target)) {  // perhaps by a block longer than the part, without a step
-          state = make_state(walk.w.pos() - target, walk.b);
-          hop[part] = GHop{static_cast<uint16_t>(walk.blocks),
-                           {static_cast<uint16_t>(walk.dc0), static_cast<uint16_t>(walk.dc1), static_cast<uint16_t>(walk.dc2)},
-                           state, 0};
-          ++part;
-          target += kPart * 8;
-          walk.start_counts();
-        } else {
-          walk.step<true>(in_copy ? at.words.staged(walk.w.wi) : at.words.word(walk.w.wi));
+      // The parts' ends in the copy: the first leaves what was counted up to
+      // it and the lane goes on to the second, unless its block goes past both.
+      const uint32_t end0 = (chunk - g.first) * (kChunk * 8) + kPart * 8, end1 = end0 + kPart * 8;
+      uint32_t state0 = kNoState, blocks0 = 0, sum0[3] = {0, 0, 0};
+      lds32* sum = (lds32*)sums + threadIdx.x;
+      for (uint32_t d = 0; d < 3; ++d) sum[d * kThreads] = 0;
+      walk.blocks = 0;
+      const auto ended = [&](uint32_t pos) {
+        if (static_cast<int32_t>(pos - end0) < 0) return false;
+        if (state0 == kNoState) {
+          state0 = make_state(pos - end0, walk.b2 / 2);
+          blocks0 = walk.blocks;
+          for (uint32_t d = 0; d < 3; ++d) sum0[d] = sum[d * kThreads];
         }
+        return static_cast<int32_t>(pos - end1) >= 0;
+      };
+      if (!ended(walk.pos())) {
+        if (in_copy) walk.walk<true>([&](uint32_t i) { return at.staged(i); }, ended);
+        else walk.walk<true>([&](uint32_t i) { return at.words.word(i / 4 - at.words.off); }, ended);
       }
+      const uint32_t state = make_state(walk.pos() - end1, walk.b2 / 2);
+      GHop* hop = pl.hops + (static_cast<uint64_t>(chunk) * kSlots + slot) * kParts;
+      GHop h0{static_cast<uint16_t>(blocks0), {}, state0, 0}, h1{static_cast<uint16_t>(walk.blocks - blocks0), {}, state, 0};
+      for (uint32_t d = 0; d < 3; ++d) {
+        h0.dc[d] = static_cast<uint16_t>(sum0[d]);
+        h1.dc[d] = static_cast<uint16_t>(sum[d * kThreads] - sum0[d]);
+      }
+      hop[0] = h0;
+      hop[1] = h1;
       uint32_t link = kNoLink;
       for (uint32_t j = kGuesses; j-- > 0;)
         if (guessed[j] == state) link = j;
@@ -924,14 +972,14 @@ __global__ __launch_bounds__(kThreads, SPLIT ? 2 : 3) void entropy_decode(const 
     uint32_t which = 0, b = 0, block = 0, left = 0, block0 = 0, bytes = 0;
     uint32_t p0 = 0, p1 = 0, p2 = 0;
     const bool have_task = tid < item.count;
-    typename std::conditional<SPLIT, StagedWords, WordRing>::type words;
+    typename std::conditional<SPLIT, StagedWords<true>, WordRing>::type words;
     BitWindow w{0, 0, 0, 0};
     if constexpr (SPLIT) {
       // the parts lie in order in memory
       words.base = (lds32*)words_mem + wave * kWaveLds;
       const uint64_t word0 = static_cast<uint64_t>(item.first + wave0) * (kPart / 4);
       words.n = 64 * (kPart / 4) + kBlockWords;
-      if (wave0 < item.count) stage_words(words.base, (gin128*)(pl.data + word0 * 4), words.n, lane, 64);
+      if (wave0 < item.count) stage_words<true>(words.base, (gin128*)(pl.data + word0 * 4), words.n, lane, 64);
       wave_sync();
       if (have_task) {
         const GTask k = pl.tasks[item.first + tid];

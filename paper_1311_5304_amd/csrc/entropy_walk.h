@@ -127,12 +127,13 @@ MJD_HD inline uint32_t more_entry(uint32_t e, uint32_t top, bool ac, const More&
 
 // Several symbols at once, for lanes that only look for block boundaries:
 // what the next kSkipLook bits determine.
-//   0            not even one symbol
-//   bits 0-4     bits of all its symbols
-//   bits 5-10    how far they move the zig-zag position, an EOB left out
-//   bits 11-14   DC: the magnitude size of its one symbol
-//   bit 15       the last symbol is EOB
-// A lane whose position would leave the block by bits 5-10 takes one symbol.
+//   bits 0-4     bits of all its symbols, 0 where there is not even one
+//   bits 5-11    how far they move the zig-zag position, and kEobStep more
+//                where the last one is EOB or there is none
+//   bits 12-15   DC: the magnitude size of its one symbol
+// So a position past 63 is the one test a lane needs for the end of a block,
+// for a code that the look-up does not hold and for symbols that together
+// leave the block (skip_takes_one: these two take one symbol instead).
 constexpr uint32_t kSkipLook = 11;
 constexpr uint32_t kSkipEntries = 1u << kSkipLook;
 
@@ -144,15 +145,18 @@ MJD_HD inline uint32_t skip_entry(uint32_t index, bool ac, const Entry& entry) {
     const uint32_t e = entry(top << bits);
     const uint32_t size = e >> 5 & 15u;
     if (e == kBadEntry || bits + (e & 31u) - size > kSkipLook) break;  // no code among the known bits
-    if (!ac) return (e & 31u) | 1u << 5 | size << 11;
-    if (e >> 9 == kEobStep) return (bits + (e & 31u)) | step << 5 | 1u << 15;
+    if (!ac) return (e & 31u) | 1u << 5 | size << 12;
+    if (e >> 9 == kEobStep) return (bits + (e & 31u)) | (step | kEobStep) << 5;
     if (step + (e >> 9) > 63) break;
     bits += e & 31u;
     step += e >> 9;
     if (bits >= kSkipLook) break;
   }
-  return bits | step << 5;
+  return bits ? bits | step << 5 : kEobStep << 5;
 }
+
+// Of an entry that takes the position to `to`, past 63.
+MJD_HD inline bool skip_takes_one(uint32_t m, uint32_t to) { return (m & 31u) == 0 || to - (m >> 5 & kEobStep) > 63; }
 
 // The value whose `size` magnitude bits end `total` bits into `top` (T.81
 // F.2.2.1 EXTEND); 0 for size 0.

@@ -72,11 +72,16 @@ int main(int argc, char** argv) {
           eob = ac && e >> 9 == kEobStep;
           step += eob ? 0 : e >> 9;
           bits += e & 31u;
-          if (!ac && (m >> 11 & 15u) != (e >> 5 & 15u)) return 3;
+          if (!ac && (m >> 12) != (e >> 5 & 15u)) return 3;
         }
-        if (m && (bits != (m & 31u) || step != (m >> 5 & 63u) || eob != (m >> 15 != 0))) {
+        if (bits == 0 ? m != kEobStep << 5 : bits != (m & 31u) || step != (m >> 5 & 63u) || eob != ((m >> 5 & kEobStep) != 0)) {
           fprintf(stderr, "table %d, skip entry %x: %u bits, %u on, eob %d, entry %x\n", id, i, bits, step, eob, m);
           return 3;
+        }
+        // past position 63 the whole entry holds if, and only if, it ends the block there
+        for (uint32_t k : {0u, 1u, 30u, 62u, 63u}) {
+          const uint32_t to = k + (m >> 5 & 127u);
+          if (to > 63 && skip_takes_one(m, to) != (bits == 0 || !eob || k + step > 63)) return 3;
         }
       }
     }
