@@ -20,7 +20,6 @@
 #include <algorithm>
 #include <new>
 #include <string>
-#include <type_traits>
 #include <vector>
 
 #include "entropy_walk.h"
@@ -117,6 +116,7 @@ struct GPlan {
   const GItem* items;
   const uint32_t* skip_jobs;  // the jobs that have split intervals
   uint32_t n_skip;
+  uint32_t many;  // entropy_follow's shape
   uint32_t n_iv, n_tiles, n_groups, n_more_groups, n_splits, n_long, n_items, n_split_items;
   uint8_t* data;      // destuffed bytes
   uint32_t* bytes;    // destuffed bytes per interval
@@ -328,10 +328,12 @@ __global__ __launch_bounds__(kThreads) void entropy_destuff(const GPlan pl) {
 
 typedef __attribute__((address_space(3))) FastTables lds_tables;
 
+// By all lanes of a workgroup.
+template <uint32_t THREADS>
 __device__ __forceinline__ void load_tables(const FastTables* from, lds_tables* to) {
   gin128* src = (gin128*)from;
   __attribute__((address_space(3))) v4u_t* dst = (__attribute__((address_space(3))) v4u_t*)to;
-  for (uint32_t i = threadIdx.x; i < sizeof(FastTables) / 16; i += kThreads) dst[i] = src[i];
+  for (uint32_t i = threadIdx.x; i < sizeof(FastTables) / 16; i += THREADS) dst[i] = src[i];
 }
 
 // The `fast` entry at the front of `top` in the table at byte offset t, and
@@ -350,30 +352,23 @@ __device__ __forceinline__ uint32_t table_of(uint32_t slots, uint32_t b) {
   return (slots >> (2 * b) & 3u) * static_cast<uint32_t>(sizeof(FastTable));
 }
 
-// Words of consecutive chunks, which a workgroup or a wave copies to LDS
-// before it decodes them: a lane then waits for no load.  A lane's words are
+// Words of consecutive chunks, which a workgroup copies to LDS before it
+// walks through them: a lane then waits for no load.  A lane's words are
 // counted from the start of its interval and end with a zero word past the
-// data.  SPREAD leaves one word in 33 free, so that lanes at the same place
-// of different chunks meet in no bank; without it a word's address takes no
-// arithmetic.
-template <bool SPREAD>
-__host__ __device__ constexpr uint32_t staged_place(uint32_t i) { return SPREAD ? i + i / 32 : i; }
-constexpr uint32_t staged_size(uint32_t words) { return words + words / 32 + 1; }
+// data.
 // Words that a block needs past the word of its first bit, the window's
 // included: a DC symbol of at most 27 bits and 63 of at most 31.
 constexpr uint32_t kBlockWords = (63 * 31 + 27 + 31) / 32 + 2;
 
 // Copies n words (a multiple of 4) from `src` on, by `lanes` lanes.
-template <bool SPREAD>
 __device__ __forceinline__ void stage_words(lds32* base, gin128* src, uint32_t n, uint32_t lane, uint32_t lanes) {
   for (uint32_t i = lane; i < n / 4; i += lanes) {
     const v4u_t v = src[i];
 #pragma unroll
-    for (uint32_t j = 0; j < 4; ++j) base[staged_place<SPREAD>(4 * i + j)] = swap_bytes(v[j]);
+    for (uint32_t j = 0; j < 4; ++j) base[4 * i + j] = swap_bytes(v[j]);
   }
 }
 
-template <bool SPREAD>
 struct StagedWords {
   lds32* base;
   gin128* src;    // the interval's data
@@ -381,12 +376,9 @@ struct StagedWords {
   uint32_t n;     // words of the copy
   uint32_t zero;  // its zero word
 
-  __device__ uint32_t staged(uint32_t w) const {
-    return base[staged_place<SPREAD>((w < zero ? w : zero) + off)];
-  }
   __device__ uint32_t word(uint32_t w) const {
     const uint32_t v = w < zero ? w : zero, i = v + off;
-    if (__builtin_expect(i < n, 1)) return base[staged_place<SPREAD>(i)];
+    if (__builtin_expect(i < n, 1)) return base[i];
     return swap_bytes(((__attribute__((address_space(1))) const uint32_t*)src)[v]);
   }
   __device__ BitWindow open(uint32_t at, uint32_t bit) const {
@@ -414,15 +406,18 @@ struct WordRing {
     for (uint32_t i = 0; i < 4; ++i) base[((at & 4u) + i) * kThreads] = swap_bytes(c[i]);  // at: a multiple of 4
   }
   __device__ uint32_t word(uint32_t w) const { return base[(w & (kRingWords - 1)) * kThreads]; }
-  // A window at the start.
-  __device__ BitWindow open(uint32_t bytes) {
-    last = bytes / 16 + 1;
-    const v4u_t c0 = src[0], c1 = src[1];  // there is always the zero chunk
-    put(0, c0);
-    put(4, c1);
-    have = 8;
+  // A window at bit 32 * word + bit of `bytes` bytes.
+  __device__ BitWindow open(uint32_t bytes, uint32_t word_, uint32_t bit) {
+    last = bytes / 16 + 1;  // there is always the zero chunk
+    const uint32_t c = word_ / 4 < last ? word_ / 4 : last;
+    const v4u_t c0 = src[c], c1 = src[c < last ? c + 1 : last];
+    have = 4 * (word_ / 4);
+    put(have, c0);
+    put(have + 4, c1);
+    have += 8;
     loading = false;
-    return window_at(0, 0, 0, word(0));
+    const uint32_t q = window_word(word_, bit);
+    return window_at(word_, bit, word(q - 1), word(q));
   }
   __device__ void refill(bool active, uint32_t wi) {
     if (loading) {
@@ -462,18 +457,21 @@ struct WordRing {
 // per MCU row takes 47 + 98 us in them, the 12-image corpus 142 + 183 us.
 constexpr uint32_t kMaxHops = 32;
 
-// The tables of a job for guess and follow.
+// The skip tables of a job in LDS, and its whole tables, which one lane in
+// 300 needs in a step: in LDS too, or in memory, which leaves room for half
+// as many waves again.
+template <bool WHOLE>
 struct SkipLds {
-  __align__(16) FastTables fast;
   __align__(16) uint16_t skip[kTableSlots * kSkipEntries];
+  __align__(16) FastTables fast[WHOLE ? 1 : 0];
 };
-typedef __attribute__((address_space(3))) SkipLds lds_skip;
 
-__device__ __forceinline__ void load_skip_tables(const GJob& jb, lds_skip* to) {
-  load_tables(jb.tables, (lds_tables*)&to->fast);
+template <bool WHOLE, uint32_t THREADS>
+__device__ __forceinline__ void load_skip_tables(const GJob& jb, SkipLds<WHOLE>* to) {
+  if constexpr (WHOLE) load_tables<THREADS>(jb.tables, (lds_tables*)&to->fast[0]);
   gin128* src = (gin128*)jb.skip;
   __attribute__((address_space(3))) v4u_t* dst = (__attribute__((address_space(3))) v4u_t*)to->skip;
-  for (uint32_t i = threadIdx.x; i < kTableSlots * kSkipEntries / 8; i += kThreads) dst[i] = src[i];
+  for (uint32_t i = threadIdx.x; i < kTableSlots * kSkipEntries / 8; i += THREADS) dst[i] = src[i];
 }
 
 // A lane on its way from a block boundary to another, over a copy of the
@@ -481,8 +479,11 @@ __device__ __forceinline__ void load_skip_tables(const GJob& jb, lds_skip* to) {
 // issues one in five cycles, and a look-up's latency is that of twenty-five),
 // so whatever only a block's end needs waits for one: the position, the next
 // block's tables, the sum that its DC difference goes to.
+template <bool WHOLE, uint32_t THREADS>
 struct Walker {
-  const lds_skip* tabs;
+  const lds16* skip;
+  const lds_tables* fast;    // WHOLE
+  const FastTables* memory;  // else
   const GHuff* codes;
   uint32_t bpm2, slots_dc, slots_ac, comp_bits;
   uint32_t w0, w1;  // the window, as in BitWindow
@@ -490,12 +491,12 @@ struct Walker {
   uint32_t at;      // byte offset in the copy of the word after w1's
   uint32_t b2, k;   // twice the block of the MCU; the zig-zag position
   uint32_t t, ac;   // slots of the next symbol's table and of the block's AC table
-  lds32* sums;      // of DC differences, a row of kThreads lanes for each component
+  lds32* sums;      // of DC differences, a row of THREADS lanes for each component
   uint32_t row;     // byte offset of the block's
   uint32_t blocks;
 
-  __device__ Walker(const GJob& jb, const lds_skip* tabs_, lds32* sums_)
-      : tabs(tabs_), codes(jb.codes), bpm2(2 * jb.bpm), slots_dc(jb.dc_slots), slots_ac(jb.ac_slots),
+  __device__ Walker(const GJob& jb, const SkipLds<WHOLE>* tabs, lds32* sums_)
+      : skip((const lds16*)tabs->skip), fast((const lds_tables*)tabs->fast), memory(jb.tables), codes(jb.codes), bpm2(2 * jb.bpm), slots_dc(jb.dc_slots), slots_ac(jb.ac_slots),
         comp_bits(jb.comp_bits), sums(sums_), blocks(0) {}
   // The lane's window, from one over words counted from `off` words into the copy.
   __device__ void open(const BitWindow& w, uint32_t off) {
@@ -509,7 +510,19 @@ struct Walker {
     k = 0;
     t = slots_dc >> b2 & 3u;
     ac = slots_ac >> b2 & 3u;
-    row = (comp_bits >> b2 & 3u) * (kThreads * 4);
+    row = (comp_bits >> b2 & 3u) * (THREADS * 4);
+  }
+  // The entry of the code at the front of `top` in the table of slot s.
+  __device__ uint32_t whole_entry(uint32_t s, uint32_t top) const {
+    if constexpr (WHOLE) {
+      const uint32_t ft = s * static_cast<uint32_t>(sizeof(FastTable)), e = fast_entry(fast, ft, top);
+      return e & 31u ? e : long_code(fast, codes, ft, top, e, k != 0);
+    } else {
+      const FastTable& ft = memory->t[s];
+      const uint32_t e = ft.fast[top >> (32 - kGLook)];
+      return e & 31u ? e : more_entry(e, top, k != 0, [&](uint32_t i) { return static_cast<uint32_t>(ft.more[i]); },
+                                      PlainTab{codes}, static_cast<int>(s));
+    }
   }
   // Position of the next unread bit in the copy, modulo 2^32.
   __device__ uint32_t pos() const { return 8 * at - 32u - static_cast<uint32_t>(sh); }
@@ -521,7 +534,7 @@ struct Walker {
   __device__ __forceinline__ void walk(const Next& next, const Ended& ended) {
     for (bool on = true; on;) {
       const uint32_t top = __builtin_amdgcn_alignbit(w0, w1, static_cast<uint32_t>(sh));
-      const uint32_t m = tabs->skip[__builtin_amdgcn_alignbit(t, top, 32 - kSkipLook)];
+      const uint32_t m = skip[__builtin_amdgcn_alignbit(t, top, 32 - kSkipLook)];
       const uint32_t word = next(at);
       uint32_t bits = m & 31u, to = k + (m >> 5 & 127u), size = m >> 12;
       lds32* sum = reinterpret_cast<lds32*>(reinterpret_cast<lds8*>(sums) + row);
@@ -530,10 +543,7 @@ struct Walker {
       if (ends) {
         bool bad = false;
         if (skip_takes_one(m, to)) {
-          const uint32_t ft = (k ? ac : slots_dc >> b2 & 3u) * static_cast<uint32_t>(sizeof(FastTable));
-          const lds_tables* fast = (const lds_tables*)&tabs->fast;
-          uint32_t e = fast_entry(fast, ft, top);
-          if ((e & 31u) == 0) e = long_code(fast, codes, ft, top, e, k != 0);
+          const uint32_t e = whole_entry(k ? ac : slots_dc >> b2 & 3u, top);
           bad = e == kBadEntry;
           bits = bad ? 1u : e & 31u;
           size = k || bad ? 0u : e >> 5 & 15u;
@@ -562,17 +572,29 @@ struct Walker {
 
 // Words that a workgroup stages of its chunks and those after them, for a
 // block that begins in the last chunk and, in `follow`, for lanes that go on.
-constexpr uint32_t kGuessGroup = 85, kFollowGroup = 96;  // chunks: one lane per guess for three blocks an MCU
-constexpr uint32_t kFollowMore = 8;
+// A lane per guess: 85 chunks of six blocks an MCU.  512 lanes to a copy of
+// the tables, as 256 left half as many waves a CU (145 us in entropy_guess for
+// the 12-image corpus, 115 here).
+constexpr uint32_t kGuessThreads = 512, kGuessGroup = 85;
 constexpr uint32_t kGuessWords = kGuessGroup * kChunkWords + kBlockWords;
-constexpr uint32_t kFollowWords = (kFollowGroup + kFollowMore) * kChunkWords;
+// About two boundaries a chunk to follow.  Where more chunks come together
+// than the small workgroups hold that fit on the chip at once, larger ones
+// with the whole tables in memory have twice the waves a CU: 145 -> 110 us for
+// the corpus (133,000 chunks); with 19,500 chunks and with 4,000 the small
+// ones take 76 and 65 us, the large ones 81 and 70.
+template <bool MANY>
+struct FollowShape {
+  static constexpr uint32_t THREADS = MANY ? 512 : 256, GROUP = MANY ? 208 : 96, MORE = 8;  // chunks
+  static constexpr uint32_t WORDS = (GROUP + MORE) * kChunkWords;
+  static constexpr uint32_t RESIDENT = 3;  // workgroups a CU
+};
 
 // A lane's chunk: its interval, its number there and the last one that holds
 // data, which hands over to none.
 struct ChunkOf {
   GSplit sp;
   uint32_t c, last;
-  StagedWords<false> words;
+  StagedWords words;
   uint32_t limit;  // byte offset of the zero word in the copy
   __device__ ChunkOf(const GPlan& pl, const GGroup& g, uint32_t chunk, lds32* staged, uint32_t n) {
     sp = pl.splits[pl.split_of[chunk]];
@@ -592,17 +614,17 @@ struct ChunkOf {
   }
 };
 
-__global__ __launch_bounds__(kThreads) void entropy_guess(const GPlan pl) {
-  __shared__ SkipLds tables;
+__global__ __launch_bounds__(kGuessThreads) void entropy_guess(const GPlan pl) {
+  __shared__ SkipLds<true> tables;
   __shared__ uint32_t staged[kGuessWords];
   const GGroup g = pl.groups[blockIdx.x];
   const GJob& jb = pl.jobs[g.job];
   const uint32_t n = g.count * kChunkWords + kBlockWords;
-  stage_words<false>((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, kThreads);
-  load_skip_tables(jb, (lds_skip*)&tables);
+  stage_words((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, kGuessThreads);
+  load_skip_tables<true, kGuessThreads>(jb, &tables);
   __syncthreads();
-  Walker walk(jb, (const lds_skip*)&tables, nullptr);
-  const uint32_t bpm = jb.bpm, mine = threadIdx.x / bpm, first = threadIdx.x - mine * bpm;
+  Walker<true, kGuessThreads> walk(jb, &tables, nullptr);
+  const uint32_t tries = jb.bpm, mine = threadIdx.x / tries, first = threadIdx.x - mine * tries;
   if (mine >= g.count) return;
   const uint32_t chunk = g.first + mine;
   const ChunkOf at(pl, g, chunk, (lds32*)staged, n);
@@ -623,27 +645,30 @@ __global__ __launch_bounds__(kThreads) void entropy_guess(const GPlan pl) {
   if (at.c + 1 < at.sp.n_chunks) {
     own[kSlots + first] = state;
     if (first == 0)
-      for (uint32_t i = bpm; i < kSlots; ++i) own[kSlots + i] = kNoState;
+      for (uint32_t i = tries; i < kSlots; ++i) own[kSlots + i] = kNoState;
   }
 }
 
-__global__ __launch_bounds__(kThreads) void entropy_follow(const GPlan pl) {
-  __shared__ SkipLds tables;
-  __shared__ uint32_t staged[kFollowWords];
-  __shared__ uint32_t sums[3 * kThreads];
-  __shared__ uint16_t list[kFollowGroup * kGuesses];  // chunk in the group << 3 | slot, without the empty and repeated ones
+template <bool MANY>
+__global__ __launch_bounds__(FollowShape<MANY>::THREADS) void entropy_follow(const GPlan pl) {
+  using F = FollowShape<MANY>;
+  constexpr uint32_t THREADS = F::THREADS;
+  __shared__ SkipLds<!MANY> tables;
+  __shared__ uint32_t staged[F::WORDS];
+  __shared__ uint32_t sums[3 * THREADS];
+  __shared__ uint16_t list[F::GROUP * kGuesses];  // chunk in the group << 3 | slot, without the empty and repeated ones
   __shared__ uint32_t n_list;
   const GGroup g = pl.groups[pl.n_groups + blockIdx.x];
   const GJob& jb = pl.jobs[g.job];
-  const uint32_t n = (g.count + kFollowMore) * kChunkWords;
+  const uint32_t n = (g.count + F::MORE) * kChunkWords;
   if (threadIdx.x == 0) n_list = 0;
-  stage_words<false>((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, kThreads);
-  load_skip_tables(jb, (lds_skip*)&tables);
+  stage_words((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, THREADS);
+  load_skip_tables<!MANY, THREADS>(jb, &tables);
   __syncthreads();
-  Walker walk(jb, (const lds_skip*)&tables, (lds32*)sums + threadIdx.x);
-  const uint32_t bpm = jb.bpm;
-  for (uint32_t i0 = 0; i0 < g.count * bpm; i0 += kThreads) {
-    const uint32_t i = i0 + threadIdx.x, mine = i / bpm, slot = i - mine * bpm;
+  Walker<!MANY, THREADS> walk(jb, &tables, (lds32*)sums + threadIdx.x);
+  const uint32_t tries = jb.bpm;
+  for (uint32_t i0 = 0; i0 < g.count * tries; i0 += THREADS) {
+    const uint32_t i = i0 + threadIdx.x, mine = i / tries, slot = i - mine * tries;
     bool use = mine < g.count;
     if (use) {
       const uint32_t* s = pl.states + static_cast<uint64_t>(g.first + mine) * kSlots;
@@ -660,7 +685,7 @@ __global__ __launch_bounds__(kThreads) void entropy_follow(const GPlan pl) {
   }
   __syncthreads();
   const uint32_t n_work = n_list;
-  for (uint32_t i = threadIdx.x; i < n_work; i += kThreads) {
+  for (uint32_t i = threadIdx.x; i < n_work; i += THREADS) {
     uint32_t chunk = g.first + (list[i] >> 3), slot = list[i] & 7u, hops = 0;
     const ChunkOf at(pl, g, chunk, (lds32*)staged, n);
     uint32_t c = at.c;
@@ -678,27 +703,27 @@ __global__ __launch_bounds__(kThreads) void entropy_follow(const GPlan pl) {
       const uint32_t end0 = (chunk - g.first) * (kChunk * 8) + kPart * 8, end1 = end0 + kPart * 8;
       uint32_t state0 = kNoState, blocks0 = 0, sum0[3] = {0, 0, 0};
       lds32* sum = (lds32*)sums + threadIdx.x;
-      for (uint32_t d = 0; d < 3; ++d) sum[d * kThreads] = 0;
+      for (uint32_t d = 0; d < 3; ++d) sum[d * THREADS] = 0;
       walk.blocks = 0;
       const auto ended = [&](uint32_t pos) {
         if (static_cast<int32_t>(pos - end0) < 0) return false;
         if (state0 == kNoState) {
           state0 = make_state(pos - end0, walk.b2 / 2);
           blocks0 = walk.blocks;
-          for (uint32_t d = 0; d < 3; ++d) sum0[d] = sum[d * kThreads];
+          for (uint32_t d = 0; d < 3; ++d) sum0[d] = sum[d * THREADS];
         }
         return static_cast<int32_t>(pos - end1) >= 0;
       };
       if (!ended(walk.pos())) {
-        if (in_copy) walk.walk<true>([&](uint32_t i) { return at.staged(i); }, ended);
-        else walk.walk<true>([&](uint32_t i) { return at.words.word(i / 4 - at.words.off); }, ended);
+        if (in_copy) walk.template walk<true>([&](uint32_t i) { return at.staged(i); }, ended);
+        else walk.template walk<true>([&](uint32_t i) { return at.words.word(i / 4 - at.words.off); }, ended);
       }
       const uint32_t state = make_state(walk.pos() - end1, walk.b2 / 2);
       GHop* hop = pl.hops + (static_cast<uint64_t>(chunk) * kSlots + slot) * kParts;
       GHop h0{static_cast<uint16_t>(blocks0), {}, state0, 0}, h1{static_cast<uint16_t>(walk.blocks - blocks0), {}, state, 0};
       for (uint32_t d = 0; d < 3; ++d) {
         h0.dc[d] = static_cast<uint16_t>(sum0[d]);
-        h1.dc[d] = static_cast<uint16_t>(sum[d * kThreads] - sum0[d]);
+        h1.dc[d] = static_cast<uint16_t>(sum[d * THREADS] - sum0[d]);
       }
       hop[0] = h0;
       hop[1] = h1;
@@ -931,11 +956,10 @@ struct BlockBuf {
 constexpr int kDecodeSteps = 4;  // between two points; every second one refills
 
 template <bool SPLIT>
-__global__ __launch_bounds__(kThreads, SPLIT ? 2 : 3) void entropy_decode(const GPlan pl) {
+__global__ __launch_bounds__(kThreads, 3) void entropy_decode(const GPlan pl) {
   __shared__ __align__(16) FastTables tables;
   __shared__ __align__(16) uint8_t block_bytes[kThreads * 128];
-  constexpr uint32_t kWaveLds = staged_size(64 * (kPart / 4) + kBlockWords);  // of a wave's parts
-  __shared__ uint32_t words_mem[SPLIT ? kWaves * kWaveLds : kRingWords * kThreads];
+  __shared__ uint32_t words_mem[kRingWords * kThreads];
   __shared__ uint32_t list_mem[kThreads];  // block | lane << 28 (its low four bits) of the wave's complete blocks
   __shared__ int s_next;
   const uint32_t tid = threadIdx.x, lane = lane_of();
@@ -961,7 +985,7 @@ __global__ __launch_bounds__(kThreads, SPLIT ? 2 : 3) void entropy_decode(const 
     const uint32_t job = uniform(item.job);
     const GJob& jb = pl.jobs[job];
     if (job != cur_job) {
-      load_tables(jb.tables, tabs);
+      load_tables<kThreads>(jb.tables, tabs);
       __syncthreads();
       cur_job = job;
     }
@@ -972,46 +996,36 @@ __global__ __launch_bounds__(kThreads, SPLIT ? 2 : 3) void entropy_decode(const 
     uint32_t which = 0, b = 0, block = 0, left = 0, block0 = 0, bytes = 0;
     uint32_t p0 = 0, p1 = 0, p2 = 0;
     const bool have_task = tid < item.count;
-    typename std::conditional<SPLIT, StagedWords<true>, WordRing>::type words;
+    WordRing words;
+    words.base = (lds32*)words_mem + tid;
+    words.src = (gin128*)pl.data;
+    words.loading = false;
+    words.have = words.last = 0;
     BitWindow w{0, 0, 0, 0};
-    if constexpr (SPLIT) {
-      // the parts lie in order in memory
-      words.base = (lds32*)words_mem + wave * kWaveLds;
-      const uint64_t word0 = static_cast<uint64_t>(item.first + wave0) * (kPart / 4);
-      words.n = 64 * (kPart / 4) + kBlockWords;
-      if (wave0 < item.count) stage_words<true>(words.base, (gin128*)(pl.data + word0 * 4), words.n, lane, 64);
-      wave_sync();
-      if (have_task) {
-        const GTask k = pl.tasks[item.first + tid];
+    if (have_task) {
+      uint32_t word = 0, bit = 0;
+      which = item.first + tid;
+      if constexpr (SPLIT) {
+        const GTask k = pl.tasks[which];
         which = k.iv;
+        word = k.word;
+        bit = k.bit_b & 255u;
         b = k.bit_b >> 8;
         block = k.block0;
         left = k.n_blocks;
         p0 = k.dc[0];
         p1 = k.dc[1];
         p2 = k.dc[2];
-        const GInterval iv = pl.ivs[which];
-        bytes = pl.bytes[which];
-        block0 = iv.block0;
-        words.src = (gin128*)(pl.data + static_cast<uint64_t>(iv.dst) * 16);
-        words.off = iv.dst * 4u - static_cast<uint32_t>(word0);
-        words.zero = (bytes + 3) / 4;
-        w = words.open(k.word, k.bit_b & 255u);
       }
-    } else {
-      words.base = (lds32*)words_mem + tid;
-      words.src = (gin128*)pl.data;
-      words.loading = false;
-      words.have = words.last = 0;
-      if (have_task) {
-        which = item.first + tid;
-        const GInterval iv = pl.ivs[which];
-        bytes = pl.bytes[which];
-        block = block0 = iv.block0;
+      const GInterval iv = pl.ivs[which];
+      bytes = pl.bytes[which];
+      block0 = iv.block0;
+      if constexpr (!SPLIT) {
+        block = block0;
         left = iv.n_blocks;
-        words.src = (gin128*)(pl.data + static_cast<uint64_t>(iv.dst) * 16);
-        w = words.open(bytes);
       }
+      words.src = (gin128*)(pl.data + static_cast<uint64_t>(iv.dst) * 16);
+      w = words.open(bytes, word, bit);
     }
     // k is the position of the block's next coefficient, at least 64 once it
     // is complete, kIdle in a lane that has nothing to do
@@ -1035,31 +1049,11 @@ __global__ __launch_bounds__(kThreads, SPLIT ? 2 : 3) void entropy_decode(const 
       w.drop(e & 31u, next);
     };
     while (__ballot(k < kIdle)) {
-      if constexpr (SPLIT) {
-        // a lane near the end of the copy (one that decodes what a broken
-        // chain left) reads from memory
-        const uint32_t i = (w.wi < words.zero ? w.wi : words.zero) + words.off;
-        if (__ballot(k < 64 && i + kDecodeSteps >= words.n)) {
-          const uint32_t at = w.wi;
-          uint32_t q[kDecodeSteps];  // the words that the steps can come to
-          for (uint32_t s = 0; s < kDecodeSteps; ++s) q[s] = words.word(at + s);
-#pragma unroll 1
-          for (int s = 0; s < kDecodeSteps; ++s) {
-            const uint32_t d = w.wi - at;
-            if (k < 64) step(d == 0 ? q[0] : d == 1 ? q[1] : d == 2 ? q[2] : q[3]);
-          }
-        } else {
+      if (refill) words.refill(k < kIdle, w.wi);
+      refill = !refill;
 #pragma unroll
-          for (int s = 0; s < kDecodeSteps; ++s)
-            if (k < 64) step(words.staged(w.wi));
-        }
-      } else {
-        if (refill) words.refill(k < kIdle, w.wi);
-        refill = !refill;
-#pragma unroll
-        for (int s = 0; s < kDecodeSteps; ++s)
-          if (k < 64 && words.ready(w.wi)) step(words.word(w.wi));
-      }
+      for (int s = 0; s < kDecodeSteps; ++s)
+        if (k < 64 && words.ready(w.wi)) step(words.word(w.wi));
       const bool full = k >= 64 && k < kIdle;
       const uint64_t m = __ballot(full);
       if (m == 0) continue;
@@ -1276,6 +1270,7 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   split_of.reserve(chunks);
   std::vector<GItem> split_items;
   std::vector<GGroup> more_groups;
+  const bool many = chunks > uint64_t{FollowShape<false>::RESIDENT * FollowShape<false>::GROUP} * static_cast<uint64_t>(cus);
   for (size_t j = 0; j < n; ++j) {
     const size_t end = j + 1 < n ? b->first_interval[j + 1] : n_iv;
     const uint32_t job = static_cast<uint32_t>(j), first_chunk = n_chunks;
@@ -1304,9 +1299,9 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
     if (n_chunks > first_chunk) {
       skip_jobs.push_back(job);
       const uint32_t parts = n_chunks * kParts;
-      uint32_t per = std::min(kThreads / gj[j].bpm, kGuessGroup);
+      uint32_t per = std::min(kGuessThreads / gj[j].bpm, kGuessGroup);
       for (uint32_t f = first_chunk; f < n_chunks; f += per) groups.push_back(GGroup{job, f, std::min(per, n_chunks - f)});
-      per = kFollowGroup;
+      per = many ? FollowShape<true>::GROUP : FollowShape<false>::GROUP;
       for (uint32_t f = first_chunk; f < n_chunks; f += per) more_groups.push_back(GGroup{job, f, std::min(per, n_chunks - f)});
       for (uint32_t f = first_chunk * kParts; f < parts; f += kThreads)
         split_items.push_back(GItem{job, f, std::min<uint32_t>(kThreads, parts - f), kPart});
@@ -1335,7 +1330,7 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
     for (uint32_t& k : split_of) k = place[k];
   }
   b->grid = std::min<int>(static_cast<int>(items.size() - n_split_items), per_cu * cus);
-  b->split_grid = std::min<int>(static_cast<int>(n_split_items), 2 * cus);
+  b->split_grid = std::min<int>(static_cast<int>(n_split_items), per_cu * cus);
   // one allocation: what the host fills first, then what the kernels write
   Layout mem;
   const uint64_t o_jobs = mem.add(n * sizeof(GJob)), o_tables = mem.add(n * sizeof(FastTables)), o_codes = mem.add(n * sizeof(GTables)),
@@ -1388,6 +1383,7 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   p.items = reinterpret_cast<const GItem*>(d + o_items);
   p.skip_jobs = reinterpret_cast<const uint32_t*>(d + o_skip_jobs);
   p.n_skip = static_cast<uint32_t>(skip_jobs.size());
+  p.many = many ? 1u : 0u;
   p.n_iv = static_cast<uint32_t>(n_iv);
   p.n_tiles = static_cast<uint32_t>(tiles.size());
   p.n_groups = static_cast<uint32_t>(n_guess_groups);
@@ -1415,8 +1411,9 @@ static hipError_t enqueue(const mjd_entropy_batch* b, hipStream_t s) {
   const uint32_t skip_groups = p.n_skip * (kTableSlots * kSkipEntries / kThreads);
   hipLaunchKernelGGL(entropy_destuff, dim3((p.n_iv + p.n_tiles + kWaves - 1) / kWaves + skip_groups), block, 0, s, p);
   if (p.n_splits) {
-    hipLaunchKernelGGL(entropy_guess, dim3(p.n_groups), block, 0, s, p);
-    hipLaunchKernelGGL(entropy_follow, dim3(p.n_more_groups), block, 0, s, p);
+    hipLaunchKernelGGL(entropy_guess, dim3(p.n_groups), dim3(kGuessThreads), 0, s, p);
+    if (p.many) hipLaunchKernelGGL(entropy_follow<true>, dim3(p.n_more_groups), dim3(FollowShape<true>::THREADS), 0, s, p);
+    else hipLaunchKernelGGL(entropy_follow<false>, dim3(p.n_more_groups), dim3(FollowShape<false>::THREADS), 0, s, p);
     if (p.n_long) hipLaunchKernelGGL(entropy_resolve<1024>, dim3(p.n_long), dim3(1024), 0, s, p);
     const uint32_t rest = p.n_splits - p.n_long;
     if (rest) hipLaunchKernelGGL(entropy_resolve<64>, dim3((rest + kWaves - 1) / kWaves), block, 0, s, p);
