@@ -449,12 +449,13 @@ struct WordRing {
 // An interval whose chain breaks (no free slot, or not within kMaxHops
 // chunks, as textures that repeat can make it) is decoded by one lane from
 // that chunk on.
-// A lane's steps are one chain of dependent operations, about 550 cycles each
-// with a table look-up in LDS on it, so both kernels take several symbols a
-// step (skip tables, 12 to 11 bits of look-up cost 2% and leave room for four
-// workgroups a CU) and are bound by that chain where lanes are few and by
-// instruction issue where they are many: a 4000x3000 4:2:0 file with a marker
-// per MCU row takes 47 + 98 us in them, the 12-image corpus 142 + 183 us.
+// Both kernels are bound by a lane's chain of look-ups where lanes are few and
+// by instruction issue where they are many, so a look-up takes several symbols
+// (skip tables; 11 bits of look-up instead of 12 cost 2% and leave room for
+// four workgroups a CU), and what only a block's end needs is done once in
+// kLooks look-ups, for the lanes that have come to one: a 4000x3000 4:2:0 file
+// with a marker per MCU row takes 31 + 55 us in them, the 12-image corpus 90 +
+// 77 us (48 + 75 and 115 + 110 with an end in every look-up).
 constexpr uint32_t kMaxHops = 32;
 
 // The skip tables of a job in LDS, and its whole tables, which one lane in
@@ -478,7 +479,12 @@ __device__ __forceinline__ void load_skip_tables(const GJob& jb, SkipLds<WHOLE>*
 // data.  A step's instructions are what it costs (a wave alone on its SIMD
 // issues one in five cycles, and a look-up's latency is that of twenty-five),
 // so whatever only a block's end needs waits for one: the position, the next
-// block's tables, the sum that its DC difference goes to.
+// block's tables, the sum that its DC difference goes to.  Of a wave's 64
+// lanes some end a block in nearly every look-up, so up to kLooks look-ups are
+// made first, by the lanes that have not come to an end (2: 182, 3: 168, 4:
+// 168, 5: 167 us for the file with markers per row, 345, 324, 325 and 327 for
+// the corpus); a block's DC symbol is then always in the first of them.
+constexpr int kLooks = 4;
 template <bool WHOLE, uint32_t THREADS>
 struct Walker {
   const lds16* skip;
@@ -532,12 +538,38 @@ struct Walker {
   // later with a new first block.
   template <bool COUNT, class Next, class Ended>
   __device__ __forceinline__ void walk(const Next& next, const Ended& ended) {
+    const auto add_dc = [&](uint32_t top, uint32_t bits, uint32_t size) {
+      __hip_atomic_fetch_add(reinterpret_cast<lds32*>(reinterpret_cast<lds8*>(sums) + row),
+                             static_cast<uint32_t>(entry_value(top, bits, size)), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WAVEFRONT);
+    };
+    const auto drop = [&](uint32_t bits, uint32_t word) {
+      sh -= static_cast<int32_t>(bits);
+      const bool over = sh < 0;
+      sh &= 31;
+      w0 = over ? w1 : w0;
+      w1 = over ? word : w1;
+      at += over ? 4u : 0u;
+    };
+    uint32_t top, m, word, bits, to;
+    const auto look = [&]() {
+      top = __builtin_amdgcn_alignbit(w0, w1, static_cast<uint32_t>(sh));
+      m = skip[__builtin_amdgcn_alignbit(t, top, 32 - kSkipLook)];
+      word = next(at);
+      bits = m & 31u;
+      to = k + (m >> 5 & 127u);
+    };
     for (bool on = true; on;) {
-      const uint32_t top = __builtin_amdgcn_alignbit(w0, w1, static_cast<uint32_t>(sh));
-      const uint32_t m = skip[__builtin_amdgcn_alignbit(t, top, 32 - kSkipLook)];
-      const uint32_t word = next(at);
-      uint32_t bits = m & 31u, to = k + (m >> 5 & 127u), size = m >> 12;
-      lds32* sum = reinterpret_cast<lds32*>(reinterpret_cast<lds8*>(sums) + row);
+      look();
+#pragma unroll
+      for (int i = 1; i < kLooks; ++i) {
+        if (to > 63) break;
+        if (COUNT && i == 1) add_dc(top, bits, m >> 12);  // 0 for AC symbols
+        k = to;
+        t = ac;
+        drop(bits, word);
+        look();
+      }
       t = ac;
       bool ends = to > 63;
       if (ends) {
@@ -546,7 +578,7 @@ struct Walker {
           const uint32_t e = whole_entry(k ? ac : slots_dc >> b2 & 3u, top);
           bad = e == kBadEntry;
           bits = bad ? 1u : e & 31u;
-          size = k || bad ? 0u : e >> 5 & 15u;
+          if (COUNT && k == 0 && !bad) add_dc(top, bits, e >> 5 & 15u);
           to = k + (e >> 9);
           ends = to > 63;
         }
@@ -557,15 +589,8 @@ struct Walker {
           on = !ended(pos() + bits);
         }
       }
-      // 0 for AC symbols
-      if constexpr (COUNT) __hip_atomic_fetch_add(sum, static_cast<uint32_t>(entry_value(top, bits, size)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
       k = to;
-      sh -= static_cast<int32_t>(bits);
-      const bool over = sh < 0;
-      sh &= 31;
-      w0 = over ? w1 : w0;
-      w1 = over ? word : w1;
-      at += over ? 4u : 0u;
+      drop(bits, word);
     }
   }
 };
