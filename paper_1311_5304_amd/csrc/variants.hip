@@ -15,7 +15,6 @@
 //          order (no contraction), floor(v + 128.5).
 #include <math.h>
 
-#include <atomic>
 #include <mutex>
 
 #include "aan.h"
@@ -65,14 +64,16 @@ struct View {
 };
 
 // --- grayscale, one block per lane ---------------------------------------------
-// A grayscale MCU is one block, so the blocks lie in raster order.  Each wave
-// takes runs of 64 consecutive blocks, one per lane: the block's 8
-// coefficient rows go straight into registers (the wave's next run loads
-// while this one is transformed), through the fused kernels' dequantise +
-// IDCT of the method (islow: the dot-product passes; ifast, float: the AAN
-// flowgraph on one lane), and out as 8-byte sample rows at any byte address
-// (unaligned access mode, as above), cropped at the image's right and
-// bottom edges.
+// A grayscale MCU is one block, so the blocks lie in raster order.  Each lane
+// takes one, its 8 coefficient rows straight into registers, through the fused
+// kernels' dequantise + IDCT of the method (islow: the dot-product passes;
+// ifast, float: the AAN flowgraph on one lane), and out as 8-byte sample rows
+// at any byte address (unaligned access mode), cropped at the image's right
+// and bottom edges.  Bound by memory: 4093x3070 takes 8.8 us (37.7 MB, 6.9 at
+// the copy kernel's rate).  One run of 64 blocks per wave: waves that loaded
+// the next run while they transformed one held twice the registers, two
+// instead of four of them to a SIMD, and half had two runs and half one (9.6
+// us); through LDS by whole lines it took 9.9.
 constexpr int kGrayThreads = 256;
 constexpr int kGrayWaves = kGrayThreads / 64;
 
@@ -94,80 +95,52 @@ __global__ __launch_bounds__(kGrayThreads) void var_gray(const View v, const Aan
     if (t < 64)
       qs[t] = static_cast<uint32_t>(M == MJD_IDCT_IFAST ? aan_ifast_mult(qt[t], t, k) : aan_float_mult(qt[t], t, k));
   }
-  __syncthreads();
   const lds32* q = (const lds32*)qs;
   const lds32* q16 = (const lds32*)qs16;
   const uint32_t n_blocks = static_cast<uint32_t>(v.n_blocks);
-  const uint32_t n_runs = (n_blocks + 63) / 64;
   const uint32_t lane = static_cast<uint32_t>(t & 63);
-  const uint32_t stride = gridDim.x * kGrayWaves;
   const uint32_t mcx = static_cast<uint32_t>(v.mcus_x);
-  auto load = [&](uint32_t run, v4i rows[8]) {
-    const uint32_t b = run * 64 + lane;
-    if (run < n_runs && b < n_blocks) {
-      const v4i* src = reinterpret_cast<const v4i*>(v.coef) + static_cast<size_t>(b) * 8;
+  const uint32_t b = (blockIdx.x * kGrayWaves + static_cast<uint32_t>(t >> 6)) * 64 + lane;
+  v4i rows[8];
+  {
+    const v4i* src = reinterpret_cast<const v4i*>(v.coef) + static_cast<size_t>(b < n_blocks ? b : n_blocks - 1) * 8;
 #pragma unroll
-      for (int r = 0; r < 8; ++r) rows[r] = src[r];
+    for (int r = 0; r < 8; ++r) rows[r] = src[r];
+  }
+  __syncthreads();  // the table
+  uint32_t out[16];
+  if constexpr (M == MJD_IDCT_ISLOW) idct_block_fast(rows, q, q16, out);  // every lane (a wave-wide range test)
+  else aan_block<M>(rows, reinterpret_cast<const ldsi*>(q), k, out);
+  if (b >= n_blocks) return;
+  const uint32_t by = b / mcx, bx = b - by * mcx;
+  const int px0 = static_cast<int>(bx) * 8;
+  const int n = min(8, v.width - px0);
+  // the output as a global (not flat) pointer: the store instructions
+  gbl8* dst = (gbl8*)(v.out + static_cast<size_t>(by) * 8 * v.pitch + px0);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    if (static_cast<int>(by) * 8 + r >= v.height) break;
+    if (n == 8) {
+      gbl32u* d = reinterpret_cast<gbl32u*>(dst);
+      __builtin_nontemporal_store(out[2 * r], &d[0]);
+      __builtin_nontemporal_store(out[2 * r + 1], &d[1]);
     } else {
-#pragma unroll
-      for (int r = 0; r < 8; ++r) rows[r] = v4i{0, 0, 0, 0};
+      // n = 1..7: a whole dword if n >= 4, then a 16-bit and a byte store
+      if (n >= 4) *reinterpret_cast<gbl32u*>(dst) = out[2 * r];
+      const uint32_t last = n >= 4 ? out[2 * r + 1] : out[2 * r];
+      gbl8* tail = dst + (n & 4);
+      if (n & 2) *reinterpret_cast<gbl16u*>(tail) = static_cast<uint16_t>(last);
+      if (n & 1) tail[n & 2] = static_cast<uint8_t>(last >> (8 * (n & 2)));
     }
-  };
-  uint32_t run = blockIdx.x * kGrayWaves + static_cast<uint32_t>(t >> 6);
-  v4i next[8];
-  load(run, next);
-  for (; run < n_runs; run += stride) {
-    v4i rows[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) rows[r] = next[r];
-    load(run + stride, next);
-    uint32_t out[16];
-    if constexpr (M == MJD_IDCT_ISLOW) idct_block_fast(rows, q, q16, out);  // every lane (a wave-wide range test)
-    else aan_block<M>(rows, reinterpret_cast<const ldsi*>(q), k, out);
-    const uint32_t b = run * 64 + lane;
-    if (b >= n_blocks) continue;
-    const uint32_t by = b / mcx, bx = b - by * mcx;
-    const int px0 = static_cast<int>(bx) * 8;
-    const int n = min(8, v.width - px0);
-    // the output as a global (not flat) pointer: the store instructions
-    gbl8* dst = (gbl8*)(v.out + static_cast<size_t>(by) * 8 * v.pitch + px0);
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      if (static_cast<int>(by) * 8 + r >= v.height) break;
-      if (n == 8) {
-        gbl32u* d = reinterpret_cast<gbl32u*>(dst);
-        __builtin_nontemporal_store(out[2 * r], &d[0]);
-        __builtin_nontemporal_store(out[2 * r + 1], &d[1]);
-      } else {
-        // n = 1..7: a whole dword if n >= 4, then a 16-bit and a byte store
-        if (n >= 4) *reinterpret_cast<gbl32u*>(dst) = out[2 * r];
-        const uint32_t last = n >= 4 ? out[2 * r + 1] : out[2 * r];
-        gbl8* tail = dst + (n & 4);
-        if (n & 2) *reinterpret_cast<gbl16u*>(tail) = static_cast<uint16_t>(last);
-        if (n & 1) tail[n & 2] = static_cast<uint8_t>(last >> (8 * (n & 2)));
-      }
-      dst += v.pitch;
-    }
+    dst += v.pitch;
   }
 }
 
-// Grayscale: as many workgroups as stay resident, at most one wave per run
-// of 64 blocks.
+// Grayscale: a wave per run of 64 blocks.
 template <int M>
-hipError_t launch_gray(const View& v, const AanConsts& k, int cu_count, hipStream_t s) {
-  static std::atomic<int> cached{0};  // resident workgroups per CU (the same on every gfx950 device)
-  int per_cu = cached.load(std::memory_order_relaxed);
-  if (per_cu == 0) {
-    int n = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, var_gray<M>, kGrayThreads, 0);
-    if (e != hipSuccess) return e;
-    per_cu = n > 0 ? n : 1;
-    cached.store(per_cu, std::memory_order_relaxed);
-  }
-  const uint64_t slots = static_cast<uint64_t>(per_cu) * (cu_count > 0 ? cu_count : 256);
+hipError_t launch_gray(const View& v, const AanConsts& k, hipStream_t s) {
   const uint64_t runs = (v.n_blocks + 63) / 64;
-  const uint64_t want = (runs + kGrayWaves - 1) / kGrayWaves;
-  const unsigned grid = static_cast<unsigned>(want < slots ? want : slots);
+  const unsigned grid = static_cast<unsigned>((runs + kGrayWaves - 1) / kGrayWaves);
   hipLaunchKernelGGL(var_gray<M>, dim3(grid), dim3(kGrayThreads), 0, s, v, k);
   return hipGetLastError();
 }
@@ -252,9 +225,9 @@ int mjd_decode_variant(mjd_ctx* ctx, const mjd_variant* variant, const int16_t* 
     v.qsel = variant->frame.qsel[0];
     const AanConsts& k = aan_consts();
     switch (variant->idct) {
-      case MJD_IDCT_ISLOW: e = var::launch_gray<MJD_IDCT_ISLOW>(v, k, ctx->cu_count, s); break;
-      case MJD_IDCT_IFAST: e = var::launch_gray<MJD_IDCT_IFAST>(v, k, ctx->cu_count, s); break;
-      default: e = var::launch_gray<MJD_IDCT_FLOAT>(v, k, ctx->cu_count, s); break;
+      case MJD_IDCT_ISLOW: e = var::launch_gray<MJD_IDCT_ISLOW>(v, k, s); break;
+      case MJD_IDCT_IFAST: e = var::launch_gray<MJD_IDCT_IFAST>(v, k, s); break;
+      default: e = var::launch_gray<MJD_IDCT_FLOAT>(v, k, s); break;
     }
   }
   if (cur != ctx->device) (void)hipSetDevice(cur);
