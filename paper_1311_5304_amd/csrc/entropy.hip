@@ -772,20 +772,22 @@ __global__ __launch_bounds__(FollowShape<MANY>::THREADS) void entropy_follow(con
   }
 }
 
-// Scans N values at once over a group of LANES lanes (64: a wave; more: the
-// workgroup): those of all lanes below go to `below`, those of the whole group
-// to `all`.
+// Scans rows of N words over a group of LANES lanes (64: a wave; more: the
+// workgroup): what then() makes of those of all lanes below goes to `below`,
+// of the whole group's to `all`.
 template <int LANES, int N, class Then>
-__device__ __forceinline__ void scan(const uint32_t (&v)[N], uint32_t none, Then then, uint32_t* lds,
+__device__ __forceinline__ void scan(const uint32_t (&v)[N], const uint32_t (&none)[N], Then then, uint32_t* lds,
                                      uint32_t (&below)[N], uint32_t (&all)[N]) {
   const uint32_t lane = lane_of();
   const auto wave_scan = [&](uint32_t (&x)[N], uint32_t width) {
-    for (uint32_t d = 1; d < width; d <<= 1)
+    for (uint32_t d = 1; d < width; d <<= 1) {
+      uint32_t y[N];
 #pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const uint32_t y = static_cast<uint32_t>(__shfl_up(static_cast<int>(x[i]), d));
-        x[i] = lane >= d ? then(y, x[i]) : x[i];
-      }
+      for (int i = 0; i < N; ++i) y[i] = static_cast<uint32_t>(__shfl_up(static_cast<int>(x[i]), d));
+      then(y, x);  // y: the result
+#pragma unroll
+      for (int i = 0; i < N; ++i) x[i] = lane >= d ? y[i] : x[i];
+    }
   };
   uint32_t x[N];
   for (int i = 0; i < N; ++i) x[i] = v[i];
@@ -793,7 +795,7 @@ __device__ __forceinline__ void scan(const uint32_t (&v)[N], uint32_t none, Then
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const uint32_t y = static_cast<uint32_t>(__shfl_up(static_cast<int>(x[i]), 1));
-    below[i] = lane ? y : none;
+    below[i] = lane ? y : none[i];
     all[i] = static_cast<uint32_t>(__shfl(static_cast<int>(x[i]), 63));
   }
   if constexpr (LANES > 64) {
@@ -807,12 +809,15 @@ __device__ __forceinline__ void scan(const uint32_t (&v)[N], uint32_t none, Then
     for (int i = 0; i < N; ++i) y[i] = lds[i * kGroupWaves + lane % kGroupWaves];
     wave_scan(y, kGroupWaves);
     __syncthreads();
+    uint32_t before[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const uint32_t before = wave ? static_cast<uint32_t>(__shfl(static_cast<int>(y[i]), static_cast<int>(wave) - 1)) : none;
-      below[i] = then(before, below[i]);
+      before[i] = wave ? static_cast<uint32_t>(__shfl(static_cast<int>(y[i]), static_cast<int>(wave) - 1)) : none[i];
       all[i] = static_cast<uint32_t>(__shfl(static_cast<int>(y[i]), kGroupWaves - 1));
     }
+    then(before, below);
+#pragma unroll
+    for (int i = 0; i < N; ++i) below[i] = before[i];
   }
 }
 
@@ -835,24 +840,29 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
   const uint32_t c0 = id * per < last ? id * per : last, c1 = c0 + per < last ? c0 + per : last;
   const uint64_t* links = reinterpret_cast<const uint64_t*>(pl.links) + sp.chunk0;
   // the maps of a run of chunks from chunk c on
-  auto load_maps = [&](uint32_t c, uint32_t (&maps)[kRun]) {
+  auto load_maps = [&](uint32_t c, SlotMap (&maps)[kRun]) {
     uint64_t l[kRun];
 #pragma unroll
     for (uint32_t i = 0; i < kRun; ++i) l[i] = links[c + i < c1 ? c + i : c];
 #pragma unroll
     for (uint32_t i = 0; i < kRun; ++i) maps[i] = map_of_links(l[i]);
   };
-  uint32_t maps[kRun];
-  uint32_t m[1] = {kSameSlots}, below[1], all_map[1];
+  SlotMap maps[kRun], mine = kSameSlots;
   for (uint32_t c = c0; c < c1; c += kRun) {
     load_maps(c, maps);
 #pragma unroll
     for (uint32_t i = 0; i < kRun; ++i)
-      if (c + i < c1) m[0] = map_then(m[0], maps[i]);
+      if (c + i < c1) mine = map_then(mine, maps[i]);
   }
-  scan<LANES, 1>(m, kSameSlots, [](uint32_t a, uint32_t b) { return map_then(a, b); }, lds, below, all_map);
-  const uint32_t slot0 = below[0] & 15u;  // the slot of chunk c0 that the chain enters by
-  // a run's slots along the chain (kNoLink after a missing link) and hops
+  const uint32_t m[2] = {mine.lo, mine.hi}, same[2] = {kSameSlots.lo, kSameSlots.hi};
+  uint32_t below[2], all_map[2];
+  scan<LANES, 2>(m, same, [](uint32_t (&x)[2], const uint32_t (&y)[2]) {
+    const SlotMap r = map_then(SlotMap{x[0], x[1]}, SlotMap{y[0], y[1]});
+    x[0] = r.lo;
+    x[1] = r.hi;
+  }, lds, below, all_map);
+  const uint32_t slot0 = below[0] & 255u;  // the slot of chunk c0 that the chain enters by
+  // a run's slots along the chain (none after a missing link) and hops
   struct Run {
     uint32_t slot[kRun];
     GHop hop[kRun][kParts];
@@ -862,7 +872,7 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
 #pragma unroll
     for (uint32_t i = 0; i < kRun; ++i) {
       r->slot[i] = slot;
-      slot = slot < kSlots ? maps[i] >> (4 * slot) & 15u : kNoLink;
+      slot = map_bytes(maps[i], slot) & 255u;
     }
 #pragma unroll
     for (uint32_t i = 0; i < kRun; ++i) {
@@ -903,7 +913,10 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
     broken = broken_lds;
   }
   uint32_t at[4], all[4];
-  scan<LANES, 4>(s, 0u, [](uint32_t a, uint32_t b) { return a + b; }, lds, at, all);
+  const uint32_t zero[4] = {0, 0, 0, 0};
+  scan<LANES, 4>(s, zero, [](uint32_t (&x)[4], const uint32_t (&y)[4]) {
+    for (int i = 0; i < 4; ++i) x[i] += y[i];
+  }, lds, at, all);
   // `state`: where part `part` of chunk c begins; n: its blocks
   auto task = [&](uint32_t c, uint32_t part, uint32_t state, uint32_t n, const uint32_t before[4]) {
     const uint32_t done = before[0] < iv.n_blocks ? before[0] : iv.n_blocks;
@@ -951,7 +964,7 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
   }
   for (uint32_t c = last + id; c < sp.n_chunks; c += LANES)
     for (uint32_t j = 0; j < kParts; ++j) {
-      if (c == last && j == 0 && stop == last) task(c, 0, entry(c, all_map[0] & 15u), iv.n_blocks, all);
+      if (c == last && j == 0 && stop == last) task(c, 0, entry(c, all_map[0] & 255u), iv.n_blocks, all);
       else no_task(c, j);
     }
 }

@@ -181,26 +181,35 @@ MJD_HD inline uint32_t make_state(uint32_t bits, uint32_t b) { return bits << 3 
 constexpr uint32_t kGuesses = 6, kSlots = 8;
 constexpr uint32_t kNoLink = 15;
 
-// Maps of a chunk's slots to the next chunk's, four bits a slot; anything
-// above 7 is no slot.
-constexpr uint32_t kSameSlots = 0x76543210u;
-MJD_HD inline uint32_t map_of_links(uint64_t links) {
-  uint32_t m = 0;
-  for (uint32_t i = 0; i < kSlots; ++i) {
-    const uint32_t v = static_cast<uint32_t>(links >> (8 * i)) & 0xFFu;
-    m |= (v < kSlots ? v : kNoLink) << (4 * i);
+// Maps of a chunk's slots to the next chunk's, a byte a slot, anything above
+// 12 for no slot: the links as they are stored, with 8 to 12 (which no link
+// is) made so, because a byte permute takes one map through another.
+struct SlotMap {
+  uint32_t lo, hi;  // slots 0-3, 4-7
+};
+constexpr SlotMap kSameSlots{0x03020100u, 0x07060504u};
+MJD_HD inline uint32_t no_slot_above_7(uint32_t x) {
+  const uint32_t b = x & 0x08080808u;
+  return x | b >> 1 | b >> 2 | b >> 3;
+}
+MJD_HD inline SlotMap map_of_links(uint64_t links) {
+  return SlotMap{no_slot_above_7(static_cast<uint32_t>(links)), no_slot_above_7(static_cast<uint32_t>(links >> 32))};
+}
+// For each byte of `slots`, what `m` maps it to.
+MJD_HD inline uint32_t map_bytes(SlotMap m, uint32_t slots) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_perm(m.hi, m.lo, slots);
+#else
+  uint32_t r = 0;
+  for (uint32_t i = 0; i < 4; ++i) {
+    const uint32_t s = slots >> (8 * i) & 0xFFu;
+    r |= (s < 4 ? m.lo >> (8 * s) & 0xFFu : s < kSlots ? m.hi >> (8 * (s - 4)) & 0xFFu : 0xFFu) << (8 * i);
   }
-  return m;
+  return r;
+#endif
 }
 // First `a`, then `b`.
-MJD_HD inline uint32_t map_then(uint32_t a, uint32_t b) {
-  uint32_t m = 0;
-  for (uint32_t i = 0; i < kSlots; ++i) {
-    const uint32_t j = (a >> (4 * i)) & 15u;
-    m |= (j < kSlots ? (b >> (4 * j)) & 15u : kNoLink) << (4 * i);
-  }
-  return m;
-}
+MJD_HD inline SlotMap map_then(SlotMap a, SlotMap b) { return SlotMap{map_bytes(b, a.lo), map_bytes(b, a.hi)}; }
 
 }  // namespace gent
 }  // namespace mjd
