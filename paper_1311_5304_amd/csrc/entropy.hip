@@ -1182,8 +1182,9 @@ struct Layout {
 //   there are (188 intervals of 14 KB: 7780 us, 9619 of 1.8 KB: 1000 us), and
 //   a batch of them at least 5.5 us a MB (1.3 million intervals of 0.2 KB:
 //   1740 us for 274 MB);
-// - a split batch takes 100 us more than 22 us a MB (2.5 MB: 226 us, 381 MB:
-//   7880 us).
+// - a split batch takes 110 us more than 12.5 us a MB (2.5 MB: 165 us, 36 MB:
+//   531, where whole intervals of 1.9 KB take 957; 77 MB: 1067 against 1026;
+//   211 MB: 2740).
 // Splitting is for what fits kSplitMost, which bounds its tables (2.8 bytes
 // per byte).
 constexpr uint64_t kSplitMost = uint64_t{256} << 20;
@@ -1206,7 +1207,7 @@ static uint32_t split_threshold(const std::vector<GInterval>& ivs) {
   for (int i = 32; i >= 7; --i) {  // all above 2^i are split
     uint32_t most = 0;
     for (int j = 0; j <= i; ++j) most = std::max(most, longest[j]);
-    const double t = (split ? 100.0 + 22e-6 * static_cast<double>(split) : 0.0) +
+    const double t = (split ? 110.0 + 12.5e-6 * static_cast<double>(split) : 0.0) +
                      std::max(0.41 * most, 5.5e-6 * static_cast<double>(rest));
     if (split <= kSplitMost && (i == 32 || t < best)) {
       best = t;
