@@ -134,7 +134,7 @@ static int batch_slots(mjd_ctx* ctx) {
   return per_cu * (ctx->cu_count > 0 ? ctx->cu_count : 256);
 }
 
-int batch_plan(mjd_ctx* ctx, const mjd_job* jobs, size_t n, int upsample, BatchPlan* plan) {
+int batch_plan(mjd_ctx* ctx, const mjd_job* jobs, size_t n, int upsample, BatchPlan* plan, uint64_t max_items) {
   if (n == 0) return fail(MJD_EINVAL, "empty batch");
   if (n > (1u << 24)) return fail(MJD_EINVAL, "batch of %zu images too large", n);
   if (upsample != MJD_UPSAMPLE_SIMPLE && upsample != MJD_UPSAMPLE_FANCY)
@@ -163,12 +163,21 @@ int batch_plan(mjd_ctx* ctx, const mjd_job* jobs, size_t n, int upsample, BatchP
   // Segment length: about 4 segments per resident workgroup over the whole
   // batch, so the queue balances the tail, and at most 6 sub-tiles, past which
   // the tail costs more than the segments' ends (48 mixed images of 252 MP:
-  // 530 us with 6, 541 with 12, 575 with 26, which 4 a workgroup gives); the
-  // tuning knob overrides it.
+  // 530 us with 6, 541 with 12, 575 with 26, which 4 a workgroup gives), unless
+  // the caller has no room for so many; the tuning knob overrides it.
   int seg_sub = static_cast<int>(ctx->tuning.seg_subtiles);
   if (seg_sub <= 0) {
     const uint64_t want = static_cast<uint64_t>(slots) * 4;
-    seg_sub = static_cast<int>(std::min<uint64_t>(6, std::max<uint64_t>(1, (subtiles + want - 1) / want)));
+    const int all = static_cast<int>(std::max<uint64_t>(1, (subtiles + want - 1) / want));
+    seg_sub = std::min(6, all);
+    uint64_t items = 0;
+    for (size_t i = 0; i < n && seg_sub < all; ++i) {
+      int sx, sy;
+      class_shape(cls[i], &sx, &sy);
+      const uint64_t rows = geo[i].mcus_y, seg_rows = static_cast<uint64_t>(seg_sub) * sy;
+      items += (geo[i].mcus_x + sx - 1) / sx * ((rows + seg_rows - 1) / seg_rows);
+    }
+    if (items > max_items) seg_sub = all;
   }
   for (size_t i = 0; i < n; ++i) {
     int sx, sy;
@@ -344,11 +353,12 @@ int mjd_decode_batch_noalloc(mjd_ctx* ctx, const mjd_job* jobs, size_t n, int up
   if (!jobs && n) return mjd::fail(MJD_EINVAL, "null jobs");
   if (!ctx->noalloc_scratch) return mjd::fail(MJD_EDEVICE, "no scratch address for device %d", ctx->device);
   mjd::BatchPlan plan;
-  int rc = mjd::batch_plan(ctx, jobs, n, upsample, &plan);
-  if (rc != MJD_OK) return rc;
-  const size_t views_bytes = plan.views.size() * sizeof(mjd::ImageView);
-  const size_t items_bytes = plan.items.size() * sizeof(mjd::BatchItem);
+  const size_t views_bytes = n * sizeof(mjd::ImageView);
   const size_t items_off = mjd::kNoAllocHeader + ((views_bytes + 255) & ~size_t(255));
+  const uint64_t room = items_off < mjd::kNoAllocScratchBytes ? (mjd::kNoAllocScratchBytes - items_off) / sizeof(mjd::BatchItem) : 0;
+  int rc = mjd::batch_plan(ctx, jobs, n, upsample, &plan, room);
+  if (rc != MJD_OK) return rc;
+  const size_t items_bytes = plan.items.size() * sizeof(mjd::BatchItem);
   const size_t need = items_off + items_bytes;
   if (need > mjd::kNoAllocScratchBytes)
     return mjd::fail(MJD_EBUDGET, "batch tables need %zu bytes; the no-allocation entry point holds at most %zu",

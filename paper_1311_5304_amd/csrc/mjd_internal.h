@@ -62,7 +62,10 @@ struct BatchPlan {
   int grid = 0;
 };
 
-int batch_plan(mjd_ctx* ctx, const mjd_job* jobs, size_t n, int upsample, BatchPlan* plan);
+// At most max_items segments, where their length is the library's choice and
+// longer ones can be as few.
+int batch_plan(mjd_ctx* ctx, const mjd_job* jobs, size_t n, int upsample, BatchPlan* plan,
+               uint64_t max_items = ~uint64_t{0});
 
 // Enqueues the persistent batch kernel over tables already on the device.
 // d_counters (2 words) must be zero; the kernel leaves them zero.

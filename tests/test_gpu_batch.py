@@ -135,3 +135,21 @@ def test_batch_rejects_bad_job(M, ctx, batch_inputs):
     assert "job 1" in str(ei.value)
     with pytest.raises(M.MjdError):
         M.Batch(ctx, [], M.MJD_UPSAMPLE_FANCY)
+
+
+def test_noalloc_takes_batches_of_more_short_segments_than_it_holds(M, ctx):
+    # 50 times one 8192x8192 image: 137,600 segments of 6 sub-tiles, more than
+    # the tables' 4 MiB, so the plan goes on with longer ones
+    w = h = 8192
+    frame = {"width": w, "height": h, "h": (1, 1, 1), "v": (1, 1, 1), "qsel": (0, 1, 1)}
+    n = M.mjd_geometry_of(frame)["n_blocks"]
+    g = torch.Generator(device="cuda").manual_seed(5)
+    coef = torch.zeros((n, 64), dtype=torch.int16, device="cuda")
+    coef[:, 0] = torch.randint(-900, 900, (n,), generator=g, device="cuda", dtype=torch.int16)
+    qt = torch.ones(256, dtype=torch.int16, device="cuda")
+    exp = M.decode(ctx, frame, coef, qt, "simple")
+    out = torch.full((h, w, 3), 3, dtype=torch.uint8, device="cuda")
+    say("50 x 8192x8192 without allocation")
+    M.mjd_decode_batch_noalloc(ctx, [(frame, coef, qt, out, 3 * w)] * 50, M.MJD_UPSAMPLE_SIMPLE)
+    torch.cuda.synchronize()
+    assert torch.equal(out, exp)
