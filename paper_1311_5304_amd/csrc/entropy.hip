@@ -448,7 +448,10 @@ struct WordRing {
 //            slots), and turns counts and sums into each chunk's task.
 // An interval whose chain breaks (no free slot, or not within kMaxHops
 // chunks, as textures that repeat can make it) is decoded by one lane from
-// that chunk on.
+// that chunk on.  The exits that a guess repeats leave their slots free for
+// that reason: with two free slots a chunk, 5 of 16 files of quality 95 with a
+// marker per row and 1 of 16 without had a broken chain (0.8 to 24 ms instead
+// of 0.2), with these none of 96.
 // Both kernels are bound by a lane's chain of look-ups where lanes are few and
 // by instruction issue where they are many, so a look-up takes several symbols
 // (skip tables; 11 bits of look-up instead of 12 cost 2% and leave room for
@@ -642,6 +645,7 @@ struct ChunkOf {
 __global__ __launch_bounds__(kGuessThreads) void entropy_guess(const GPlan pl) {
   __shared__ SkipLds<true> tables;
   __shared__ uint32_t staged[kGuessWords];
+  __shared__ uint32_t exits[kGuessThreads];
   const GGroup g = pl.groups[blockIdx.x];
   const GJob& jb = pl.jobs[g.job];
   const uint32_t n = g.count * kChunkWords + kBlockWords;
@@ -650,21 +654,26 @@ __global__ __launch_bounds__(kGuessThreads) void entropy_guess(const GPlan pl) {
   __syncthreads();
   Walker<true, kGuessThreads> walk(jb, &tables, nullptr);
   const uint32_t tries = jb.bpm, mine = threadIdx.x / tries, first = threadIdx.x - mine * tries;
-  if (mine >= g.count) return;
-  const uint32_t chunk = g.first + mine;
+  const bool used = mine < g.count;
+  const uint32_t chunk = g.first + (used ? mine : 0u);
   const ChunkOf at(pl, g, chunk, (lds32*)staged, n);
   uint32_t state = kNoState;
-  if (at.c < at.last && (at.c > 0 || first == 0)) {
+  if (used && at.c < at.last && (at.c > 0 || first == 0)) {
     const uint32_t target = (mine + 1) * (kChunk * 8);
     walk.open(at.words.open(at.c * kChunkWords, 0), at.words.off);
     walk.block(2 * first);
     walk.walk<false>([&](uint32_t i) { return at.staged(i); },
                      [&](uint32_t pos) { return static_cast<int32_t>(pos - target) >= 0; });
-    state = make_state(walk.pos() - target, walk.b2 / 2);
+    state = make_state(walk.pos() - target, walk.b2 / 2) | kGuessed;
   }
+  exits[threadIdx.x] = state;
+  __syncthreads();
+  if (!used) return;
+  for (uint32_t j = 0; j < first; ++j)
+    if (exits[threadIdx.x - first + j] == state) state = kNoState;
   uint32_t* own = pl.states + static_cast<uint64_t>(chunk) * kSlots;
   if (at.c == 0 && first == 0) {
-    own[0] = make_state(0, 0);
+    own[0] = make_state(0, 0) | kGuessed;
     for (uint32_t i = 1; i < kSlots; ++i) own[i] = kNoState;
   }
   if (at.c + 1 < at.sp.n_chunks) {
@@ -681,7 +690,7 @@ __global__ __launch_bounds__(FollowShape<MANY>::THREADS) void entropy_follow(con
   __shared__ SkipLds<!MANY> tables;
   __shared__ uint32_t staged[F::WORDS];
   __shared__ uint32_t sums[3 * THREADS];
-  __shared__ uint16_t list[F::GROUP * kGuesses];  // chunk in the group << 3 | slot, without the empty and repeated ones
+  __shared__ uint16_t list[F::GROUP * kGuesses];  // chunk in the group << 3 | slot of the boundaries that were guessed
   __shared__ uint32_t n_list;
   const GGroup g = pl.groups[pl.n_groups + blockIdx.x];
   const GJob& jb = pl.jobs[g.job];
@@ -696,11 +705,9 @@ __global__ __launch_bounds__(FollowShape<MANY>::THREADS) void entropy_follow(con
     const uint32_t i = i0 + threadIdx.x, mine = i / tries, slot = i - mine * tries;
     bool use = mine < g.count;
     if (use) {
-      const uint32_t* s = pl.states + static_cast<uint64_t>(g.first + mine) * kSlots;
-      const uint32_t own = s[slot];
-      use = own != kNoState;
-      for (uint32_t j = 0; j + 1 < kGuesses; ++j)
-        if (j < slot && s[j] == own) use = false;
+      // not those that a lane of the chunk before has put there by now
+      const uint32_t own = pl.states[static_cast<uint64_t>(g.first + mine) * kSlots + slot];
+      use = own != kNoState && (own & kGuessed);
     }
     const uint64_t m = __ballot(use);
     uint32_t base = 0;
@@ -715,7 +722,7 @@ __global__ __launch_bounds__(FollowShape<MANY>::THREADS) void entropy_follow(con
     const ChunkOf at(pl, g, chunk, (lds32*)staged, n);
     uint32_t c = at.c;
     if (c >= at.last) continue;
-    const uint32_t from = pl.states[static_cast<uint64_t>(chunk) * kSlots + slot];
+    const uint32_t from = pl.states[static_cast<uint64_t>(chunk) * kSlots + slot] & ~kGuessed;
     walk.open(at.words.open(c * kChunkWords + (from >> 8), (from >> 3) & 31u), at.words.off);
     walk.block(2 * (from & 7u));
     for (bool on = true; on;) {
@@ -754,10 +761,14 @@ __global__ __launch_bounds__(FollowShape<MANY>::THREADS) void entropy_follow(con
       hop[1] = h1;
       uint32_t link = kNoLink;
       for (uint32_t j = kGuesses; j-- > 0;)
-        if (guessed[j] == state) link = j;
+        if (guessed[j] == (state | kGuessed)) link = j;
       on = false;  // unless this lane goes on from a slot of its own
       if (link == kNoLink && ++hops < kMaxHops) {
-        for (uint32_t j = kGuesses; j < kSlots && link == kNoLink; ++j) {
+        // the first free slot; whoever took it for the same boundary before
+        // found those below it taken too
+#pragma unroll
+        for (uint32_t j = 0; j < kSlots; ++j) {
+          if (link != kNoLink || (j < kGuesses && guessed[j] != kNoState && (guessed[j] & kGuessed))) continue;
           const uint32_t was = atomicCAS(&to[j], kNoState, state);
           if (was == kNoState || was == state) link = j;
           on = was == kNoState;
@@ -934,7 +945,7 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
   };
   auto no_task = [&](uint32_t c, uint32_t part) { task(c, part, 0, 0, s); };
   auto entry = [&](uint32_t c, uint32_t in) {
-    return in < kSlots ? pl.states[static_cast<uint64_t>(sp.chunk0 + c) * kSlots + in] : 0u;
+    return in < kSlots ? pl.states[static_cast<uint64_t>(sp.chunk0 + c) * kSlots + in] & ~kGuessed : 0u;
   };
   // up to the broken chunk each part decodes its own blocks; the first of
   // that chunk, or of the last, all that are left

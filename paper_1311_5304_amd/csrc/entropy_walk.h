@@ -176,9 +176,11 @@ MJD_HD inline int32_t entry_value(uint32_t top, uint32_t total, uint32_t size) {
 constexpr uint32_t kNoState = 0xFFFFFFFFu;
 MJD_HD inline uint32_t make_state(uint32_t bits, uint32_t b) { return bits << 3 | b; }
 
-// Slots of a chunk: the exits of the chunk before it for each first block
-// that is tried there, and two for boundaries that none of them reached.
+// Slots of a chunk: the distinct exits of the chunk before it for the first
+// blocks that are tried there, marked, and the boundaries that none of them
+// reached, in the slots that are left (six on average for 4:2:0, at least two).
 constexpr uint32_t kGuesses = 6, kSlots = 8;
+constexpr uint32_t kGuessed = 1u << 31;
 constexpr uint32_t kNoLink = 15;
 
 // Maps of a chunk's slots to the next chunk's, a byte a slot, anything above
