@@ -465,8 +465,8 @@ def variants_workload(args, M, ctx, dev):
     headline 4:2:0 fancy coefficients and on h1v2 and 4:1:1 coefficient sets
     (seeded decaying random blocks on the documented domain), all through
     the fused segment kernel; grayscale (one launch); and the headline image
-    decoded at 1/2, 1/4 and 1/8 (two launches with sample planes between
-    them; MPix/s counts the source image's pixels).  Four buffer sets rotate
+    decoded at 1/2, 1/4 and 1/8 (one launch;
+    MPix/s counts the source image's pixels).  Four buffer sets rotate
     so the working set exceeds the 256 MB Infinity Cache.  Algorithmic bytes
     are the coefficients read and the output written."""
     import torch
@@ -539,8 +539,8 @@ def variants_workload(args, M, ctx, dev):
 
 def gpu_entropy_workload(args, M, ctx, dev, jpgs, frames, sample_idx, sample):
     """The same corpus decoded on the device end to end: the bitstreams
-    resident in HBM, Huffman decoding by the entropy kernel (one lane per
-    restart interval, all images in one persistent launch), then the batched
+    resident in HBM, Huffman decoding by the entropy kernels (all images in
+    one batch), then the batched
     back half (one persistent launch) into RGB8 buffers in HBM.  Planning
     (headers, restart index, tables) happens before the timed region; the
     host->device copy of the bitstreams is timed on its own."""

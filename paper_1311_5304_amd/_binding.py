@@ -538,7 +538,7 @@ def mjd_entropy_decode(jpg, scan: mjd_scan, offsets, coef, row0: int, row1: int,
 
 class EntropyBatch:
     """Owns an mjd_entropy_batch*: Huffman decoding of many scans on the GPU,
-    one lane per restart interval."""
+    by restart intervals and by chunks of the long ones."""
 
     def __init__(self, ctx: Context, jobs):
         """jobs: sequence of (scan, offsets, d_jpg, length, d_coef): the mjd_scan

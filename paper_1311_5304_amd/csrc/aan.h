@@ -8,8 +8,7 @@
 //   float: IEEE single precision, multipliers fp32(q / (8 s(u) s(v))), one
 //          rounding per operation in the order written (no fused
 //          multiply-adds), output floor(v + 128.5).
-// Both the two-launch variant kernels and the fused segment decoder use
-// these.
+// Both the grayscale kernel and the fused segment decoder use these.
 #pragma once
 
 #include <hip/hip_runtime.h>

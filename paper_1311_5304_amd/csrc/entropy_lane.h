@@ -1,21 +1,21 @@
-// Huffman decoding of one restart interval of a baseline scan, written once
-// for one GPU lane and, through small memory interfaces, for a CPU caller
-// too.  The paper leaves entropy decoding on the CPU because code words have
-// variable length (Sec. 1); restart intervals restart the bit stream and the
-// DC predictions, so each of them decodes on its own (ITU-T T.81 restart
-// markers).
+// Huffman decoding of one restart interval of a baseline scan: the tables'
+// entry format, which the GPU kernels share, and a sequential decoder over
+// small memory interfaces for CPU callers (the kernels work on destuffed
+// words, entropy_walk.h).  The paper leaves entropy decoding on the CPU
+// because code words have variable length (Sec. 1); restart intervals restart
+// the bit stream and the DC predictions, so each of them decodes on its own
+// (ITU-T T.81 restart markers).
 //
-// A lane advances one Huffman symbol per call of lane_step, so that the 64
-// lanes of a wave, each in its own interval, run the same short path:
+// One Huffman symbol is decoded per call of lane_step, every kind on one
+// short path:
 // - one 16-bit table entry gives the length, zero run and magnitude size of
 //   any code of at most kGLook bits, and the magnitude bits are read from
 //   the same 32-bit window (T.81 F.1.2.2, F.2.2.1);
 // - longer codes take their length from the left-aligned code-space limits
 //   of the canonical code (T.81 Annex C), without a loop over lengths;
 // - a finished block leaves through the block interface.
-// The stream comes through StreamRing, which serves bytes from a per-lane
-// ring filled ahead of use at points the whole wave reaches together, so
-// that loads are issued well before any lane waits for them.
+// The stream comes through StreamRing, which serves bytes from a ring that is
+// filled ahead of use.
 #pragma once
 
 #include <stdint.h>
