@@ -67,8 +67,10 @@ struct GTile {
 
 // An interval decoded by chunks of destuffed bytes.  Chunks are numbered over
 // the batch, a job's one after the other, and lie in that order in memory.
-// 128 bytes: the 12-image corpus of 4:2:0 files takes 500 us, 625 with 256
-// and 1050 with 512; shorter ones leave more boundaries unguessed.
+// 128 bytes: a 12-image corpus of 4:2:0 files took 500 us, 625 with 256 and
+// 1050 with 512.  64 bytes leave more boundaries unguessed: a 4000x3000 file
+// with markers per row takes 129 instead of 166 us, but 5 of 16 files of
+// quality 95 without markers had a broken chain, which costs tens of ms.
 constexpr uint32_t kChunk = 128, kChunkWords = kChunk / 4;
 struct GSplit {
   uint32_t iv, chunk0, n_chunks;
@@ -604,7 +606,7 @@ struct Walker {
 // the tables, as 256 left half as many waves a CU (145 us in entropy_guess for
 // the 12-image corpus, 115 here).
 constexpr uint32_t kGuessThreads = 512, kGuessGroup = 85;
-constexpr uint32_t kGuessWords = kGuessGroup * kChunkWords + kBlockWords;
+constexpr uint32_t kGuessWords = (kGuessGroup * kChunkWords + kBlockWords + 3) & ~3u;
 // About two boundaries a chunk to follow.  Where more chunks come together
 // than the small workgroups hold that fit on the chip at once, larger ones
 // with the whole tables in memory have twice the waves a CU: 145 -> 110 us for
@@ -648,7 +650,7 @@ __global__ __launch_bounds__(kGuessThreads) void entropy_guess(const GPlan pl) {
   __shared__ uint32_t exits[kGuessThreads];
   const GGroup g = pl.groups[blockIdx.x];
   const GJob& jb = pl.jobs[g.job];
-  const uint32_t n = g.count * kChunkWords + kBlockWords;
+  const uint32_t n = (g.count * kChunkWords + kBlockWords + 3) & ~3u;
   stage_words((lds32*)staged, (gin128*)(pl.data + static_cast<uint64_t>(g.first) * kChunk), n, threadIdx.x, kGuessThreads);
   load_skip_tables<true, kGuessThreads>(jb, &tables);
   __syncthreads();
