@@ -197,22 +197,42 @@ static hipError_t launch_variant_method(const ImageView& im, int hf, int vf, boo
   }
 }
 
+// The default sub-tile shapes of the classes without row pairs, with lanes
+// enough to convert a sub-tile in one round (4:4:4: two) instead of two to
+// six: for images of at most one sub-tile a CU, whose time is one workgroup's.
+static constexpr Shape kSmall420S = shape_of<SegCfg<2, 2, false, 16, 2, 512>>();
+static constexpr Shape kSmall422F = shape_of<SegCfg<2, 1, true, 8, 4, 512>>();
+static constexpr Shape kSmall422S = shape_of<SegCfg<2, 1, false, 16, 2, 512>>();
+static constexpr Shape kSmall444 = shape_of<SegCfg<1, 1, false, 16, 4, 512>>();
+
 hipError_t launch_image(const ImageView& im, int row0, int row1, int hf, int vf, bool fancy, int cu_count,
                         const mjd_tuning& tu, hipStream_t stream) {
   const Shape* l;
   int n;
   class_shapes(hf, vf, fancy, &l, &n);
   int i = static_cast<int>(tu.shape) < n ? static_cast<int>(tu.shape) : 0;
+  const int cus = cu_count > 0 ? cu_count : 256;
+  auto tiles = [&](const Shape& sh) {
+    return static_cast<int64_t>((im.mcus_x + sh.sx - 1) / sh.sx) * ((row1 - row0 + sh.sy - 1) / sh.sy);
+  };
+  // 256x256: 4:2:0 simple 6.2 -> 5.5 us, 4:2:2 simple 5.7 -> 5.0, 4:4:4 5.8 ->
+  // 5.2, 4:2:2 fancy 6.0 -> 5.7; 1024x768 (96 to 192 sub-tiles) 6.5 -> 5.8,
+  // 5.9 -> 5.4, 6.1 -> 5.5, 6.3 -> 6.0; at 1921x1081 (272 to 544) the wide
+  // workgroups, of which one fits a CU, take 10.0 for 8.2, 11.0 for 7.9, 11.6
+  // for 9.2 and 11.9 for 8.7.
+  if (tu.shape == 0 && tu.seg_subtiles == 0 && tu.workgroups == 0) {
+    const Shape* small = l == k420S ? &kSmall420S : l == k422S ? &kSmall422S : l == k444 ? &kSmall444 : l == k422F ? &kSmall422F : nullptr;
+    if (small && tiles(*small) <= cus) return small->launch(im, row0, row1, cu_count, tu, stream);
+  }
   // Fancy 4:2:2 images that give each workgroup one or two sub-tiles of the
   // default shape take the 8x4 one, whose fourth wave shares the second phase:
   // 256x256 7.4 -> 6.3 us, 1921x1081 10.1 -> 9.1, 2592x1944 15.1 -> 13.2; at
   // 4096x3072 the two are equal (21.4, 21.1), at 6000x4000 the default leads.
   if (l == k422F && tu.shape == 0 && tu.seg_subtiles == 0) {
-    const int64_t tiles = static_cast<int64_t>((im.mcus_x + l[0].sx - 1) / l[0].sx) * ((row1 - row0 + l[0].sy - 1) / l[0].sy);
     int per_cu = 0;
     const hipError_t e = l[0].per_cu(&per_cu);
     if (e != hipSuccess) return e;
-    if (tiles <= 2ll * per_cu * (cu_count > 0 ? cu_count : 256)) i = 2;
+    if (tiles(l[0]) <= 2ll * per_cu * cus) i = 2;
   }
   return l[i].launch(im, row0, row1, cu_count, tu, stream);
 }

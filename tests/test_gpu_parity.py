@@ -284,3 +284,31 @@ def test_422_fancy_default_shape_equals_every_shape(M, ctx, w, h):
             assert torch.equal(M.decode(ctx, frame, c, q, "fancy"), got), shape
     finally:
         M.mjd_ctx_set_tuning(ctx, 0, 0, 0)
+
+
+@pytest.mark.parametrize("h,v,mode", [(1, 1, "fancy"), (2, 1, "simple"), (2, 1, "fancy"), (2, 2, "simple")])
+def test_small_images_default_launch_equals_the_shapes(M, ctx, h, v, mode):
+    # up to one sub-tile a CU and just past it, partial sub-tiles on both
+    # sides, padded rows at odd addresses
+    rng = np.random.default_rng(10 * h + v)
+    for w, hh in ((1, 1), (129, 33), (257, 190), (1024, 768), (1031, 1001), (1921, 1081)):
+        frame = {"width": w, "height": hh, "h": (h, 1, 1), "v": (v, 1, 1), "qsel": (0, 1, 1)}
+        n = M.mjd_geometry_of(frame)["n_blocks"]
+        coef = (rng.standard_normal((n, 64)) * (40 / (1 + np.arange(64)))).astype(np.int16)
+        qt = rng.integers(1, 17, (4, 64)).astype(np.uint16)
+        c, q = to_dev(coef, qt)
+        say(f"default launch {h}x{v} {mode} {w}x{hh}")
+        pitch = 3 * w + 5
+        buf = torch.full((hh * pitch + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        M.mjd_decode(ctx, frame, c, q, M.UPSAMPLE[mode], buf.data_ptr() + 1, pitch, 0, M.mjd_geometry_of(frame)["mcus_y"])
+        torch.cuda.synchronize()
+        rows = buf.cpu().numpy()[1:1 + hh * pitch].reshape(hh, pitch)
+        assert np.all(rows[:, 3 * w:] == 0xA5) and int(buf[0]) == 0xA5 and bool((buf[1 + hh * pitch:] == 0xA5).all())
+        got = rows[:, :3 * w].reshape(hh, w, 3)
+        if w * hh < 100000:
+            assert_same(got, oracle.decode(frame, coef, qt, mode), f"{w}x{hh}")
+        try:
+            M.mjd_ctx_set_tuning(ctx, 1, 0, 0)  # a shape of the list
+            assert np.array_equal(M.decode(ctx, frame, c, q, mode).cpu().numpy(), got)
+        finally:
+            M.mjd_ctx_set_tuning(ctx, 0, 0, 0)
