@@ -1,0 +1,185 @@
+"""The GPU entropy decoder's plan and kernels, entropy.hip itself, run on the
+CPU (CPU only) under AddressSanitizer and UBSan: lanes as fibers, every table,
+stream and coefficient buffer in memory of exactly its size.  The host decoder
+says what each stream holds: every coefficient of a valid one is equal, and a
+damaged one is reported, whatever its bytes.  Coefficients are whole numbers:
+no tolerance."""
+import os
+import random
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from synth import bitstream, encode, images
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1311_5304_amd", "csrc")
+LUMA = {"444": (1, 1), "422": (2, 1), "420": (2, 2), "440": (1, 2), "411": (4, 1)}
+CHUNK = 128  # bytes of a chunk of a split interval
+
+
+def clang():
+    for cand in ("/opt/rocm/llvm/bin/clang++", shutil.which("clang++")):
+        if cand and os.path.exists(cand):
+            return cand
+    pytest.skip("no clang++ (the kernels' vector types)")
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    d = tmp_path_factory.mktemp("kernels")
+    # the source as it is, beside a header that stands for the library's own
+    shutil.copy(os.path.join(CSRC, "entropy.hip"), d / "entropy_under_test.h")
+    (d / "mjd_internal.h").write_text("#pragma once\n")
+    exe = str(d / "harness")
+    sanitize = ["-fsanitize=address,undefined", "-fno-sanitize=alignment", "-fno-sanitize-recover=undefined",
+                "-fsanitize-address-use-after-return=never"]
+    r = subprocess.run([clang(), "-x", "c++", "-O1", "-g", "-std=c++17", "-fwrapv", "-pthread",
+                        "-fno-omit-frame-pointer", *sanitize, "-Wall", "-Werror", "-Wno-unused-function",
+                        "-I", str(d), "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "tests"),
+                        "-I", CSRC, os.path.join(ROOT, "tests", "entropy_cpu_harness.cpp"),
+                        os.path.join(CSRC, "host_common.cpp"), os.path.join(CSRC, "host_jpeg.cpp"), "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+
+    def run(streams, **options):
+        """The counts that the harness prints."""
+        args = [f"{k}={v}" for k, v in options.items()]
+        for i, data in enumerate(streams):
+            (d / f"{i}.jpg").write_bytes(data)
+            args.append(str(d / f"{i}.jpg"))
+        r = subprocess.run([exe, *args], capture_output=True, text=True, timeout=600,
+                           env=dict(os.environ, ASAN_OPTIONS="detect_leaks=1"))
+        assert r.returncode == 0, (r.returncode, r.stdout[-2000:], r.stderr[-6000:])
+        words = r.stdout.split()
+        return dict(zip(words[::2], map(int, words[1::2])))
+    return run
+
+
+def photograph(w, h, samp, quality, interval=0, seed=31):
+    frame, coef, qt = encode.encode_rgb(images.texture_rgb(w, h, seed, sigma=12), samp, quality)
+    return bitstream.write_jpeg(frame, coef, qt, restart_interval=interval)
+
+
+def frame_of(w, h, samp):
+    hy, vy = LUMA[samp]
+    return {"width": w, "height": h, "h": (hy, 1, 1), "v": (vy, 1, 1), "qsel": (0, 1, 1)}
+
+
+def gray(n, seed, span=9):
+    rng = np.random.default_rng(seed)
+    frame = {"width": 8 * n, "height": 8, "h": (1, 1, 1), "v": (1, 1, 1), "qsel": (0, 0, 0), "ncomp": 1}
+    coef = np.zeros((n, 64), dtype=np.int16)
+    coef[:, 0] = rng.integers(-60, 61, size=n)
+    coef[:, 1:8] = rng.integers(-span, span + 1, size=(n, 7))
+    return bitstream.write_jpeg(frame, coef, np.ones((4, 64), dtype=np.uint16))
+
+
+def periodic(seed, samp, w, h, period, density):
+    """Blocks that repeat every `period` MCUs: a lane that starts in the wrong
+    place may never find the right one."""
+    hy, vy = LUMA[samp]
+    bpm, n = hy * vy + 2, (w // (8 * hy)) * (h // (8 * vy))
+    rng = np.random.default_rng(seed)
+    pat = np.zeros((period * bpm, 64), dtype=np.int16)
+    m = rng.random(pat.shape) < density
+    pat[m] = rng.integers(-3, 4, int(m.sum()))
+    pat[:, 0] = rng.integers(-5, 6)
+    coef = np.tile(pat, (n // period + 1, 1))[:n * bpm]
+    return bitstream.write_jpeg(frame_of(w, h, samp), coef, np.ones((4, 64), dtype=np.uint16))
+
+
+def scan_range(data):
+    import paper_1311_5304_amd as M
+    scan, _ = M.mjd_parse(data)
+    return int(scan.data_offset), int(scan.data_end)
+
+
+@pytest.mark.parametrize("samp", ["420", "422", "444"])
+@pytest.mark.parametrize("cus", [256, 1])
+def test_photographs_whole_and_in_chunks(run, samp, cus):
+    # one CU: the shape of entropy_follow for more chunks than the chip holds
+    streams = [photograph(333, 250, samp, 85), photograph(160, 120, samp, 60, 1), photograph(256, 160, samp, 90, 7)]
+    c = run(streams, cus=cus, seed=cus, same=3)
+    assert c["splits"] > 3 and c["splits"] < c["intervals"] and c["many"] == (cus == 1)
+
+
+def test_long_and_short_split_intervals_together(run):
+    # a workgroup and a wave each resolve theirs; the list is reordered
+    streams = [photograph(200, 120, "420", 85), photograph(800, 500, "420", 85), photograph(300, 200, "444", 85, 40)]
+    c = run(streams, seed=2)
+    assert c["long"] == 1 and c["splits"] > 3 and c["tiles"] > 10
+
+
+@pytest.mark.parametrize("samp", ["440", "411", "420", "gray"])
+def test_dense_blocks_of_every_sampling(run, samp):
+    """Blocks longer than a chunk, codes past both look-ups."""
+    if samp == "gray":
+        frame = {"width": 200, "height": 160, "h": (1, 1, 1), "v": (1, 1, 1), "qsel": (0, 0, 0), "ncomp": 1}
+        n = 25 * 20
+    else:
+        frame = frame_of(160, 128, samp)
+        n = (160 // (8 * LUMA[samp][0])) * (128 // (8 * LUMA[samp][1])) * (LUMA[samp][0] * LUMA[samp][1] + 2)
+    rng = np.random.default_rng(5)
+    size = np.minimum(rng.geometric(0.3, size=(n, 64)), 10)
+    mag = (1 << (size - 1)) + (rng.random((n, 64)) * (1 << (size - 1))).astype(np.int64)
+    coef = np.where(rng.random((n, 64)) < 0.5, -mag, mag).astype(np.int16)
+    coef[:, 0] = rng.integers(-1023, 1024, size=n)
+    coef[rng.random((n, 64)) < 0.2] = 0
+    widest = np.full((n, 64), 1023, dtype=np.int16)  # 63 times code and magnitude of 11 bits and more, ones
+    widest[::2] = -1023
+    widest[:, 0] = np.where(np.arange(n) % 2, 1023, -1024)
+    qt = np.ones((4, 64), dtype=np.uint16)
+    c = run([bitstream.write_jpeg(frame, k, qt) for k in (coef, widest)], seed=1)
+    assert c["splits"] == 2 and c["global_words"] > 0
+
+
+def test_lengths_around_chunks(run):
+    """Split intervals of every length near one, two and three chunks, and
+    around the sixteen bytes of a load."""
+    streams, near = [photograph(333, 250, "420", 85)], set()
+    for seed in range(40):
+        for n in range(1, 70):
+            data = gray(n, 100 * seed + n)
+            lo, hi = scan_range(data)
+            length = hi - lo - data[lo:hi].count(b"\xFF\x00")
+            key = length if length <= 20 else length if (length + 3) % CHUNK < 7 else None
+            if key is not None and key not in near and length < 400:
+                near.add(key)
+                streams.append(data)
+        if len(near) >= 38:
+            break
+    wanted = {k * CHUNK + d for k in (1, 2, 3) for d in range(-2, 3)}
+    assert len(wanted & near) >= 12
+    c = run(streams, seed=7)
+    assert c["splits"] > 12
+
+
+@pytest.mark.parametrize("seed,samp,period,density", [(0, "420", 3, 0.5), (10, "444", 3, 0.9), (31, "444", 2, 0.9),
+                                                      (44, "422", 3, 0.05)])
+def test_periodic_content(run, seed, samp, period, density):
+    run([periodic(seed, samp, 512, 256, period, density)], seed=seed)
+
+
+@pytest.mark.parametrize("samp", ["420", "444"])
+def test_damaged_streams(run, samp):
+    rnd = random.Random(3)
+    data = photograph(256, 160, samp, 85)
+    lo, hi = scan_range(data)
+    bad = 0
+    for k in range(20):
+        b = bytearray(data)
+        for _ in range(rnd.choice((1, 1, 2, 5))):
+            p = rnd.randrange(lo, hi)
+            if b[p] != 0xFF and b[p - 1] != 0xFF:
+                b[p] = rnd.randrange(255)
+        if k % 5 == 0:  # bytes are missing at the end
+            b = b[:hi - 40 - 100 * k] + b[hi:]
+        if k % 5 == 1:  # nothing of the scan is left but its length
+            b[lo:hi] = bytes(rnd.randrange(255) for _ in range(hi - lo))
+        if k % 5 == 2:  # ones, then zeros: codes that do not exist
+            b[lo:hi] = b"\xFF\x00" * ((hi - lo) // 4) + bytes(hi - lo - 2 * ((hi - lo) // 4))
+        bad += run([bytes(b)], seed=k)["bad"]
+    assert bad >= 12
