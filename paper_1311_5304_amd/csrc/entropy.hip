@@ -60,7 +60,8 @@ struct GInterval {
   uint32_t job;
 };
 
-// A tile of an interval longer than kTile; first: the interval's first tile.
+// A tile of an interval longer than kTile; first: the interval's first tile
+// among the pass's.
 struct GTile {
   uint32_t iv, index, first;
 };
@@ -107,6 +108,16 @@ struct GItem {
   uint32_t bytes;  // of its longest lane
 };
 
+// Whole intervals are decoded in passes that share the memory of their
+// destuffed bytes: a pass takes the intervals [iv0, iv0 + n_iv) of the list,
+// their tiles and items.  Split intervals are destuffed with the pass that they
+// lie in, to memory of their own, and decoded with the last.
+struct GPass {
+  uint32_t iv0, n_iv;
+  uint32_t tile0, n_tiles;
+  uint32_t item0, n_items;  // after the split intervals' items
+};
+
 // Device tables of a batch (one allocation).
 struct GPlan {
   const GJob* jobs;
@@ -120,6 +131,7 @@ struct GPlan {
   uint32_t n_skip;
   uint32_t many;  // entropy_follow's shape
   uint32_t n_iv, n_tiles, n_groups, n_more_groups, n_splits, n_long, n_items, n_split_items;
+  GPass pass;
   uint8_t* data;      // destuffed bytes
   uint32_t* bytes;    // destuffed bytes per interval
   uint32_t* kept;     // per tile: bytes kept, bit 31 where the data ends in it
@@ -259,14 +271,14 @@ __device__ __forceinline__ uint32_t destuff_tile(gin8* jpg, uint32_t start, uint
 
 __global__ __launch_bounds__(kThreads) void entropy_destuff_count(const GPlan pl) {
   const uint32_t w = uniform(blockIdx.x * kWaves + (threadIdx.x >> 6));
-  if (w >= pl.n_tiles) return;
-  const GTile t = pl.tiles[w];
+  if (w >= pl.pass.n_tiles) return;
+  const GTile t = pl.tiles[pl.pass.tile0 + w];
   const GInterval iv = pl.ivs[t.iv];
   const uint32_t a = iv.start + t.index * kTile;
   const uint32_t b = iv.end - a < kTile ? iv.end : a + kTile;
   bool ends;
   const uint32_t n = destuff_tile<false>((gin8*)pl.jobs[iv.job].jpg, iv.start, iv.end, a, b, nullptr, &ends);
-  if (lane_of() == 0) pl.kept[w] = n | (ends ? 0x80000000u : 0u);
+  if (lane_of() == 0) pl.kept[pl.pass.tile0 + w] = n | (ends ? 0x80000000u : 0u);
 }
 
 // One entry per lane of a job's skip tables.
@@ -290,19 +302,20 @@ __device__ __forceinline__ void fill_skip_tables(const GPlan& pl, uint32_t i) {
 // the workgroups after those fill the skip tables that entropy_guess and
 // entropy_follow read.
 __global__ __launch_bounds__(kThreads) void entropy_destuff(const GPlan pl) {
-  const uint32_t groups = (pl.n_iv + pl.n_tiles + kWaves - 1) / kWaves;
+  const GPass ps = pl.pass;
+  const uint32_t groups = (ps.n_iv + ps.n_tiles + kWaves - 1) / kWaves;
   if (blockIdx.x >= groups) return fill_skip_tables(pl, (blockIdx.x - groups) * kThreads + threadIdx.x);
   const uint32_t w = uniform(blockIdx.x * kWaves + (threadIdx.x >> 6));
-  if (w >= pl.n_iv + pl.n_tiles) return;
+  if (w >= ps.n_iv + ps.n_tiles) return;
   const uint32_t lane = lane_of();
-  uint32_t which = w, tile = 0, at = 0;
-  if (w >= pl.n_iv) {
-    const GTile t = pl.tiles[w - pl.n_iv];
+  uint32_t which = ps.iv0 + w, tile = 0, at = 0;
+  if (w >= ps.n_iv) {
+    const GTile t = pl.tiles[ps.tile0 + w - ps.n_iv];
     which = t.iv;
     tile = t.index;
     bool ended = false;
     for (uint32_t i = lane; i < tile; i += 64) {
-      const uint32_t k = pl.kept[t.first + i];
+      const uint32_t k = pl.kept[ps.tile0 + t.first + i];
       at += k & 0x7FFFFFFFu;
       ended = ended || (k >> 31);
     }
@@ -311,7 +324,7 @@ __global__ __launch_bounds__(kThreads) void entropy_destuff(const GPlan pl) {
     if (__ballot(ended)) return;
   }
   const GInterval iv = pl.ivs[which];
-  if (w < pl.n_iv) {
+  if (w < ps.n_iv) {
     if (lane == 0) pl.status[which] = kStatusOk;
     if (iv.end - iv.start > kTile) return;
   }
@@ -1023,8 +1036,8 @@ __global__ __launch_bounds__(kThreads, 3) void entropy_decode(const GPlan pl) {
 #pragma unroll
   for (uint32_t i = 0; i < 8; ++i) *reinterpret_cast<lds128*>(blocks + buf.base + 16 * i) = v4i_t{0, 0, 0, 0};
   uint32_t cur_job = 0xFFFFFFFFu;
-  const uint32_t n_items = SPLIT ? pl.n_split_items : pl.n_items - pl.n_split_items;
-  const GItem* items = pl.items + (SPLIT ? 0 : pl.n_split_items);
+  const uint32_t n_items = SPLIT ? pl.n_split_items : pl.pass.n_items;
+  const GItem* items = pl.items + (SPLIT ? 0 : pl.n_split_items + pl.pass.item0);
   unsigned* counters = pl.counters + (SPLIT ? 0 : 2);
   for (;;) {
     if (tid == 0) s_next = static_cast<int>(atomicAdd(&counters[0], 1u));
@@ -1168,7 +1181,8 @@ __global__ __launch_bounds__(kThreads, 3) void entropy_decode(const GPlan pl) {
 struct mjd_entropy_batch {
   mjd_ctx* ctx = nullptr;
   mjd::gent::GPlan plan{};
-  int grid = 0, split_grid = 0;
+  std::vector<mjd::gent::GPass> passes;
+  int grid = 0, split_grid = 0;          // workgroups of a decoding launch, at most
   uint8_t* d_mem = nullptr;              // every table and buffer of the plan
   std::vector<uint32_t> first_interval;  // per job, into the interval list
   std::vector<uint32_t> iv_index;        // per listed interval, its number in its scan
@@ -1198,38 +1212,160 @@ struct Layout {
 // - a split batch takes 110 us more than 12.5 us a MB (2.5 MB: 165 us, 36 MB:
 //   531, where whole intervals of 1.9 KB take 957; 77 MB: 1067 against 1026;
 //   211 MB: 2740).
-// Splitting is for what fits kSplitMost, which bounds its tables (2.8 bytes
-// per byte).
+// Splitting is for what fits kSplitMost, which bounds its memory: a split byte
+// takes one of data and 2.8 of tables, and a job's skip tables count as the
+// bytes that take as much.
 constexpr uint64_t kSplitMost = uint64_t{256} << 20;
+constexpr uint64_t kSkipBytes = kTableSlots * kSkipEntries * sizeof(uint16_t);
 static uint32_t split_threshold(const std::vector<GInterval>& ivs) {
   uint64_t bytes[33] = {};  // of the intervals of 2^(i-1) < length <= 2^i
   uint64_t count[33] = {};
+  uint64_t jobs[33] = {};  // whose longest interval is one of them
   uint32_t longest[33] = {};
-  for (const GInterval& iv : ivs) {
-    const uint32_t len = iv.end - iv.start;
+  for (size_t k = 0; k < ivs.size(); ++k) {
+    const uint32_t len = ivs[k].end - ivs[k].start;
     int i = 0;
     while (i < 32 && (uint64_t{1} << i) < len) ++i;
     bytes[i] += len;
     ++count[i];
+    if (k == 0 || ivs[k - 1].job != ivs[k].job) ++jobs[i];  // a job's longest comes first
     longest[i] = std::max(longest[i], len);
   }
   double best = 0;
   uint32_t over = 0xFFFFFFFFu;
-  uint64_t split = 0, rest = 0;
+  uint64_t split = 0, skips = 0, rest = 0;
   for (int i = 0; i <= 32; ++i) rest += bytes[i];
   for (int i = 32; i >= 7; --i) {  // all above 2^i are split
     uint32_t most = 0;
     for (int j = 0; j <= i; ++j) most = std::max(most, longest[j]);
     const double t = (split ? 110.0 + 12.5e-6 * static_cast<double>(split) : 0.0) +
                      std::max(0.41 * most, 5.5e-6 * static_cast<double>(rest));
-    if (split <= kSplitMost && (i == 32 || t < best)) {
+    if (split + skips <= kSplitMost && (i == 32 || t < best)) {
       best = t;
       over = i == 32 ? 0xFFFFFFFFu : 1u << i;
     }
     split += bytes[i] + count[i] * 2 * kChunk;
+    skips += jobs[i] * (kSkipBytes / 4);
     rest -= bytes[i];
   }
   return over;
+}
+
+// How a batch is decoded, from its list of intervals: each job's one after the
+// other, longest first.
+struct Schedule {
+  std::vector<GTile> tiles;
+  std::vector<GSplit> splits;
+  std::vector<GGroup> groups, more_groups;
+  std::vector<GItem> items, split_items;
+  std::vector<uint32_t> skip_jobs, split_of;
+  std::vector<GPass> passes;
+  uint64_t chunks = 0;  // of split intervals
+  uint64_t units = 0;   // of 16 bytes of data
+  uint32_t n_long = 0;
+  bool many = false;
+};
+
+// The passes' data takes kPassBytes at most, or one interval's.  A larger
+// corpus fills the chip in each pass: 211 MB are decoded in 1.3 ms.
+constexpr uint64_t kPassBytes = uint64_t{256} << 20;
+// lanes of the largest entropy_destuff: a wave per interval and tile, and the
+// skip tables' (a launch's lanes are counted in 32 bits)
+static_assert((kPassBytes / kPad + kSplitMost / (2 * kChunk) + (kPassBytes + kSplitMost) / kTile) * 64 +
+                  kSplitMost / (kSkipBytes / 4) * (kSkipBytes / 2) < 0xFFFFFFFFu,
+              "a launch holds a pass");
+
+// Intervals above split_over are split, the others take passes of pass_bytes.
+static void schedule(std::vector<GInterval>& ivs, const std::vector<uint32_t>& first_interval,
+                     const std::vector<GJob>& gj, int cus, uint32_t split_over, uint64_t pass_bytes, Schedule* out) {
+  Schedule& sc = *out;
+  const size_t n = gj.size(), n_iv = ivs.size();
+  // Split intervals lie in whole chunks, so that chunk i of the batch is at
+  // byte i * kChunk of the data; the others follow them.
+  for (const GInterval& iv : ivs)
+    if (iv.end - iv.start > split_over) sc.chunks += (static_cast<uint64_t>(iv.end - iv.start) + kPad) / kChunk + 1;
+  const uint64_t base = sc.chunks ? (sc.chunks * kChunk + kTail) / 16 : 0;
+  uint64_t units = base;
+  uint32_t n_chunks = 0;
+  sc.split_of.reserve(sc.chunks);
+  sc.many = sc.chunks > uint64_t{FollowShape<false>::RESIDENT * FollowShape<false>::GROUP} * static_cast<uint64_t>(cus);
+  GPass pass{};
+  const auto close_pass = [&](size_t end) {
+    pass.n_iv = static_cast<uint32_t>(end) - pass.iv0;
+    pass.n_tiles = static_cast<uint32_t>(sc.tiles.size()) - pass.tile0;
+    pass.n_items = static_cast<uint32_t>(sc.items.size()) - pass.item0;
+    // longest items first, so that the last ones to start are short
+    std::stable_sort(sc.items.begin() + pass.item0, sc.items.end(),
+                     [](const GItem& x, const GItem& y) { return x.bytes > y.bytes; });
+    sc.passes.push_back(pass);
+    pass = GPass{static_cast<uint32_t>(end), 0, static_cast<uint32_t>(sc.tiles.size()), 0,
+                 static_cast<uint32_t>(sc.items.size()), 0};
+    sc.units = std::max(sc.units, units);
+    units = base;
+  };
+  for (size_t j = 0; j < n; ++j) {
+    const size_t end = j + 1 < n ? first_interval[j + 1] : n_iv;
+    const uint32_t job = static_cast<uint32_t>(j), first_chunk = n_chunks;
+    GItem item{job, 0, 0, 0};
+    const auto close_item = [&] {
+      if (item.count) sc.items.push_back(item);
+      item.count = 0;
+    };
+    for (size_t k = first_interval[j]; k < end; ++k) {
+      GInterval& iv = ivs[k];
+      const uint32_t len = iv.end - iv.start;
+      if (len > split_over) {
+        const uint32_t c = static_cast<uint32_t>((static_cast<uint64_t>(len) + kPad) / kChunk + 1);
+        iv.dst = n_chunks * (kChunk / 16);
+        sc.split_of.insert(sc.split_of.end(), c, static_cast<uint32_t>(sc.splits.size()));
+        sc.splits.push_back(GSplit{static_cast<uint32_t>(k), n_chunks, c});
+        n_chunks += c;
+      } else {
+        const uint64_t u = (static_cast<uint64_t>(len) + kPad + 15) / 16;
+        if (units > base && (units - base + u) * 16 > pass_bytes) {
+          close_item();
+          close_pass(k);
+        }
+        iv.dst = static_cast<uint32_t>(units);
+        units += u;
+        if (item.count == 0) {
+          item.first = static_cast<uint32_t>(k);
+          item.bytes = len;
+        }
+        if (++item.count == kThreads) close_item();
+      }
+      if (len > kTile) {
+        const uint32_t first = static_cast<uint32_t>(sc.tiles.size()) - pass.tile0;
+        for (uint32_t t = 0; t <= (len - 1) / kTile; ++t) sc.tiles.push_back(GTile{static_cast<uint32_t>(k), t, first});
+      }
+    }
+    close_item();
+    if (n_chunks > first_chunk) {
+      sc.skip_jobs.push_back(job);
+      const uint32_t parts = n_chunks * kParts;
+      uint32_t per = std::min(kGuessThreads / gj[j].bpm, kGuessGroup);
+      for (uint32_t f = first_chunk; f < n_chunks; f += per) sc.groups.push_back(GGroup{job, f, std::min(per, n_chunks - f)});
+      per = sc.many ? FollowShape<true>::GROUP : FollowShape<false>::GROUP;
+      for (uint32_t f = first_chunk; f < n_chunks; f += per) sc.more_groups.push_back(GGroup{job, f, std::min(per, n_chunks - f)});
+      for (uint32_t f = first_chunk * kParts; f < parts; f += kThreads)
+        sc.split_items.push_back(GItem{job, f, std::min<uint32_t>(kThreads, parts - f), kPart});
+    }
+  }
+  close_pass(n_iv);
+  // a workgroup of its own resolves each long split interval, so these come first
+  std::vector<uint32_t> order(sc.splits.size()), place(sc.splits.size());
+  for (size_t k = 0; k < order.size(); ++k) order[k] = static_cast<uint32_t>(k);
+  const auto is_long = [&](uint32_t k) { return sc.splits[k].n_chunks > kLongSplit; };
+  sc.n_long = static_cast<uint32_t>(std::stable_partition(order.begin(), order.end(), is_long) - order.begin());
+  if (sc.n_long && sc.n_long < sc.splits.size()) {
+    std::vector<GSplit> sorted(sc.splits.size());
+    for (size_t k = 0; k < order.size(); ++k) {
+      sorted[k] = sc.splits[order[k]];
+      place[order[k]] = static_cast<uint32_t>(k);
+    }
+    sc.splits.swap(sorted);
+    for (uint32_t& k : sc.split_of) k = place[k];
+  }
 }
 
 static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entropy_batch* b) {
@@ -1239,11 +1375,6 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   std::vector<GTables> gt(n);
   std::vector<FastTables> ft(n);
   std::vector<GInterval> ivs;
-  std::vector<GTile> tiles;
-  std::vector<GSplit> splits;
-  std::vector<GGroup> groups;
-  std::vector<GItem> items;
-  uint64_t chunks = 0;  // of split intervals
   b->first_interval.resize(n);
   for (size_t j = 0; j < n; ++j) {
     const mjd_entropy_job& J = jobs[j];
@@ -1306,122 +1437,83 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
     b->bytes += J.len;
   }
   const size_t n_iv = ivs.size();
+  b->iv_index.resize(n_iv);
+  for (size_t k = 0; k < n_iv; ++k) b->iv_index[k] = ivs[k].dst;
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, entropy_decode<false>, kThreads, 0) != hipSuccess || per_cu < 1)
     per_cu = 1;
   const int cus = ctx->cu_count > 0 ? ctx->cu_count : 256;
-  const uint32_t split_over = split_threshold(ivs);
-  b->iv_index.resize(n_iv);
-  // Split intervals lie in whole chunks, so that chunk i of the batch is at
-  // byte i * kChunk of the data; the others follow them.
-  for (const GInterval& iv : ivs)
-    if (iv.end - iv.start > split_over) chunks += (static_cast<uint64_t>(iv.end - iv.start) + kPad) / kChunk + 1;
-  uint64_t units = chunks ? (chunks * kChunk + kTail) / 16 : 0;  // 16-byte units taken
-  uint32_t n_chunks = 0;
-  std::vector<uint32_t> skip_jobs, split_of;
-  split_of.reserve(chunks);
-  std::vector<GItem> split_items;
-  std::vector<GGroup> more_groups;
-  const bool many = chunks > uint64_t{FollowShape<false>::RESIDENT * FollowShape<false>::GROUP} * static_cast<uint64_t>(cus);
-  for (size_t j = 0; j < n; ++j) {
-    const size_t end = j + 1 < n ? b->first_interval[j + 1] : n_iv;
-    const uint32_t job = static_cast<uint32_t>(j), first_chunk = n_chunks;
-    size_t i = b->first_interval[j];
-    for (size_t k = i; k < end; ++k) {
-      GInterval& iv = ivs[k];
-      const uint32_t len = iv.end - iv.start;
-      b->iv_index[k] = iv.dst;
-      if (len > kTile) {
-        const uint32_t first = static_cast<uint32_t>(tiles.size());
-        for (uint32_t t = 0; t <= (len - 1) / kTile; ++t) tiles.push_back(GTile{static_cast<uint32_t>(k), t, first});
-      }
-      if (len > split_over) {
-        const uint32_t c = static_cast<uint32_t>((static_cast<uint64_t>(len) + kPad) / kChunk + 1);
-        iv.dst = n_chunks * (kChunk / 16);
-        split_of.insert(split_of.end(), c, static_cast<uint32_t>(splits.size()));
-        splits.push_back(GSplit{static_cast<uint32_t>(k), n_chunks, c});
-        n_chunks += c;
-        i = k + 1;  // the longest come first
-      } else {
-        iv.dst = static_cast<uint32_t>(units);
-        units += (static_cast<uint64_t>(len) + kPad + 15) / 16;
-        if (units > 0xFFFFFFFFu) return fail(MJD_ENOMEM, "entropy batch holds too many stream bytes");
-      }
-    }
-    if (n_chunks > first_chunk) {
-      skip_jobs.push_back(job);
-      const uint32_t parts = n_chunks * kParts;
-      uint32_t per = std::min(kGuessThreads / gj[j].bpm, kGuessGroup);
-      for (uint32_t f = first_chunk; f < n_chunks; f += per) groups.push_back(GGroup{job, f, std::min(per, n_chunks - f)});
-      per = many ? FollowShape<true>::GROUP : FollowShape<false>::GROUP;
-      for (uint32_t f = first_chunk; f < n_chunks; f += per) more_groups.push_back(GGroup{job, f, std::min(per, n_chunks - f)});
-      for (uint32_t f = first_chunk * kParts; f < parts; f += kThreads)
-        split_items.push_back(GItem{job, f, std::min<uint32_t>(kThreads, parts - f), kPart});
-    }
-    for (; i < end; i += kThreads)
-      items.push_back(GItem{job, static_cast<uint32_t>(i), static_cast<uint32_t>(std::min<size_t>(kThreads, end - i)),
-                            ivs[i].end - ivs[i].start});
-  }
-  // longest items first, so that the last ones to start are short
-  std::stable_sort(items.begin(), items.end(), [](const GItem& x, const GItem& y) { return x.bytes > y.bytes; });
-  const size_t n_split_items = split_items.size(), n_guess_groups = groups.size();
-  groups.insert(groups.end(), more_groups.begin(), more_groups.end());
-  items.insert(items.begin(), split_items.begin(), split_items.end());
-  // a workgroup of its own resolves each long split interval, so these come first
-  std::vector<uint32_t> order(splits.size()), place(splits.size());
-  for (size_t k = 0; k < order.size(); ++k) order[k] = static_cast<uint32_t>(k);
-  const auto is_long = [&](uint32_t k) { return splits[k].n_chunks > kLongSplit; };
-  const uint32_t n_long = static_cast<uint32_t>(std::stable_partition(order.begin(), order.end(), is_long) - order.begin());
-  if (n_long && n_long < splits.size()) {
-    std::vector<GSplit> sorted(splits.size());
-    for (size_t k = 0; k < order.size(); ++k) {
-      sorted[k] = splits[order[k]];
-      place[order[k]] = static_cast<uint32_t>(k);
-    }
-    splits.swap(sorted);
-    for (uint32_t& k : split_of) k = place[k];
-  }
-  b->grid = std::min<int>(static_cast<int>(items.size() - n_split_items), per_cu * cus);
-  b->split_grid = std::min<int>(static_cast<int>(n_split_items), per_cu * cus);
-  // one allocation: what the host fills first, then what the kernels write
+  // One allocation: what the host fills first, then what the kernels write.
+  // On a device with too little memory left for it the batch goes on without
+  // splitting, then with smaller passes, down to one interval's data.
+  uint32_t longest = 0;
+  for (const GInterval& iv : ivs) longest = std::max(longest, iv.end - iv.start);
+  uint32_t split_over = split_threshold(ivs);
+  uint64_t pass_bytes = kPassBytes;
+  Schedule sc;
   Layout mem;
-  const uint64_t o_jobs = mem.add(n * sizeof(GJob)), o_tables = mem.add(n * sizeof(FastTables)), o_codes = mem.add(n * sizeof(GTables)),
-                 o_ivs = mem.add(n_iv * sizeof(GInterval)), o_tiles = mem.add(tiles.size() * sizeof(GTile)),
-                 o_splits = mem.add(splits.size() * sizeof(GSplit)), o_groups = mem.add(groups.size() * sizeof(GGroup)),
-                 o_split_of = mem.add(split_of.size() * sizeof(uint32_t)),
-                 o_items = mem.add(items.size() * sizeof(GItem)),
-                 o_skip_jobs = mem.add(skip_jobs.size() * sizeof(uint32_t)), o_counters = mem.add(4 * sizeof(unsigned)),
-                 o_status = mem.add(n_iv * sizeof(uint32_t));
-  const uint64_t upload = mem.size;
-  const uint64_t o_bytes = mem.add(n_iv * sizeof(uint32_t)), o_kept = mem.add(tiles.size() * sizeof(uint32_t)),
-                 o_states = mem.add(chunks * kSlots * sizeof(uint32_t)),
-                 o_links = mem.add(chunks * kSlots), o_hops = mem.add(chunks * kSlots * kParts * sizeof(GHop)),
-                 o_tasks = mem.add(chunks * kParts * sizeof(GTask)),
-                 o_skip = mem.add(skip_jobs.size() * kTableSlots * kSkipEntries * sizeof(uint16_t)),
-                 o_data = mem.add(units * 16);
-  if (hipMalloc(&b->d_mem, mem.size) != hipSuccess)
-    return fail(MJD_ENOMEM, "device allocation for the entropy batch failed");
+  uint64_t o_jobs, o_tables, o_codes, o_ivs, o_tiles, o_splits, o_groups, o_split_of, o_items, o_skip_jobs, o_counters,
+      o_status, upload, o_bytes, o_kept, o_states, o_links, o_hops, o_tasks, o_skip, o_data;
+  for (;;) {
+    sc = Schedule{};
+    schedule(ivs, b->first_interval, gj, cus, split_over, pass_bytes, &sc);
+    mem = Layout{};
+    o_jobs = mem.add(n * sizeof(GJob));
+    o_tables = mem.add(n * sizeof(FastTables));
+    o_codes = mem.add(n * sizeof(GTables));
+    o_ivs = mem.add(n_iv * sizeof(GInterval));
+    o_tiles = mem.add(sc.tiles.size() * sizeof(GTile));
+    o_splits = mem.add(sc.splits.size() * sizeof(GSplit));
+    o_groups = mem.add((sc.groups.size() + sc.more_groups.size()) * sizeof(GGroup));
+    o_split_of = mem.add(sc.split_of.size() * sizeof(uint32_t));
+    o_items = mem.add((sc.split_items.size() + sc.items.size()) * sizeof(GItem));
+    o_skip_jobs = mem.add(sc.skip_jobs.size() * sizeof(uint32_t));
+    o_counters = mem.add(4 * sizeof(unsigned));
+    o_status = mem.add(n_iv * sizeof(uint32_t));
+    upload = mem.size;
+    o_bytes = mem.add(n_iv * sizeof(uint32_t));
+    o_kept = mem.add(sc.tiles.size() * sizeof(uint32_t));
+    o_states = mem.add(sc.chunks * kSlots * sizeof(uint32_t));
+    o_links = mem.add(sc.chunks * kSlots);
+    o_hops = mem.add(sc.chunks * kSlots * kParts * sizeof(GHop));
+    o_tasks = mem.add(sc.chunks * kParts * sizeof(GTask));
+    o_skip = mem.add(sc.skip_jobs.size() * kSkipBytes);
+    o_data = mem.add(sc.units * 16);
+    if (hipMalloc(&b->d_mem, mem.size) == hipSuccess) break;
+    b->d_mem = nullptr;
+    (void)hipGetLastError();  // the launches ask for it
+    if (split_over != 0xFFFFFFFFu) split_over = 0xFFFFFFFFu;
+    else if (pass_bytes > longest) pass_bytes /= 4;
+    else return fail(MJD_ENOMEM, "device allocation for the entropy batch failed");
+  }
+  b->passes = sc.passes;
+  uint32_t most_items = 0;
+  for (const GPass& ps : sc.passes) most_items = std::max(most_items, ps.n_items);
+  b->grid = std::min<int>(static_cast<int>(most_items), per_cu * cus);
+  b->split_grid = std::min<int>(static_cast<int>(sc.split_items.size()), per_cu * cus);
   uint8_t* d = b->d_mem;
   for (size_t j = 0; j < n; ++j) {
     gj[j].tables = reinterpret_cast<const FastTables*>(d + o_tables) + j;
     gj[j].codes = (reinterpret_cast<const GTables*>(d + o_codes) + j)->t;
   }
-  for (size_t i = 0; i < skip_jobs.size(); ++i)
-    gj[skip_jobs[i]].skip = reinterpret_cast<uint16_t*>(d + o_skip) + i * kTableSlots * kSkipEntries;
+  for (size_t i = 0; i < sc.skip_jobs.size(); ++i)
+    gj[sc.skip_jobs[i]].skip = reinterpret_cast<uint16_t*>(d + o_skip + i * kSkipBytes);
   std::vector<uint8_t> host(upload);
-  auto fill = [&](uint64_t at, const void* from, size_t bytes) {
-    if (bytes) memcpy(host.data() + at, from, bytes);
+  auto fill = [&](uint64_t at, const auto& from) {
+    const size_t bytes = from.size() * sizeof(from[0]);
+    if (bytes) memcpy(host.data() + at, from.data(), bytes);
+    return at + bytes;
   };
-  fill(o_jobs, gj.data(), n * sizeof(GJob));
-  fill(o_tables, ft.data(), n * sizeof(FastTables));
-  fill(o_codes, gt.data(), n * sizeof(GTables));
-  fill(o_ivs, ivs.data(), n_iv * sizeof(GInterval));
-  fill(o_tiles, tiles.data(), tiles.size() * sizeof(GTile));
-  fill(o_splits, splits.data(), splits.size() * sizeof(GSplit));
-  fill(o_groups, groups.data(), groups.size() * sizeof(GGroup));
-  fill(o_split_of, split_of.data(), split_of.size() * sizeof(uint32_t));
-  fill(o_items, items.data(), items.size() * sizeof(GItem));
-  fill(o_skip_jobs, skip_jobs.data(), skip_jobs.size() * sizeof(uint32_t));
+  fill(o_jobs, gj);
+  fill(o_tables, ft);
+  fill(o_codes, gt);
+  fill(o_ivs, ivs);
+  fill(o_tiles, sc.tiles);
+  fill(o_splits, sc.splits);
+  fill(fill(o_groups, sc.groups), sc.more_groups);
+  fill(o_split_of, sc.split_of);
+  fill(fill(o_items, sc.split_items), sc.items);
+  fill(o_skip_jobs, sc.skip_jobs);
   memset(host.data() + o_status, 0xFF, n_iv * sizeof(uint32_t));  // kStatusOk; the counters are zero
   if (hipMemcpy(d, host.data(), upload, hipMemcpyHostToDevice) != hipSuccess)
     return fail(MJD_EDEVICE, "uploading the entropy batch tables failed");
@@ -1434,16 +1526,16 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   p.split_of = reinterpret_cast<const uint32_t*>(d + o_split_of);
   p.items = reinterpret_cast<const GItem*>(d + o_items);
   p.skip_jobs = reinterpret_cast<const uint32_t*>(d + o_skip_jobs);
-  p.n_skip = static_cast<uint32_t>(skip_jobs.size());
-  p.many = many ? 1u : 0u;
+  p.n_skip = static_cast<uint32_t>(sc.skip_jobs.size());
+  p.many = sc.many ? 1u : 0u;
   p.n_iv = static_cast<uint32_t>(n_iv);
-  p.n_tiles = static_cast<uint32_t>(tiles.size());
-  p.n_groups = static_cast<uint32_t>(n_guess_groups);
-  p.n_more_groups = static_cast<uint32_t>(more_groups.size());
-  p.n_splits = static_cast<uint32_t>(splits.size());
-  p.n_long = n_long;
-  p.n_items = static_cast<uint32_t>(items.size());
-  p.n_split_items = static_cast<uint32_t>(n_split_items);
+  p.n_tiles = static_cast<uint32_t>(sc.tiles.size());
+  p.n_groups = static_cast<uint32_t>(sc.groups.size());
+  p.n_more_groups = static_cast<uint32_t>(sc.more_groups.size());
+  p.n_splits = static_cast<uint32_t>(sc.splits.size());
+  p.n_long = sc.n_long;
+  p.n_items = static_cast<uint32_t>(sc.split_items.size() + sc.items.size());
+  p.n_split_items = static_cast<uint32_t>(sc.split_items.size());
   p.data = d + o_data;
   p.bytes = reinterpret_cast<uint32_t*>(d + o_bytes);
   p.kept = reinterpret_cast<uint32_t*>(d + o_kept);
@@ -1456,22 +1548,30 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   return MJD_OK;
 }
 
-static hipError_t enqueue(const mjd_entropy_batch* b, hipStream_t s) {
-  const GPlan& p = b->plan;
+static void enqueue_splits(const GPlan& p, int grid, hipStream_t s) {
   const dim3 block(kThreads);
-  if (p.n_tiles) hipLaunchKernelGGL(entropy_destuff_count, dim3((p.n_tiles + kWaves - 1) / kWaves), block, 0, s, p);
-  const uint32_t skip_groups = p.n_skip * (kTableSlots * kSkipEntries / kThreads);
-  hipLaunchKernelGGL(entropy_destuff, dim3((p.n_iv + p.n_tiles + kWaves - 1) / kWaves + skip_groups), block, 0, s, p);
-  if (p.n_splits) {
-    hipLaunchKernelGGL(entropy_guess, dim3(p.n_groups), dim3(kGuessThreads), 0, s, p);
-    if (p.many) hipLaunchKernelGGL(entropy_follow<true>, dim3(p.n_more_groups), dim3(FollowShape<true>::THREADS), 0, s, p);
-    else hipLaunchKernelGGL(entropy_follow<false>, dim3(p.n_more_groups), dim3(FollowShape<false>::THREADS), 0, s, p);
-    if (p.n_long) hipLaunchKernelGGL(entropy_resolve<1024>, dim3(p.n_long), dim3(1024), 0, s, p);
-    const uint32_t rest = p.n_splits - p.n_long;
-    if (rest) hipLaunchKernelGGL(entropy_resolve<64>, dim3((rest + kWaves - 1) / kWaves), block, 0, s, p);
-    hipLaunchKernelGGL(entropy_decode<true>, dim3(b->split_grid), block, 0, s, p);
+  hipLaunchKernelGGL(entropy_guess, dim3(p.n_groups), dim3(kGuessThreads), 0, s, p);
+  if (p.many) hipLaunchKernelGGL(entropy_follow<true>, dim3(p.n_more_groups), dim3(FollowShape<true>::THREADS), 0, s, p);
+  else hipLaunchKernelGGL(entropy_follow<false>, dim3(p.n_more_groups), dim3(FollowShape<false>::THREADS), 0, s, p);
+  if (p.n_long) hipLaunchKernelGGL(entropy_resolve<1024>, dim3(p.n_long), dim3(1024), 0, s, p);
+  const uint32_t rest = p.n_splits - p.n_long;
+  if (rest) hipLaunchKernelGGL(entropy_resolve<64>, dim3((rest + kWaves - 1) / kWaves), block, 0, s, p);
+  hipLaunchKernelGGL(entropy_decode<true>, dim3(grid), block, 0, s, p);
+}
+
+static hipError_t enqueue(const mjd_entropy_batch* b, hipStream_t s) {
+  GPlan p = b->plan;
+  const dim3 block(kThreads);
+  for (size_t i = 0; i < b->passes.size(); ++i) {
+    const GPass& ps = p.pass = b->passes[i];
+    const bool last = i + 1 == b->passes.size();
+    if (ps.n_tiles) hipLaunchKernelGGL(entropy_destuff_count, dim3((ps.n_tiles + kWaves - 1) / kWaves), block, 0, s, p);
+    const uint32_t skip_groups = last ? p.n_skip * (kTableSlots * kSkipEntries / kThreads) : 0;
+    hipLaunchKernelGGL(entropy_destuff, dim3((ps.n_iv + ps.n_tiles + kWaves - 1) / kWaves + skip_groups), block, 0, s, p);
+    if (last && p.n_splits) enqueue_splits(p, b->split_grid, s);
+    const uint32_t grid = std::min(static_cast<uint32_t>(b->grid), ps.n_items);
+    if (grid) hipLaunchKernelGGL(entropy_decode<false>, dim3(grid), block, 0, s, p);
   }
-  if (b->grid) hipLaunchKernelGGL(entropy_decode<false>, dim3(b->grid), block, 0, s, p);
   return hipGetLastError();
 }
 
@@ -1491,7 +1591,12 @@ int mjd_entropy_batch_create(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n
   mjd_entropy_batch* b = new (std::nothrow) mjd_entropy_batch;
   if (!b) return mjd::fail(MJD_ENOMEM, "entropy batch allocation failed");
   b->ctx = ctx;
-  int rc = mjd::gent::build(ctx, jobs, n, b);
+  int rc;
+  try {
+    rc = mjd::gent::build(ctx, jobs, n, b);
+  } catch (const std::bad_alloc&) {
+    rc = mjd::fail(MJD_ENOMEM, "host allocation for the entropy batch failed");
+  }
   if (cur != ctx->device) (void)hipSetDevice(cur);
   if (rc != MJD_OK) {
     if (b->d_mem) (void)hipFree(b->d_mem);

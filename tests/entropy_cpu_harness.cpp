@@ -70,7 +70,6 @@ int main(int argc, char** argv) {
     else if (!strncmp(argv[i], "cus=", 4)) ctx.cu_count = atoi(argv[i] + 4);
     else if (!strncmp(argv[i], "same=", 5)) same = static_cast<unsigned>(atoi(argv[i] + 5));
     else if (!strncmp(argv[i], "largest=", 8)) cpu::options.largest = strtoull(argv[i] + 8, nullptr, 10);
-    else if (!strncmp(argv[i], "threads=", 8)) cpu::options.most_threads = strtoull(argv[i] + 8, nullptr, 10);
     else images.push_back(Image{read_file(argv[i]), {}, {}, 0, {}, false, nullptr, nullptr});
   }
   std::vector<mjd_entropy_job> jobs;
@@ -110,6 +109,7 @@ int main(int argc, char** argv) {
     printf("create: %s\n", mjd_last_error());
     return 1;
   }
+  const unsigned long long memory = cpu::options.allocated;
   const GPlan& plan = b->plan;
   uint64_t chunks = 0, bytes = 0;
   for (uint32_t i = 0; i < plan.n_splits; ++i) chunks += plan.splits[i].n_chunks;
@@ -181,8 +181,8 @@ int main(int argc, char** argv) {
       memset(jobs[j].d_coef, 0x33, of[j]->n_blocks * 128);
     }
   }
-  printf("intervals %u tiles %u splits %u long %u chunks %llu many %u breaks %lu out_of_hops %lu global_words %lu bad %d\n",
-         p.n_iv, p.n_tiles, p.n_splits, p.n_long, static_cast<unsigned long long>(chunks), p.many, breaks, out_of_hops,
+  printf("memory %llu passes %zu intervals %u tiles %u splits %u long %u chunks %llu many %u breaks %lu out_of_hops %lu global_words %lu bad %d\n",
+         memory, b->passes.size(), p.n_iv, p.n_tiles, p.n_splits, p.n_long, static_cast<unsigned long long>(chunks), p.many, breaks, out_of_hops,
          global_words, any_bad ? 1 : 0);
   mjd_entropy_batch_destroy(b);
   for (void* o : owned) free(o);

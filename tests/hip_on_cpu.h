@@ -36,7 +36,7 @@ namespace cpu {
 struct Options {
   unsigned seed = 0;              // order of a launch's workgroups, contents of new device memory
   size_t largest = SIZE_MAX;      // an allocation above this fails
-  uint64_t most_threads = 0xFFFFFFFFu;  // of one launch, as the hardware's 32-bit grid
+  size_t allocated = 0;           // by the last one that did not
 };
 inline Options options;
 
@@ -171,8 +171,7 @@ inline void run_workgroup(unsigned threads) {
 }
 
 inline bool launch(dim3 grid, dim3 block, const std::function<void()>& f) {
-  if (grid.x == 0 || block.x == 0 || block.x > 1024 || static_cast<uint64_t>(grid.x) * block.x > options.most_threads)
-    return false;
+  if (grid.x == 0 || block.x == 0 || block.x > 1024 || uint64_t{grid.x} * block.x > 0xFFFFFFFFu) return false;
   body = &f;
   grid_dim = grid;
   block_dim = block;
@@ -272,7 +271,8 @@ inline hipError_t cpu_last_error = hipSuccess;
 
 template <class T>
 inline hipError_t hipMalloc(T** p, size_t bytes) {
-  if (bytes > cpu::options.largest) return hipErrorOutOfMemory;
+  if (bytes > cpu::options.largest) return cpu_last_error = hipErrorOutOfMemory;
+  cpu::options.allocated = bytes;
   uint8_t* d = static_cast<uint8_t*>(aligned_alloc(256, bytes));
   if (!d) return hipErrorOutOfMemory;
   std::mt19937 rng(cpu::options.seed + 1);

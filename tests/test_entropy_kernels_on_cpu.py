@@ -163,6 +163,18 @@ def test_periodic_content(run, seed, samp, period, density):
     run([periodic(seed, samp, 512, 256, period, density)], seed=seed)
 
 
+def test_with_less_memory_than_it_would_take(run):
+    """A batch for which the device has no room is decoded without splitting,
+    and then in passes that share the memory of their bytes."""
+    streams = [photograph(333, 250, "420", 85), photograph(160, 120, "420", 60, 1), photograph(256, 160, "444", 90, 7)]
+    c = run(streams, same=3)
+    assert c["splits"] > 3 and c["passes"] == 1
+    whole = run(streams, same=3, largest=c["memory"] - 1)
+    assert whole["splits"] == 0 and whole["passes"] == 1 and whole["memory"] < c["memory"]
+    few = run(streams, same=3, largest=whole["memory"] - 1)
+    assert few["splits"] == 0 and few["passes"] > 1 and few["intervals"] == c["intervals"]
+
+
 @pytest.mark.parametrize("samp", ["420", "444"])
 def test_damaged_streams(run, samp):
     rnd = random.Random(3)
