@@ -466,7 +466,7 @@ typedef struct mjd_entropy_batch mjd_entropy_batch;
  * An invalid job fails the whole call, naming the job.  The device buffers
  * are only recorded, not accessed.
  * Device memory of a batch: 21 KB a job, 40 bytes a restart interval, a copy
- * of the entropy-coded bytes (256 MiB at most, or the longest interval; a
+ * of the entropy-coded bytes (1 GiB at most, or the longest interval; a
  * larger batch is decoded in passes that share it), and where intervals are
  * cut into chunks 3.8 bytes for each of their bytes and 16 KB a job, 1 GiB at
  * most.  Where the device has less left, the intervals stay whole and the
@@ -475,7 +475,7 @@ typedef struct mjd_entropy_batch mjd_entropy_batch;
 int mjd_entropy_batch_create(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entropy_batch** out);
 
 /* Enqueue the decoding of every job on `stream`: two or three kernels for
- * every 256 MiB, and up to five more where intervals are cut into chunks.
+ * every GiB, and up to five more where intervals are cut into chunks.
  * Launches of one
  * batch must be serialised (one stream).  Reads only the first len bytes of
  * each job's stream, rounded up to 16, and writes only its coefficient

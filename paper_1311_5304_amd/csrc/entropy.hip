@@ -1266,9 +1266,11 @@ struct Schedule {
   bool many = false;
 };
 
-// The passes' data takes kPassBytes at most, or one interval's.  A larger
-// corpus fills the chip in each pass: 211 MB are decoded in 1.3 ms.
-constexpr uint64_t kPassBytes = uint64_t{256} << 20;
+// The passes' data takes kPassBytes at most, or one interval's.  A pass ends
+// with a round of workgroups that does not fill the chip, which a corpus of
+// small files notices: 4096 of 80 KB with a marker per MCU row take 13.3 ms in
+// one pass, 15.7 in two of 256 MiB.
+constexpr uint64_t kPassBytes = uint64_t{1} << 30;
 // lanes of the largest entropy_destuff: a wave per interval and tile, and the
 // skip tables' (a launch's lanes are counted in 32 bits)
 static_assert((kPassBytes / kPad + kSplitMost / (2 * kChunk) + (kPassBytes + kSplitMost) / kTile) * 64 +

@@ -27,7 +27,7 @@ def ctx(M):
 
 
 def test_more_bytes_than_a_pass_holds(M, ctx):
-    """400 MB of intervals of an MCU row, decoded in two passes, with a long
+    """1.3 GB of intervals of an MCU row, decoded in two passes, with a long
     interval at the end of the list, which many lanes decode."""
     frame, coef, qt = encode.encode_rgb(images.texture_rgb(2000, 1504, 7, sigma=12), "420", 85)
     exp = torch.from_numpy(coef.reshape(-1)).cuda()
@@ -38,11 +38,11 @@ def test_more_bytes_than_a_pass_holds(M, ctx):
         off = M.mjd_restart_index(data, scan)
         d_jpg = torch.zeros(-(-len(data) // 16) * 16, dtype=torch.uint8, device="cuda")
         d_jpg[:len(data)] = torch.from_numpy(np.frombuffer(data, dtype=np.uint8).copy()).cuda()
-        copies = 400_000_000 // len(data) if interval else 1
-        # every tenth has coefficients of its own, the others share theirs
-        own = [torch.zeros_like(exp) for _ in range(copies // 10 + 1)]
-        jobs += [(scan, off, d_jpg, len(data), own[i // 10] if i % 10 == 0 else own[-1]) for i in range(copies)]
-    assert sum(j[3] for j in jobs) > 390_000_000
+        copies = 1_300_000_000 // len(data) if interval else 1
+        # every 40th has coefficients of its own, the others share theirs
+        own = [torch.zeros_like(exp) for _ in range(copies // 40 + 1)]
+        jobs += [(scan, off, d_jpg, len(data), own[i // 40] if i % 40 == 0 else own[-1]) for i in range(copies)]
+    assert sum(j[3] for j in jobs) > 1_290_000_000
     print(f"{len(jobs)} jobs of {jobs[0][3]} bytes", flush=True)
     b = M.EntropyBatch(ctx, jobs)
     outs = {j[4].data_ptr(): j[4] for j in jobs}.values()
