@@ -465,7 +465,7 @@ typedef struct mjd_entropy_batch mjd_entropy_batch;
  * be increasing and inside [0, len)) and upload the tables (synchronous).
  * An invalid job fails the whole call, naming the job.  The device buffers
  * are only recorded, not accessed.
- * Device memory of a batch: 21 KB a job, 40 bytes a restart interval, a copy
+ * Device memory of a batch: 13 KB a job, 40 bytes a restart interval, a copy
  * of the entropy-coded bytes (1 GiB at most, or the longest interval; a
  * larger batch is decoded in passes that share it), and where intervals are
  * cut into chunks 3.8 bytes for each of their bytes and 16 KB a job, 1 GiB at

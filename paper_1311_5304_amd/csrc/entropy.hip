@@ -15,6 +15,7 @@
 // Both decoding kernels write whole blocks in MCU order, the layout that
 // mjd_decode reads.  Each interval's status goes to a device array.
 #include <stdio.h>
+#include <stdlib.h>
 #include <string.h>
 
 #include <algorithm>
@@ -42,7 +43,7 @@ struct GJob {
   const uint8_t* jpg;
   int16_t* coef;
   const FastTables* tables;
-  const GHuff* codes;  // the same tables' canonical codes
+  const GCodes* codes;  // the same tables' canonical codes
   uint16_t* skip;      // kTableSlots skip tables, where the job has split intervals
   uint32_t bpm;        // blocks per MCU
   uint32_t comp_bits;  // component of block b of an MCU in bits 2b..2b+1
@@ -143,8 +144,22 @@ struct GPlan {
   unsigned* counters;
 };
 
-static int tables_for(const mjd_scan& scan, GTables* g, uint32_t* tsel) {
-  switch (plan_gtables(scan, g, tsel)) {
+// A scan's tables into `codes` and `fast`, kTableSlots each.
+static int tables_for(const mjd_scan& scan, GCodes* codes, FastTable* fast, uint32_t* tsel) {
+  uint32_t used = 0;
+  const int rc = plan_slots(scan, tsel, [&](int slot, const mjd_huffman& h, bool ac) {
+    const int e = build_codes(h, &codes[slot]);
+    if (e != kTableOk) return e;
+    used |= 1u << slot;
+    build_fast_table(codes[slot], ac, &fast[slot]);
+    return e;
+  });
+  for (int i = 0; i < kTableSlots; ++i)
+    if (!(used >> i & 1u)) {  // no code begins with anything
+      memset(&codes[i], 0, sizeof(GCodes));
+      build_fast_table(codes[i], false, &fast[i]);
+    }
+  switch (rc) {
     case kTableOk:
       return MJD_OK;
     case kTableUndefined:
@@ -293,7 +308,7 @@ __device__ __forceinline__ void fill_skip_tables(const GPlan& pl, uint32_t i) {
   jb.skip[at] = static_cast<uint16_t>(skip_entry(at % kSkipEntries, ac, [&](uint32_t top) {
     const uint32_t e = ft.fast[top >> (32 - kGLook)];
     return e & 31u ? e : more_entry(e, top, ac, [&](uint32_t k) { return static_cast<uint32_t>(ft.more[k]); },
-                                    PlainTab{jb.codes}, static_cast<int>(t));
+                                    CodeTab{jb.codes}, static_cast<int>(t));
   }));
 }
 
@@ -356,10 +371,10 @@ __device__ __forceinline__ void load_tables(const FastTables* from, lds_tables* 
 __device__ __forceinline__ uint32_t fast_entry(const lds_tables* tabs, uint32_t t, uint32_t top) {
   return *reinterpret_cast<const lds16*>((const lds8*)tabs + t + (top >> 21 & 0x7FEu));
 }
-__device__ __forceinline__ uint32_t long_code(const lds_tables* tabs, const GHuff* codes, uint32_t t, uint32_t top,
+__device__ __forceinline__ uint32_t long_code(const lds_tables* tabs, const GCodes* codes, uint32_t t, uint32_t top,
                                               uint32_t e, bool ac) {
   const lds16* more = reinterpret_cast<const lds16*>((const lds8*)tabs + t + sizeof(FastTable::fast));
-  return more_entry(e, top, ac, [more](uint32_t i) { return static_cast<uint32_t>(more[i]); }, PlainTab{codes},
+  return more_entry(e, top, ac, [more](uint32_t i) { return static_cast<uint32_t>(more[i]); }, CodeTab{codes},
                     static_cast<int>(t / sizeof(FastTable)));
 }
 // Byte offset of the table that two bits of `slots` name for block b.
@@ -508,7 +523,7 @@ struct Walker {
   const lds16* skip;
   const lds_tables* fast;    // WHOLE
   const FastTables* memory;  // else
-  const GHuff* codes;
+  const GCodes* codes;
   uint32_t bpm2, slots_dc, slots_ac, comp_bits;
   uint32_t w0, w1;  // the window, as in BitWindow
   int32_t sh;
@@ -545,7 +560,7 @@ struct Walker {
       const FastTable& ft = memory->t[s];
       const uint32_t e = ft.fast[top >> (32 - kGLook)];
       return e & 31u ? e : more_entry(e, top, k != 0, [&](uint32_t i) { return static_cast<uint32_t>(ft.more[i]); },
-                                      PlainTab{codes}, static_cast<int>(s));
+                                      CodeTab{codes}, static_cast<int>(s));
     }
   }
   // Position of the next unread bit in the copy, modulo 2^32.
@@ -1054,7 +1069,7 @@ __global__ __launch_bounds__(kThreads, 3) void entropy_decode(const GPlan pl) {
       cur_job = job;
     }
     const uint32_t bpm = jb.bpm, comp_bits = jb.comp_bits, slots_dc = jb.dc_slots, slots_ac = jb.ac_slots;
-    const GHuff* codes = jb.codes;
+    const GCodes* codes = jb.codes;
     gout128* coef = (gout128*)jb.coef;
     // the lane's task
     uint32_t which = 0, b = 0, block = 0, left = 0, block0 = 0, bytes = 0;
@@ -1200,6 +1215,24 @@ struct Layout {
     size = (size + bytes + 255) & ~uint64_t{255};
     return at;
   }
+};
+
+// Bytes on the host that are not cleared, and that grow without a copy where
+// they are many.
+class HostBytes {
+ public:
+  HostBytes() = default;
+  HostBytes(const HostBytes&) = delete;
+  ~HostBytes() { free(bytes_); }
+  void resize(size_t n) {
+    uint8_t* p = static_cast<uint8_t*>(realloc(bytes_, n));
+    if (!p) throw std::bad_alloc();
+    bytes_ = p;
+  }
+  uint8_t* at(uint64_t offset) { return bytes_ + offset; }
+
+ private:
+  uint8_t* bytes_ = nullptr;
 };
 
 // The length above which intervals are split: the power of two (or none)
@@ -1374,8 +1407,12 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   if (n == 0) return fail(MJD_EINVAL, "empty entropy batch");
   if (n > (1u << 24)) return fail(MJD_EINVAL, "entropy batch of %zu jobs too large", n);
   std::vector<GJob> gj(n);
-  std::vector<GTables> gt(n);
-  std::vector<FastTables> ft(n);
+  // what is uploaded, the tables first: they are built where they go from
+  Layout mem;
+  const uint64_t o_tables = mem.add(n * sizeof(FastTables)), o_codes = mem.add(n * sizeof(GCodes[kTableSlots]));
+  const Layout after_tables = mem;
+  HostBytes host;
+  host.resize(mem.size);
   std::vector<GInterval> ivs;
   b->first_interval.resize(n);
   for (size_t j = 0; j < n; ++j) {
@@ -1394,16 +1431,14 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
     }
     if (L.bpm > static_cast<int>(kGuesses)) return fail(MJD_EINVAL, "job %zu: %d blocks per MCU", j, L.bpm);
     uint32_t tsel;
-    rc = tables_for(*J.scan, &gt[j], &tsel);
+    FastTables* ft = reinterpret_cast<FastTables*>(host.at(o_tables)) + j;
+    rc = tables_for(*J.scan, reinterpret_cast<GCodes*>(host.at(o_codes)) + kTableSlots * j, ft->t, &tsel);
     if (rc != MJD_OK) {
       const std::string why = mjd_last_error();
       return fail(rc, "job %zu: %s", j, why.c_str());
     }
     gj[j] = GJob{J.d_jpg, J.d_coef, nullptr, nullptr, nullptr, static_cast<uint32_t>(L.bpm), 0, 0, 0};
-    uint32_t ac_used = 0;
-    for (int c = 0; c < 3; ++c) ac_used |= 1u << (tsel >> (4 * c + 2) & 3u);
-    for (int t = 0; t < kTableSlots; ++t) build_fast_table(gt[j].t[t], ac_used >> t & 1u, &ft[j].t[t]);
-    build_places(host::zigzag_to_natural(), ft[j].nat2);
+    build_places(host::zigzag_to_natural(), ft->nat2);
     for (int i = 0; i < L.bpm; ++i) {
       const uint32_t c = static_cast<uint32_t>(L.comp_of[i]);
       gj[j].comp_bits |= c << (2 * i);
@@ -1453,16 +1488,13 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   uint32_t split_over = split_threshold(ivs);
   uint64_t pass_bytes = kPassBytes;
   Schedule sc;
-  Layout mem;
-  uint64_t o_jobs, o_tables, o_codes, o_ivs, o_tiles, o_splits, o_groups, o_split_of, o_items, o_skip_jobs, o_counters,
+  uint64_t o_jobs, o_ivs, o_tiles, o_splits, o_groups, o_split_of, o_items, o_skip_jobs, o_counters,
       o_status, upload, o_bytes, o_kept, o_states, o_links, o_hops, o_tasks, o_skip, o_data;
   for (;;) {
     sc = Schedule{};
     schedule(ivs, b->first_interval, gj, cus, split_over, pass_bytes, &sc);
-    mem = Layout{};
+    mem = after_tables;
     o_jobs = mem.add(n * sizeof(GJob));
-    o_tables = mem.add(n * sizeof(FastTables));
-    o_codes = mem.add(n * sizeof(GTables));
     o_ivs = mem.add(n_iv * sizeof(GInterval));
     o_tiles = mem.add(sc.tiles.size() * sizeof(GTile));
     o_splits = mem.add(sc.splits.size() * sizeof(GSplit));
@@ -1496,19 +1528,17 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   uint8_t* d = b->d_mem;
   for (size_t j = 0; j < n; ++j) {
     gj[j].tables = reinterpret_cast<const FastTables*>(d + o_tables) + j;
-    gj[j].codes = (reinterpret_cast<const GTables*>(d + o_codes) + j)->t;
+    gj[j].codes = reinterpret_cast<const GCodes*>(d + o_codes) + kTableSlots * j;
   }
   for (size_t i = 0; i < sc.skip_jobs.size(); ++i)
     gj[sc.skip_jobs[i]].skip = reinterpret_cast<uint16_t*>(d + o_skip + i * kSkipBytes);
-  std::vector<uint8_t> host(upload);
+  host.resize(upload);
   auto fill = [&](uint64_t at, const auto& from) {
     const size_t bytes = from.size() * sizeof(from[0]);
-    if (bytes) memcpy(host.data() + at, from.data(), bytes);
+    if (bytes) memcpy(host.at(at), from.data(), bytes);
     return at + bytes;
   };
   fill(o_jobs, gj);
-  fill(o_tables, ft);
-  fill(o_codes, gt);
   fill(o_ivs, ivs);
   fill(o_tiles, sc.tiles);
   fill(o_splits, sc.splits);
@@ -1516,8 +1546,9 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   fill(o_split_of, sc.split_of);
   fill(fill(o_items, sc.split_items), sc.items);
   fill(o_skip_jobs, sc.skip_jobs);
-  memset(host.data() + o_status, 0xFF, n_iv * sizeof(uint32_t));  // kStatusOk; the counters are zero
-  if (hipMemcpy(d, host.data(), upload, hipMemcpyHostToDevice) != hipSuccess)
+  memset(host.at(o_counters), 0, 4 * sizeof(unsigned));
+  memset(host.at(o_status), 0xFF, n_iv * sizeof(uint32_t));  // kStatusOk
+  if (hipMemcpy(d, host.at(0), upload, hipMemcpyHostToDevice) != hipSuccess)
     return fail(MJD_EDEVICE, "uploading the entropy batch tables failed");
   GPlan& p = b->plan;
   p.jobs = reinterpret_cast<const GJob*>(d + o_jobs);

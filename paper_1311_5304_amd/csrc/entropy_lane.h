@@ -64,12 +64,15 @@ MJD_HD inline uint32_t table_entry(uint32_t length, uint32_t sym, bool ac) {
   return (length + size) | size << 5 | step << 9;
 }
 
-struct GHuff {
-  uint16_t fast[1 << kGLook];
+// The canonical code itself, for codes that the tables leave out.
+struct GCodes {
   int32_t lim[17];     // lim[l]: codes of length <= l fill [0, lim[l]) of the 16-bit left-aligned code space
   int32_t valoff[17];  // symbol index = code + valoff[length]
   uint8_t vals[256];
   uint8_t pad[8];
+};
+struct GHuff : GCodes {
+  uint16_t fast[1 << kGLook];
 };
 
 // A scan's distinct tables in up to four slots (a baseline scan uses at
@@ -87,42 +90,54 @@ MJD_HD inline int extend_value(int raw, int s) { return raw < (1 << (s - 1)) ? r
 
 enum : int { kTableOk = 0, kTableUndefined = 1, kTableTooMany = 2, kTableOverfull = 3 };
 
-// Builds a table from its DHT code counts and symbols (canonical codes,
-// T.81 Annex C).
-inline int build_gtable(const mjd_huffman& h, bool ac, GHuff* t) {
-  memset(t, 0, sizeof(*t));
+// Builds the canonical code of a DHT's counts and symbols (T.81 Annex C).
+inline int build_codes(const mjd_huffman& h, GCodes* t) {
   if (!h.defined) return kTableUndefined;
   int n = 0;
   for (int l = 0; l < 16; ++l) n += h.bits[l];
   if (n > 256) return kTableTooMany;
+  memset(t->pad, 0, sizeof(t->pad));
   memcpy(t->vals, h.vals, sizeof(t->vals));
+  t->lim[0] = t->valoff[0] = 0;
   int32_t code = 0;
   int k = 0;
   for (int l = 1; l <= 16; ++l) {
     t->valoff[l] = k - code;
-    for (int i = 0; i < h.bits[l - 1]; ++i) {
-      if (code >= (1 << l)) return kTableOverfull;
-      if (l <= kGLook) {
-        const uint32_t e = table_entry(static_cast<uint32_t>(l), h.vals[k], ac);
-        const int lo = code << (kGLook - l), hi = (code + 1) << (kGLook - l);
-        for (int p = lo; p < hi; ++p) t->fast[p] = static_cast<uint16_t>(e);
-      }
-      ++code;
-      ++k;
-    }
+    if (h.bits[l - 1] > (1 << l) - code) return kTableOverfull;
+    code += h.bits[l - 1];
+    k += h.bits[l - 1];
     t->lim[l] = code << (16 - l);
     code <<= 1;
   }
   return kTableOk;
 }
 
+// Calls take(code, length, entry) for the codes of lengths [from, to], in order.
+template <class Take>
+inline void for_codes(const GCodes& t, bool ac, int from, int to, const Take& take) {
+  for (int l = from; l <= to; ++l)
+    for (int32_t code = t.lim[l - 1] >> (16 - l); code < t.lim[l] >> (16 - l); ++code)
+      take(static_cast<uint32_t>(code), l, table_entry(static_cast<uint32_t>(l), t.vals[code + t.valoff[l]], ac));
+}
+
+inline int build_gtable(const mjd_huffman& h, bool ac, GHuff* t) {
+  const int rc = build_codes(h, t);
+  if (rc != kTableOk) return rc;
+  memset(t->fast, 0, sizeof(t->fast));
+  for_codes(*t, ac, 1, kGLook, [t](uint32_t code, int l, uint32_t e) {
+    const uint32_t lo = code << (kGLook - l), hi = (code + 1) << (kGLook - l);
+    for (uint32_t p = lo; p < hi; ++p) t->fast[p] = static_cast<uint16_t>(e);
+  });
+  return kTableOk;
+}
+
 enum : int { kPlanTooManyTables = 4 };
 
-// Builds the distinct tables a scan selects into slots and returns their
-// component map in *tsel; kTableOk or the first table error, or
-// kPlanTooManyTables when the scan needs more than kTableSlots tables.
-inline int plan_gtables(const mjd_scan& scan, GTables* g, uint32_t* tsel) {
-  memset(g, 0, sizeof(*g));
+// The distinct tables a scan selects go to slots, each by build(slot, table,
+// ac), and the slots of each component to *tsel; kTableOk or the first table
+// error, or kPlanTooManyTables when the scan needs more than kTableSlots tables.
+template <class Build>
+inline int plan_slots(const mjd_scan& scan, uint32_t* tsel, const Build& build) {
   int key[kTableSlots];
   int n = 0;
   uint32_t sel = 0;
@@ -135,7 +150,7 @@ inline int plan_gtables(const mjd_scan& scan, GTables* g, uint32_t* tsel) {
         if (key[i] == k) slot = i;
       if (slot < 0) {
         if (n == kTableSlots) return kPlanTooManyTables;
-        const int rc = build_gtable(ac ? scan.ac[id] : scan.dc[id], ac != 0, &g->t[n]);
+        const int rc = build(n, ac ? scan.ac[id] : scan.dc[id], ac != 0);
         if (rc != kTableOk) return rc;
         key[n] = k;
         slot = n++;
@@ -145,6 +160,10 @@ inline int plan_gtables(const mjd_scan& scan, GTables* g, uint32_t* tsel) {
   }
   *tsel = sel;
   return kTableOk;
+}
+inline int plan_gtables(const mjd_scan& scan, GTables* g, uint32_t* tsel) {
+  memset(g, 0, sizeof(*g));
+  return plan_slots(scan, tsel, [g](int slot, const mjd_huffman& h, bool ac) { return build_gtable(h, ac, &g->t[slot]); });
 }
 
 // Stream bytes of one lane, all read from a ring of kRing bytes that holds

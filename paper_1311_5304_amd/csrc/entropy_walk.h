@@ -81,33 +81,52 @@ struct PlainTab {
   MJD_HD int val(int t, int i) const { return tab[t].vals[i]; }
 };
 
-inline void build_fast_table(const GHuff& h, bool ac, FastTable* f) {
+// The same of the canonical code alone.
+struct CodeTab {
+  const GCodes* tab;
+  MJD_HD int lim(int t, int l) const { return tab[t].lim[l]; }
+  MJD_HD int valoff(int t, int l) const { return tab[t].valoff[l]; }
+  MJD_HD int val(int t, int i) const { return tab[t].vals[i]; }
+};
+
+// Code by code (256 at most): a batch of many small files spends its time here.
+inline void build_fast_table(const GCodes& h, bool ac, FastTable* f) {
   memset(f->more, 0, sizeof(f->more));
   f->more[2] = kBadEntry;
-  for (uint32_t p = 0; p < 1u << kGLook; ++p) f->fast[p] = h.fast[p] ? h.fast[p] : static_cast<uint16_t>(kBadPrefix);
-  const PlainTab tab{&h};
-  uint32_t used = 3;
-  const uint32_t last = (static_cast<uint32_t>(h.lim[16]) + 63u) >> 6;
-  for (uint32_t p = static_cast<uint32_t>(h.lim[kGLook]) >> 6; p < last; ++p) {
-    uint32_t n = 0;  // bits past the prefix of its longest code
-    for (uint32_t v = 0; v < 64; ++v) {
-      const uint32_t e = long_entry(tab, 0, (p << 6 | v) << 16, ac);
-      const uint32_t len = (e & 31u) - ((e >> 5) & 15u);
-      if (e && len - kGLook > n) n = len - kGLook;
-    }
-    if (n == 0) continue;
+  uint32_t filled = 0;  // canonical codes follow each other from 0 on
+  for_codes(h, ac, 1, kGLook, [&](uint32_t code, int l, uint32_t e) {
+    const uint32_t end = (code + 1) << (kGLook - l);
+    for (; filled < end; ++filled) f->fast[filled] = static_cast<uint16_t>(e ? e : kBadPrefix);
+  });
+  for (; filled < 1u << kGLook; ++filled) f->fast[filled] = static_cast<uint16_t>(kBadPrefix);
+  uint32_t prefix = 1u << kGLook, bits = 0, used = 3;  // bits past the prefix of its longest code
+  const auto place = [&] {
+    if (prefix == 1u << kGLook) return;
     const uint32_t at = (used + 1u) & ~1u;
-    if (at + (1u << n) > kMore) {
-      f->fast[p] = 0;
-      continue;
+    if (at + (1u << bits) > kMore) {
+      f->fast[prefix] = 0;
+      return;
     }
-    for (uint32_t v = 0; v < 1u << n; ++v) {
-      const uint32_t e = long_entry(tab, 0, (p << 6 | v << (6 - n)) << 16, ac);
-      f->more[at + v] = static_cast<uint16_t>(e ? e : kBadEntry);
+    for (uint32_t v = 0; v < 1u << bits; ++v) f->more[at + v] = static_cast<uint16_t>(kBadEntry);
+    f->fast[prefix] = static_cast<uint16_t>(bits << 5 | at >> 1 << 8);
+    used = at + (1u << bits);
+  };
+  for_codes(h, ac, kGLook + 1, 16, [&](uint32_t code, int l, uint32_t e) {
+    if (e == 0) return;
+    const uint32_t n = static_cast<uint32_t>(l - kGLook);
+    if (code >> n != prefix) {
+      place();
+      prefix = code >> n;
     }
-    f->fast[p] = static_cast<uint16_t>(n << 5 | at >> 1 << 8);
-    used = at + (1u << n);
-  }
+    bits = n;  // never shorter than the codes before
+  });
+  place();
+  for_codes(h, ac, kGLook + 1, 16, [&](uint32_t code, int l, uint32_t e) {
+    const uint32_t n = static_cast<uint32_t>(l - kGLook), to = f->fast[code >> n];
+    if (e == 0 || to == 0) return;
+    const uint32_t m = to >> 5 & 7u, at = (to >> 8) * 2 + ((code & ((1u << n) - 1u)) << (m - n));
+    for (uint32_t v = 0; v < 1u << (m - n); ++v) f->more[at + v] = static_cast<uint16_t>(e);
+  });
 }
 
 inline void build_places(const uint8_t* natural, uint8_t nat2[kPlaces]) {

@@ -125,7 +125,7 @@ int main(int argc, char** argv) {
   for (uint64_t j = 0; j < n; ++j) {
     GJob& jb = const_cast<GJob*>(p.jobs)[j];
     move_out<FastTables>(jb.tables, 1, &owned);
-    move_out<GHuff>(jb.codes, kTableSlots, &owned);
+    move_out<GCodes>(jb.codes, kTableSlots, &owned);
     if (jb.skip) move_out<uint16_t>(jb.skip, kTableSlots * kSkipEntries, &owned);
   }
   move_out<GInterval>(p.ivs, p.n_iv, &owned);

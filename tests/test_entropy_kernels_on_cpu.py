@@ -175,6 +175,15 @@ def test_with_less_memory_than_it_would_take(run):
     assert few["splits"] == 0 and few["passes"] > 1 and few["intervals"] == c["intervals"]
 
 
+def test_memory_of_a_job(run):
+    """What the header states: 13 KB, here with 200 bytes of data; the tables
+    are what a corpus of small files is planned and uploaded for."""
+    data = gray(20, 3)
+    one, many = run([data]), run([data], same=65)
+    assert many["splits"] == 0
+    assert (many["memory"] - one["memory"]) / 64 < 13 * 1024 + 300
+
+
 @pytest.mark.parametrize("samp", ["420", "444"])
 def test_damaged_streams(run, samp):
     rnd = random.Random(3)
