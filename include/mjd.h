@@ -493,6 +493,14 @@ int mjd_entropy_batch_status(mjd_entropy_batch* batch, int64_t* bad_job);
 int mjd_entropy_batch_info(const mjd_entropy_batch* batch, uint32_t* intervals, uint32_t* workgroups,
                            uint64_t* bytes);
 
+/* How the batch is decoded: restart intervals cut into chunks, and their
+ * chunks; and, after synchronising the device, how many times the last launch
+ * found that a chunk's boundary was not among those it had followed and had
+ * one lane read on from it (rare but for dense blocks; each takes tens of
+ * microseconds). */
+int mjd_entropy_batch_splits(mjd_entropy_batch* batch, uint32_t* split_intervals, uint64_t* chunks,
+                             uint32_t* mended);
+
 /* Synchronise the device and free the batch's tables. */
 void mjd_entropy_batch_destroy(mjd_entropy_batch* batch);
 

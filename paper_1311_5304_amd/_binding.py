@@ -212,6 +212,9 @@ def lib() -> ctypes.CDLL:
         L.mjd_entropy_batch_info.argtypes = [vp, ctypes.POINTER(u32), ctypes.POINTER(u32),
                                              ctypes.POINTER(ctypes.c_uint64)]
         L.mjd_entropy_batch_info.restype = i32
+        L.mjd_entropy_batch_splits.argtypes = [vp, ctypes.POINTER(u32), ctypes.POINTER(ctypes.c_uint64),
+                                               ctypes.POINTER(u32)]
+        L.mjd_entropy_batch_splits.restype = i32
         L.mjd_entropy_batch_destroy.argtypes = [vp]
         L.mjd_entropy_batch_destroy.restype = None
         L.mjd_decode_host.argtypes = [ctypes.POINTER(mjd_frame), vp, vp, i32, vp, sz, u32, u32, i32]
@@ -562,6 +565,13 @@ class EntropyBatch:
         _check(lib().mjd_entropy_batch_info(self.handle, ctypes.byref(iv), ctypes.byref(wg), ctypes.byref(nb)))
         return {"intervals": iv.value, "workgroups": wg.value, "bytes": nb.value}
 
+    def splits(self) -> dict:
+        """Intervals cut into chunks, their chunks, and (synchronises) how many
+        times the last launch read on from a chunk that it had not followed."""
+        iv, ch, mended = ctypes.c_uint32(), ctypes.c_uint64(), ctypes.c_uint32()
+        _check(lib().mjd_entropy_batch_splits(self.handle, ctypes.byref(iv), ctypes.byref(ch), ctypes.byref(mended)))
+        return {"intervals": iv.value, "chunks": ch.value, "mended": mended.value}
+
     def launch(self, stream=None):
         _check(lib().mjd_entropy_batch_launch(self.handle, _stream(stream)))
 
@@ -601,6 +611,10 @@ def mjd_entropy_batch_status(batch: EntropyBatch) -> int:
 
 def mjd_entropy_batch_info(batch: EntropyBatch) -> dict:
     return batch.info()
+
+
+def mjd_entropy_batch_splits(batch: EntropyBatch) -> dict:
+    return batch.splits()
 
 
 def mjd_entropy_batch_destroy(batch: EntropyBatch):

@@ -37,6 +37,7 @@ constexpr uint32_t kTile = 4096;              // raw bytes that one wave destuff
 constexpr uint32_t kLongSplit = 512;          // chunks above which a workgroup resolves an interval
 constexpr uint32_t kTail = 8192;              // bytes past the chunks that a workgroup may copy
 constexpr uint32_t kPad = 48;                 // bytes past an interval's raw length in its region
+constexpr uint32_t kMended = 4, kCounters = 5;  // the counter of the breaks that a launch has mended; counters
 constexpr uint32_t kStatusOk = 0xFFFFFFFFu;   // else (block in the interval) << 2 | kBadCode, kBadRun or kOverrun
 
 struct GJob {
@@ -141,7 +142,7 @@ struct GPlan {
   uint8_t* links;     // kSlots per chunk
   GHop* hops;         // kParts per slot
   GTask* tasks;       // kParts per chunk
-  unsigned* counters;
+  unsigned* counters;  // two of each decoding kernel's queue, and kMended
 };
 
 // A scan's tables into `codes` and `fast`, kTableSlots each.
@@ -341,6 +342,7 @@ __global__ __launch_bounds__(kThreads) void entropy_destuff(const GPlan pl) {
   const GInterval iv = pl.ivs[which];
   if (w < ps.n_iv) {
     if (lane == 0) pl.status[which] = kStatusOk;
+    if (lane == 0 && which == 0) pl.counters[kMended] = 0;
     if (iv.end - iv.start > kTile) return;
   }
   const uint32_t a = iv.start + tile * kTile;
@@ -476,12 +478,15 @@ struct WordRing {
 //            arrives elsewhere takes a free slot there and goes on;
 //   resolve  chains the links from the interval's start (a scan over maps of
 //            slots), and turns counts and sums into each chunk's task.
-// An interval whose chain breaks (no free slot, or not within kMaxHops
-// chunks, as textures that repeat can make it) is decoded by one lane from
-// that chunk on.  The exits that a guess repeats leave their slots free for
-// that reason: with two free slots a chunk, 5 of 16 files of quality 95 with a
-// marker per row and 1 of 16 without had a broken chain (0.8 to 24 ms instead
-// of 0.2), with these none of 96.
+// A chain breaks where the boundary it arrives at has no slot (none was free,
+// or the lane had gone on for kMaxHops chunks): dense blocks, whose lanes take
+// long to fall into step, and content that repeats.  entropy_resolve then lets
+// one lane read on to the next boundary that has been followed, and scans
+// again.  The exits that a guess repeats leave their slots free, which makes
+// breaks rare up to quality 90 (none in 64 files of quality 50 and 85).  Noisy
+// 1024x768 files without markers have 13 at quality 95 and 500 to 750 at 98,
+// and take 0.6 and 17 to 27 ms; 100 and 155 when one lane decoded the rest of
+// the interval instead.
 // Both kernels are bound by a lane's chain of look-ups where lanes are few and
 // by instruction issue where they are many, so a look-up takes several symbols
 // (skip tables; 11 bits of look-up instead of 12 cost 2% and leave room for
@@ -862,6 +867,91 @@ __device__ __forceinline__ void scan(const uint32_t (&v)[N], const uint32_t (&no
   }
 }
 
+// Reads on from a block boundary of chunk c of a split interval to the first
+// one past it and leaves the hops of its parts; returns the boundary as a
+// state of the next chunk.  One lane, its tables and words in memory: 128
+// bytes take 22 us, most of them the latency of the look-ups (70 with one
+// symbol a look-up, more than the 50 that entropy_decode needs for them, so
+// content that never falls into step is read at no loss).
+__device__ __forceinline__ uint32_t walk_chunk(const GPlan& pl, const GSplit& sp, const GJob& jb, uint32_t bytes,
+                                               uint32_t c, uint32_t state, GHop* hops) {
+  StagedWords words;
+  words.base = nullptr;  // no copy
+  words.src = (gin128*)(pl.data + static_cast<uint64_t>(sp.chunk0) * kChunk);
+  words.off = words.n = 0;
+  words.zero = (bytes + 3) / 4;
+  const uint32_t bpm = jb.bpm, comp_bits = jb.comp_bits, slots_dc = jb.dc_slots, slots_ac = jb.ac_slots;
+  const uint16_t* skip = jb.skip;
+  const FastTables* tables = jb.tables;
+  const CodeTab codes{jb.codes};
+  BitWindow w = words.open(c * kChunkWords + (state >> 8), (state >> 3) & 31u);
+  uint32_t pos = state >> 3, b = state & 7u;  // in bits of the chunk
+  for (uint32_t j = 0; j < kParts; ++j) {
+    const uint32_t end = (j + 1) * kPart * 8;
+    uint32_t blocks = 0, d0 = 0, d1 = 0, d2 = 0;
+    while (pos < end) {
+      bool bad = false;
+      uint32_t t = slots_dc >> (2 * b) & 3u, dc = 0;
+      for (uint32_t k = 0; k < 64;) {
+        const uint32_t top = w.top(), next = words.word(w.wi);
+        const uint32_t m = skip[t * kSkipEntries + (top >> (32 - kSkipLook))];
+        uint32_t bits = m & 31u, size = m >> 12, to = k + (m >> 5 & 127u);
+        if (to > 63 && skip_takes_one(m, to)) {
+          const FastTable& ft = tables->t[t];
+          uint32_t e = ft.fast[top >> (32 - kGLook)];
+          if ((e & 31u) == 0)
+            e = more_entry(e, top, k != 0, [&](uint32_t i) { return static_cast<uint32_t>(ft.more[i]); }, codes,
+                           static_cast<int>(t));
+          bad = e == kBadEntry;
+          bits = bad ? 1u : e & 31u;
+          size = bad ? 0u : e >> 5 & 15u;
+          to = k + (e >> 9);
+        }
+        if (k == 0) dc = static_cast<uint32_t>(entry_value(top, bits, size));
+        t = slots_ac >> (2 * b) & 3u;
+        w.drop(bits, next);
+        pos += bits;
+        k = to;
+      }
+      const uint32_t comp = comp_bits >> (2 * b) & 3u;
+      d0 += comp == 0 ? dc : 0u;
+      d1 += comp == 1 ? dc : 0u;
+      d2 += comp == 2 ? dc : 0u;
+      ++blocks;
+      b = bad || b + 1 == bpm ? 0u : b + 1;
+    }
+    hops[j] = GHop{static_cast<uint16_t>(blocks),
+                   {static_cast<uint16_t>(d0), static_cast<uint16_t>(d1), static_cast<uint16_t>(d2)},
+                   make_state(pos - end, b), 0};
+  }
+  return make_state(pos - kChunk * 8, b);
+}
+
+// Mends the chain of a split interval that ends at chunk c, entered by slot
+// `slot`: the boundary it arrives at has no slot in chunk c + 1.  No slot of
+// that chunk but this boundary's matters then, so it takes the first one, and
+// the lane reads on until it arrives at a boundary that has been followed.
+__device__ __forceinline__ void mend_chain(const GPlan& pl, const GSplit& sp, const GJob& jb, uint32_t bytes,
+                                           uint32_t last, uint32_t c, uint32_t slot) {
+  const auto at = [&](uint32_t chunk, uint32_t i) { return static_cast<uint64_t>(sp.chunk0 + chunk) * kSlots + i; };
+  uint32_t state = pl.hops[at(c, slot) * kParts + kParts - 1].state;
+  for (;;) {
+    uint32_t link = kNoLink;
+    for (uint32_t j = 0; j < kSlots; ++j) {
+      const uint32_t there = pl.states[at(c + 1, j)];
+      if (there != kNoState && (there & ~kGuessed) == state) link = j;
+    }
+    const bool met = link != kNoLink;
+    pl.links[at(c, slot)] = static_cast<uint8_t>(met ? link : 0u);
+    if (met) return;
+    ++c;
+    slot = 0;
+    pl.states[at(c, 0)] = state;
+    if (c == last) return;
+    state = walk_chunk(pl, sp, jb, bytes, c, state, pl.hops + at(c, 0) * kParts);
+  }
+}
+
 // One group of LANES lanes per split interval: a wave for most, a workgroup
 // for those of many chunks (pl.n_long of them, first in the list).  A lane
 // takes a run of chunks, kRun at a time so that their loads overlap.
@@ -869,7 +959,6 @@ constexpr uint32_t kRun = 4;
 template <int LANES>
 __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve(const GPlan pl) {
   __shared__ uint32_t lds[LANES > 64 ? 4 * (LANES / 64) : 1];
-  __shared__ uint32_t broken_lds;
   const uint32_t which = LANES > 64 ? blockIdx.x : pl.n_long + uniform(blockIdx.x * kWaves + (threadIdx.x >> 6));
   if (which >= pl.n_splits) return;
   const uint32_t id = LANES > 64 ? threadIdx.x : lane_of();
@@ -888,26 +977,12 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
 #pragma unroll
     for (uint32_t i = 0; i < kRun; ++i) maps[i] = map_of_links(l[i]);
   };
-  SlotMap maps[kRun], mine = kSameSlots;
-  for (uint32_t c = c0; c < c1; c += kRun) {
-    load_maps(c, maps);
-#pragma unroll
-    for (uint32_t i = 0; i < kRun; ++i)
-      if (c + i < c1) mine = map_then(mine, maps[i]);
-  }
-  const uint32_t m[2] = {mine.lo, mine.hi}, same[2] = {kSameSlots.lo, kSameSlots.hi};
-  uint32_t below[2], all_map[2];
-  scan<LANES, 2>(m, same, [](uint32_t (&x)[2], const uint32_t (&y)[2]) {
-    const SlotMap r = map_then(SlotMap{x[0], x[1]}, SlotMap{y[0], y[1]});
-    x[0] = r.lo;
-    x[1] = r.hi;
-  }, lds, below, all_map);
-  const uint32_t slot0 = below[0] & 255u;  // the slot of chunk c0 that the chain enters by
   // a run's slots along the chain (none after a missing link) and hops
   struct Run {
     uint32_t slot[kRun];
     GHop hop[kRun][kParts];
   };
+  SlotMap maps[kRun];
   auto load_run = [&](uint32_t c, uint32_t slot, Run* r) {
     if (per > kRun) load_maps(c, maps);  // else they are still there
 #pragma unroll
@@ -924,34 +999,55 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
     }
     return slot;
   };
-  uint32_t s[4] = {0, 0, 0, 0};
-  uint32_t slot = slot0, broken = 0xFFFFFFFFu;  // the first chunk whose link is missing
+  uint32_t s[4], slot0, exit_slot;  // the slots by which the chain enters chunk c0 and the last one
   Run run;
-  for (uint32_t c = c0; c < c1 && broken == 0xFFFFFFFFu; c += kRun) {
-    const uint32_t next = load_run(c, slot, &run);
+  for (;;) {  // once, and again after each break that is mended
+    SlotMap mine = kSameSlots;
+    for (uint32_t c = c0; c < c1; c += kRun) {
+      load_maps(c, maps);
 #pragma unroll
-    for (uint32_t i = 0; i < kRun; ++i) {
-      if (c + i >= c1 || run.slot[i] >= kSlots) continue;
-#pragma unroll
-      for (uint32_t j = 0; j < kParts; ++j) {
-        s[0] += run.hop[i][j].blocks;
-        for (int d = 0; d < 3; ++d) s[1 + d] += run.hop[i][j].dc[d];
-      }
-      const uint32_t after = i + 1 < kRun ? run.slot[i + 1] : next;
-      if (after >= kSlots) broken = c + i;
+      for (uint32_t i = 0; i < kRun; ++i)
+        if (c + i < c1) mine = map_then(mine, maps[i]);
     }
-    slot = next;
-  }
-  for (int d = 32; d; d >>= 1) {
-    const uint32_t o = static_cast<uint32_t>(__shfl_xor(static_cast<int>(broken), d));
-    broken = o < broken ? o : broken;
-  }
-  if constexpr (LANES > 64) {
-    if (threadIdx.x == 0) broken_lds = 0xFFFFFFFFu;
-    __syncthreads();
-    if (lane_of() == 0) atomicMin(&broken_lds, broken);
-    __syncthreads();
-    broken = broken_lds;
+    const uint32_t m[2] = {mine.lo, mine.hi}, same[2] = {kSameSlots.lo, kSameSlots.hi};
+    uint32_t below[2], all_map[2];
+    scan<LANES, 2>(m, same, [](uint32_t (&x)[2], const uint32_t (&y)[2]) {
+      const SlotMap r = map_then(SlotMap{x[0], x[1]}, SlotMap{y[0], y[1]});
+      x[0] = r.lo;
+      x[1] = r.hi;
+    }, lds, below, all_map);
+    slot0 = below[0] & 255u;
+    exit_slot = all_map[0] & 255u;
+    for (int d = 0; d < 4; ++d) s[d] = 0;
+    uint32_t slot = slot0, broken = 0xFFFFFFFFu, broken_slot = 0;  // the first chunk whose link is missing
+    for (uint32_t c = c0; c < c1 && broken == 0xFFFFFFFFu; c += kRun) {
+      const uint32_t next = load_run(c, slot, &run);
+#pragma unroll
+      for (uint32_t i = 0; i < kRun; ++i) {
+        if (c + i >= c1 || run.slot[i] >= kSlots) continue;
+#pragma unroll
+        for (uint32_t j = 0; j < kParts; ++j) {
+          s[0] += run.hop[i][j].blocks;
+          for (int d = 0; d < 3; ++d) s[1 + d] += run.hop[i][j].dc[d];
+        }
+        const uint32_t after = i + 1 < kRun ? run.slot[i + 1] : next;
+        if (after >= kSlots) {
+          broken = c + i;
+          broken_slot = run.slot[i];
+        }
+      }
+      slot = next;
+    }
+    if (exit_slot < kSlots) break;  // the same for the whole group
+    // every slot past the first break is none, so one lane has found one
+    if (broken != 0xFFFFFFFFu) {
+      atomicAdd(&pl.counters[kMended], 1u);
+      mend_chain(pl, sp, pl.jobs[iv.job], bytes, last, broken, broken_slot);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if constexpr (LANES > 64) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   }
   uint32_t at[4], all[4];
   const uint32_t zero[4] = {0, 0, 0, 0};
@@ -973,14 +1069,10 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
     }
     pl.tasks[static_cast<uint64_t>(sp.chunk0 + c) * kParts + part] = k;
   };
-  auto no_task = [&](uint32_t c, uint32_t part) { task(c, part, 0, 0, s); };
   auto entry = [&](uint32_t c, uint32_t in) {
     return in < kSlots ? pl.states[static_cast<uint64_t>(sp.chunk0 + c) * kSlots + in] & ~kGuessed : 0u;
   };
-  // up to the broken chunk each part decodes its own blocks; the first of
-  // that chunk, or of the last, all that are left
-  const uint32_t stop = broken < last ? broken : last;
-  slot = slot0;
+  uint32_t slot = slot0;
   for (uint32_t c = c0; c < c1; c += kRun) {
     if (per > kRun) slot = load_run(c, slot, &run);  // else it is still there
     uint32_t state[kRun];
@@ -992,21 +1084,18 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
       uint32_t st = state[i];
 #pragma unroll
       for (uint32_t j = 0; j < kParts; ++j) {
-        if (c + i > stop || (c + i == stop && j > 0)) {
-          no_task(c + i, j);
-          continue;
-        }
-        task(c + i, j, st, c + i == stop ? iv.n_blocks : run.hop[i][j].blocks, at);
+        task(c + i, j, st, run.hop[i][j].blocks, at);
         st = run.hop[i][j].state;
         at[0] += run.hop[i][j].blocks;
         for (int d = 0; d < 3; ++d) at[1 + d] += run.hop[i][j].dc[d];
       }
     }
   }
+  // the last chunk's first part decodes all blocks that are left
   for (uint32_t c = last + id; c < sp.n_chunks; c += LANES)
     for (uint32_t j = 0; j < kParts; ++j) {
-      if (c == last && j == 0 && stop == last) task(c, 0, entry(c, all_map[0] & 255u), iv.n_blocks, all);
-      else no_task(c, j);
+      if (c == last && j == 0) task(c, 0, entry(c, exit_slot), iv.n_blocks, all);
+      else task(c, j, 0, 0, all);
     }
 }
 
@@ -1201,7 +1290,7 @@ struct mjd_entropy_batch {
   uint8_t* d_mem = nullptr;              // every table and buffer of the plan
   std::vector<uint32_t> first_interval;  // per job, into the interval list
   std::vector<uint32_t> iv_index;        // per listed interval, its number in its scan
-  uint64_t bytes = 0;
+  uint64_t bytes = 0, chunks = 0;
 };
 
 namespace mjd {
@@ -1502,7 +1591,7 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
     o_split_of = mem.add(sc.split_of.size() * sizeof(uint32_t));
     o_items = mem.add((sc.split_items.size() + sc.items.size()) * sizeof(GItem));
     o_skip_jobs = mem.add(sc.skip_jobs.size() * sizeof(uint32_t));
-    o_counters = mem.add(4 * sizeof(unsigned));
+    o_counters = mem.add(kCounters * sizeof(unsigned));
     o_status = mem.add(n_iv * sizeof(uint32_t));
     upload = mem.size;
     o_bytes = mem.add(n_iv * sizeof(uint32_t));
@@ -1521,6 +1610,7 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
     else return fail(MJD_ENOMEM, "device allocation for the entropy batch failed");
   }
   b->passes = sc.passes;
+  b->chunks = sc.chunks;
   uint32_t most_items = 0;
   for (const GPass& ps : sc.passes) most_items = std::max(most_items, ps.n_items);
   b->grid = std::min<int>(static_cast<int>(most_items), per_cu * cus);
@@ -1546,7 +1636,7 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   fill(o_split_of, sc.split_of);
   fill(fill(o_items, sc.split_items), sc.items);
   fill(o_skip_jobs, sc.skip_jobs);
-  memset(host.at(o_counters), 0, 4 * sizeof(unsigned));
+  memset(host.at(o_counters), 0, kCounters * sizeof(unsigned));
   memset(host.at(o_status), 0xFF, n_iv * sizeof(uint32_t));  // kStatusOk
   if (hipMemcpy(d, host.at(0), upload, hipMemcpyHostToDevice) != hipSuccess)
     return fail(MJD_EDEVICE, "uploading the entropy batch tables failed");
@@ -1682,6 +1772,23 @@ int mjd_entropy_batch_info(const mjd_entropy_batch* b, uint32_t* intervals, uint
   if (intervals) *intervals = b->plan.n_iv;
   if (workgroups) *workgroups = static_cast<uint32_t>(b->grid + b->split_grid);
   if (bytes) *bytes = b->bytes;
+  return MJD_OK;
+}
+
+int mjd_entropy_batch_splits(mjd_entropy_batch* b, uint32_t* split_intervals, uint64_t* chunks, uint32_t* mended) {
+  if (!b) return mjd::fail(MJD_EINVAL, "null entropy batch");
+  if (split_intervals) *split_intervals = b->plan.n_splits;
+  if (chunks) *chunks = b->chunks;
+  if (!mended) return MJD_OK;
+  int cur = 0;
+  (void)hipGetDevice(&cur);
+  if (cur != b->ctx->device && hipSetDevice(b->ctx->device) != hipSuccess)
+    return mjd::fail(MJD_EDEVICE, "hipSetDevice(%d) failed", b->ctx->device);
+  hipError_t e = hipDeviceSynchronize();
+  if (e == hipSuccess)
+    e = hipMemcpy(mended, b->plan.counters + mjd::gent::kMended, sizeof(uint32_t), hipMemcpyDeviceToHost);
+  if (cur != b->ctx->device) (void)hipSetDevice(cur);
+  if (e != hipSuccess) return mjd::fail(MJD_EDEVICE, "reading the entropy batch failed: %s", hipGetErrorString(e));
   return MJD_OK;
 }
 

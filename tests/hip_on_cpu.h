@@ -192,6 +192,9 @@ struct ThreadIdx {
 };
 inline ThreadIdx thread_idx;
 
+// Called with the name of each kernel that is launched.
+inline std::function<void(const char*)> before_launch = [](const char*) {};
+
 }  // namespace cpu
 
 #define threadIdx (cpu::thread_idx)
@@ -306,4 +309,4 @@ inline hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, F, int, s
   return hipSuccess;
 }
 #define hipLaunchKernelGGL(kernel, grid, block, shared, stream, ...) \
-  (void)(stream), (void)(cpu::launch(grid, block, [&] { kernel(__VA_ARGS__); }) || (cpu_last_error = hipErrorInvalidConfiguration))
+  (void)(stream), cpu::before_launch(#kernel), (void)(cpu::launch(grid, block, [&] { kernel(__VA_ARGS__); }) || (cpu_last_error = hipErrorInvalidConfiguration))

@@ -77,18 +77,22 @@ def gray(n, seed, span=9):
     return bitstream.write_jpeg(frame, coef, np.ones((4, 64), dtype=np.uint16))
 
 
-def periodic(seed, samp, w, h, period, density):
-    """Blocks that repeat every `period` MCUs: a lane that starts in the wrong
-    place may never find the right one."""
+def periodic(seed, w=512, h=256):
+    """(coefficients, file) of blocks that repeat every one to three MCUs: a
+    lane that starts in the wrong place may never find the right one."""
+    rng = np.random.default_rng(seed)
+    samp = ("420", "444", "422")[seed % 3]
     hy, vy = LUMA[samp]
     bpm, n = hy * vy + 2, (w // (8 * hy)) * (h // (8 * vy))
-    rng = np.random.default_rng(seed)
+    period = int(rng.integers(1, 4))
     pat = np.zeros((period * bpm, 64), dtype=np.int16)
-    m = rng.random(pat.shape) < density
+    m = rng.random(pat.shape) < rng.choice([0.05, 0.2, 0.5, 0.9])
     pat[m] = rng.integers(-3, 4, int(m.sum()))
+    if rng.random() < 0.5:
+        pat[:] = pat[rng.integers(0, period * bpm)]
     pat[:, 0] = rng.integers(-5, 6)
     coef = np.tile(pat, (n // period + 1, 1))[:n * bpm]
-    return bitstream.write_jpeg(frame_of(w, h, samp), coef, np.ones((4, 64), dtype=np.uint16))
+    return coef, bitstream.write_jpeg(frame_of(w, h, samp), coef, np.ones((4, 64), dtype=np.uint16))
 
 
 def scan_range(data):
@@ -157,10 +161,18 @@ def test_lengths_around_chunks(run):
     assert c["splits"] > 12
 
 
-@pytest.mark.parametrize("seed,samp,period,density", [(0, "420", 3, 0.5), (10, "444", 3, 0.9), (31, "444", 2, 0.9),
-                                                      (44, "422", 3, 0.05)])
-def test_periodic_content(run, seed, samp, period, density):
-    run([periodic(seed, samp, 512, 256, period, density)], seed=seed)
+@pytest.mark.parametrize("seed", [0, 5, 10, 31, 44])
+def test_periodic_content(run, seed):
+    """Broken chains: without a free slot, and (10 and 31) after too many hops."""
+    c = run([periodic(seed)[1]], seed=seed)
+    assert c["breaks"] == 1 and c["mended"] > 1 and c["out_of_hops"] == (seed in (10, 31))
+
+
+def test_dense_photographs_break_chains(run):
+    """A workgroup and waves mend chains of their own, and no other."""
+    streams = [photograph(400, 300, "420", 98), photograph(200, 150, "420", 97, 75, 3), photograph(333, 250, "420", 85)]
+    c = run(streams, seed=5)
+    assert c["long"] == 1 and c["breaks"] > 1 and c["mended"] > c["breaks"] and c["splits"] > 3
 
 
 def test_with_less_memory_than_it_would_take(run):
@@ -186,8 +198,15 @@ def test_memory_of_a_job(run):
 
 @pytest.mark.parametrize("samp", ["420", "444"])
 def test_damaged_streams(run, samp):
+    damaged(run, photograph(256, 160, samp, 85), 12)
+
+
+def test_damage_in_broken_chains(run):
+    damaged(run, periodic(0, 256, 128)[1], 8)
+
+
+def damaged(run, data, least):
     rnd = random.Random(3)
-    data = photograph(256, 160, samp, 85)
     lo, hi = scan_range(data)
     bad = 0
     for k in range(20):
@@ -203,4 +222,4 @@ def test_damaged_streams(run, samp):
         if k % 5 == 2:  # ones, then zeros: codes that do not exist
             b[lo:hi] = b"\xFF\x00" * ((hi - lo) // 4) + bytes(hi - lo - 2 * ((hi - lo) // 4))
         bad += run([bytes(b)], seed=k)["bad"]
-    assert bad >= 12
+    assert bad >= least
