@@ -110,7 +110,8 @@ typedef struct mjd_ctx mjd_ctx;
  * segments when it finishes one.
  *   seg_subtiles  sub-tile rows per segment; 0: the automatic choice
  *                 (single image: enough segments to fill every resident
- *                 slot once; batch: about four segments per slot).
+ *                 slot once; batch: about four segments per slot, of at
+ *                 most six sub-tile rows where the tables have room).
  *   workgroups    workgroups launched; 0: as many as the device keeps
  *                 resident.  A larger count is allowed: the extra
  *                 workgroups start as resident ones finish.  Never more
