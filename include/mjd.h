@@ -119,8 +119,11 @@ typedef struct mjd_ctx mjd_ctx;
  *   shape         sub-tile shape of the single-image kernel, an index into
  *                 the sampling class's list (mjd_shape_count /
  *                 mjd_shape_info); 0 is the class's default, and an index
- *                 past the end of a class's list selects that default.  The
- *                 batch kernel has one fixed shape per class.
+ *                 past the end of a class's list selects that default.  With
+ *                 the default and no other field set, images too small to
+ *                 fill the device may run in a shape that suits them better,
+ *                 listed or not.  The batch kernel has one fixed shape per
+ *                 class.
  * The values change only speed, never the output. */
 typedef struct mjd_tuning {
   uint32_t seg_subtiles;

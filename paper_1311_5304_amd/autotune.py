@@ -116,7 +116,9 @@ def tune(ctx, frame, coef_sets, qt, mode: int, out_sets, reps: int = 10, reps_to
     rows are dicts {shape, sx, sy, threads, resident_per_cu, seg_subtiles,
     workgroups (asked), segments, launched, workgroups_per_cu (launched per
     CU), ms[, ms_refined]}.  A candidate whose launch equals one already
-    timed (more workgroups asked than there are segments) is skipped."""
+    timed (more workgroups asked than there are segments) is skipped.  Where
+    the untuned call is as fast as the winner (small images have shapes that no
+    list holds), best is that call: the fields 0, no shape, in no table."""
     g = B.mjd_geometry_of(frame)
     w = int(frame["width"])
     shp = shapes(ctx, frame, mode)
@@ -151,6 +153,9 @@ def tune(ctx, frame, coef_sets, qt, mode: int, out_sets, reps: int = 10, reps_to
                     r["ms"] = time_of(r, reps)
                     table.append(r)
         best = _refine(table, time_of, reps_top, top)
+        own = {"shape": 0, "seg_subtiles": 0, "workgroups": 0, "workgroups_per_cu": 0}
+        own["ms"] = time_of(own, reps)
+        best = _refine([own, best], time_of, reps_top, 2)
     finally:
         B.mjd_ctx_set_tuning(ctx, saved["seg_subtiles"], saved["workgroups"], saved["shape"])
     return best, table

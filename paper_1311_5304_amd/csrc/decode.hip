@@ -220,15 +220,15 @@ hipError_t launch_image(const ImageView& im, int row0, int row1, int hf, int vf,
   // 5.9 -> 5.4, 6.1 -> 5.5, 6.3 -> 6.0; at 1921x1081 (272 to 544) the wide
   // workgroups, of which one fits a CU, take 10.0 for 8.2, 11.0 for 7.9, 11.6
   // for 9.2 and 11.9 for 8.7.
-  if (tu.shape == 0 && tu.seg_subtiles == 0 && tu.workgroups == 0) {
+  if (i == 0 && tu.seg_subtiles == 0 && tu.workgroups == 0) {
     const Shape* small = l == k420S ? &kSmall420S : l == k422S ? &kSmall422S : l == k444 ? &kSmall444 : l == k422F ? &kSmall422F : nullptr;
     if (small && tiles(*small) <= cus) return small->launch(im, row0, row1, cu_count, tu, stream);
   }
   // Fancy 4:2:2 images that give each workgroup one or two sub-tiles of the
   // default shape take the 8x4 one, whose fourth wave shares the second phase:
-  // 256x256 7.4 -> 6.3 us, 1921x1081 10.1 -> 9.1, 2592x1944 15.1 -> 13.2; at
-  // 4096x3072 the two are equal (21.4, 21.1), at 6000x4000 the default leads.
-  if (l == k422F && tu.shape == 0 && tu.seg_subtiles == 0) {
+  // 1921x1081 10.1 -> 9.1 us, 2592x1944 15.1 -> 13.2; at 4096x3072 the two are
+  // equal (21.4, 21.1), at 6000x4000 the default leads.
+  if (l == k422F && i == 0 && tu.seg_subtiles == 0) {
     int per_cu = 0;
     const hipError_t e = l[0].per_cu(&per_cu);
     if (e != hipSuccess) return e;
