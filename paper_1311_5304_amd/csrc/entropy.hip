@@ -1339,20 +1339,20 @@ class HostBytes {
 // bytes that take as much.
 constexpr uint64_t kSplitMost = uint64_t{256} << 20;
 constexpr uint64_t kSkipBytes = kTableSlots * kSkipEntries * sizeof(uint16_t);
-static uint32_t split_threshold(const std::vector<GInterval>& ivs) {
+static uint32_t split_threshold(const std::vector<GInterval>& ivs, uint32_t* longest_of_all) {
   uint64_t bytes[33] = {};  // of the intervals of 2^(i-1) < length <= 2^i
   uint64_t count[33] = {};
   uint64_t jobs[33] = {};  // whose longest interval is one of them
   uint32_t longest[33] = {};
   for (size_t k = 0; k < ivs.size(); ++k) {
     const uint32_t len = ivs[k].end - ivs[k].start;
-    int i = 0;
-    while (i < 32 && (uint64_t{1} << i) < len) ++i;
+    const int i = len > 1 ? 32 - __builtin_clz(len - 1) : 0;
     bytes[i] += len;
     ++count[i];
     if (k == 0 || ivs[k - 1].job != ivs[k].job) ++jobs[i];  // a job's longest comes first
     longest[i] = std::max(longest[i], len);
   }
+  *longest_of_all = *std::max_element(longest, longest + 33);
   double best = 0;
   uint32_t over = 0xFFFFFFFFu;
   uint64_t split = 0, skips = 0, rest = 0;
@@ -1406,8 +1406,8 @@ static void schedule(std::vector<GInterval>& ivs, const std::vector<uint32_t>& f
   const size_t n = gj.size(), n_iv = ivs.size();
   // Split intervals lie in whole chunks, so that chunk i of the batch is at
   // byte i * kChunk of the data; the others follow them.
-  for (const GInterval& iv : ivs)
-    if (iv.end - iv.start > split_over) sc.chunks += (static_cast<uint64_t>(iv.end - iv.start) + kPad) / kChunk + 1;
+  for (size_t k = 0; k < n_iv && split_over != 0xFFFFFFFFu; ++k)
+    if (ivs[k].end - ivs[k].start > split_over) sc.chunks += (static_cast<uint64_t>(ivs[k].end - ivs[k].start) + kPad) / kChunk + 1;
   const uint64_t base = sc.chunks ? (sc.chunks * kChunk + kTail) / 16 : 0;
   uint64_t units = base;
   uint32_t n_chunks = 0;
@@ -1503,6 +1503,9 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   HostBytes host;
   host.resize(mem.size);
   std::vector<GInterval> ivs;
+  uint64_t want = 0;  // as the scans say, which are not checked yet
+  for (size_t j = 0; j < n; ++j) want += jobs[j].scan ? jobs[j].scan->n_intervals : 0;
+  ivs.reserve(std::min<uint64_t>(want, 1u << 20));
   b->first_interval.resize(n);
   for (size_t j = 0; j < n; ++j) {
     const mjd_entropy_job& J = jobs[j];
@@ -1573,8 +1576,7 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
   // On a device with too little memory left for it the batch goes on without
   // splitting, then with smaller passes, down to one interval's data.
   uint32_t longest = 0;
-  for (const GInterval& iv : ivs) longest = std::max(longest, iv.end - iv.start);
-  uint32_t split_over = split_threshold(ivs);
+  uint32_t split_over = split_threshold(ivs, &longest);
   uint64_t pass_bytes = kPassBytes;
   Schedule sc;
   uint64_t o_jobs, o_ivs, o_tiles, o_splits, o_groups, o_split_of, o_items, o_skip_jobs, o_counters,
