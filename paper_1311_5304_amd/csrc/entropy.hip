@@ -11,7 +11,8 @@
 //   _resolve                block counts and DC predictions at which their
 //                           parts begin;
 //   entropy_decode<true>    the parts of split intervals, a lane each;
-//   entropy_decode<false>   the other intervals, a lane each.
+//   entropy_decode<false>   the other intervals, a lane each (in passes, where
+//                           their destuffed bytes exceed kPassBytes).
 // Both decoding kernels write whole blocks in MCU order, the layout that
 // mjd_decode reads.  Each interval's status goes to a device array.
 #include <stdio.h>
@@ -70,10 +71,11 @@ struct GTile {
 
 // An interval decoded by chunks of destuffed bytes.  Chunks are numbered over
 // the batch, a job's one after the other, and lie in that order in memory.
-// 128 bytes: a 12-image corpus of 4:2:0 files took 500 us, 625 with 256 and
-// 1050 with 512.  64 bytes leave more boundaries unguessed: a 4000x3000 file
-// with markers per row takes 129 instead of 166 us, but 5 of 16 files of
-// quality 95 without markers had a broken chain, which costs tens of ms.
+// 128 bytes: a 12-image corpus of 4:2:0 files takes 322 us (330 with 64, 421
+// with 256, 595 with 512), a 4000x3000 file with markers per row 162 (134, 263,
+// 445).  Shorter ones leave more boundaries unguessed: a noisy 1024x768 file
+// without markers has 12 broken chains at quality 95 (265 with 64, none with
+// 256) and takes 0.59 ms (6.3, 0.31), and at 98 462 (1702, 33) and 18 ms (60, 2.1).
 constexpr uint32_t kChunk = 128, kChunkWords = kChunk / 4;
 struct GSplit {
   uint32_t iv, chunk0, n_chunks;
@@ -215,7 +217,7 @@ __device__ __forceinline__ void wave_sync() {
 // test every byte nor run the byte-wise path that one lane in six of a wave
 // needs in every step.  One wave takes kTile raw bytes, 16 a lane, and leaves
 // them by 16-byte stores at any address; bound by memory (15 us for the 17 MB
-// of the 12-image corpus, of 500).  Data ends at the first 0xFF that no zero
+// of the 12-image corpus, of 322).  Data ends at the first 0xFF that no zero
 // follows, as at the interval's end.
 
 // Bits 0..3: the bytes of x that are zero.

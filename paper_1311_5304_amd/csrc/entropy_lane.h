@@ -1,13 +1,14 @@
 // Huffman decoding of one restart interval of a baseline scan: the tables'
-// entry format, which the GPU kernels share, and a sequential decoder over
-// small memory interfaces for CPU callers (the kernels work on destuffed
-// words, entropy_walk.h).  The paper leaves entropy decoding on the CPU
+// entry format and the canonical codes, which the GPU entropy kernels use
+// (with the pieces of entropy_walk.h, over destuffed words), and a sequential
+// decoder over small memory interfaces, which no kernel uses: it reads stuffed
+// bytes one symbol at a time and is what tests compare with.  The paper leaves entropy decoding on the CPU
 // because code words have variable length (Sec. 1); restart intervals restart
 // the bit stream and the DC predictions, so each of them decodes on its own
 // (ITU-T T.81 restart markers).
 //
-// One Huffman symbol is decoded per call of lane_step, every kind on one
-// short path:
+// The sequential decoder takes one Huffman symbol per call of lane_step, every
+// kind on one short path:
 // - one 16-bit table entry gives the length, zero run and magnitude size of
 //   any code of at most kGLook bits, and the magnitude bits are read from
 //   the same 32-bit window (T.81 F.1.2.2, F.2.2.1);

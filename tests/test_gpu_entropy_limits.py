@@ -150,6 +150,41 @@ def test_long_and_short_split_intervals(M, ctx):
     assert s["intervals"] > 4 and s["chunks"] > 2 * 512
 
 
+def test_captured_and_on_two_streams(M, ctx):
+    """Launches of a graph, with eager work between them, and two batches at
+    once: split intervals, whole ones and broken chains."""
+    sets = [[photograph(640, 480, 98), photograph(400, 300, 85, 2)], [photograph(640, 480, 95, 40, 31), periodic(10)]]
+    jobs = [[job(M, data) for _, data in streams] for streams in sets]
+    batches = [M.EntropyBatch(ctx, j) for j in jobs]
+
+    def check_and_clear(which):
+        torch.cuda.synchronize()
+        for (coef, _), j in zip(sets[which], jobs[which]):
+            assert np.array_equal(j[4].cpu().numpy().reshape(-1, 64), coef), which
+            j[4].fill_(0x5A5A)
+
+    batches[0].launch()
+    check_and_clear(0)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        batches[0].launch()
+    for rep in range(4):
+        torch.zeros(1 << 20, device="cuda").sum()
+        graph.replay()
+        check_and_clear(0)
+        assert batches[0].status() == -1 and batches[0].splits()["mended"] > 0
+    streams = [torch.cuda.Stream() for _ in batches]
+    for rep in range(3):
+        torch.cuda.synchronize()
+        for b, s in zip(batches, streams):
+            b.launch(s)
+        for k, b in enumerate(batches):
+            check_and_clear(k)
+            assert b.status() == -1
+    for b in batches:
+        b.close()
+
+
 def test_more_bytes_than_a_pass_holds(M, ctx):
     """1.3 GB of intervals of an MCU row, decoded in two passes, with a long
     interval at the end of the list, which many lanes decode."""
