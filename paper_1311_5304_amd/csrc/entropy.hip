@@ -186,6 +186,7 @@ typedef int v4i_t __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i_t lds128;
 typedef __attribute__((address_space(1))) const uint8_t gin8;
+typedef __attribute__((address_space(1))) const uint16_t gin16;
 typedef __attribute__((address_space(1))) const v4u_t gin128;
 typedef __attribute__((address_space(1))) v4i_t gout128;
 typedef __attribute__((address_space(1))) uint8_t gout8;
@@ -883,11 +884,11 @@ __device__ __forceinline__ uint32_t walk_chunk(const GPlan& pl, const GSplit& sp
   words.off = words.n = 0;
   words.zero = (bytes + 3) / 4;
   const uint32_t bpm = jb.bpm, comp_bits = jb.comp_bits, slots_dc = jb.dc_slots, slots_ac = jb.ac_slots;
-  const uint16_t* skip = jb.skip;
-  const FastTables* tables = jb.tables;
+  gin16* skip = (gin16*)jb.skip;
   const CodeTab codes{jb.codes};
   BitWindow w = words.open(c * kChunkWords + (state >> 8), (state >> 3) & 31u);
   uint32_t pos = state >> 3, b = state & 7u;  // in bits of the chunk
+#pragma unroll 1
   for (uint32_t j = 0; j < kParts; ++j) {
     const uint32_t end = (j + 1) * kPart * 8;
     uint32_t blocks = 0, d0 = 0, d1 = 0, d2 = 0;
@@ -899,10 +900,10 @@ __device__ __forceinline__ uint32_t walk_chunk(const GPlan& pl, const GSplit& sp
         const uint32_t m = skip[t * kSkipEntries + (top >> (32 - kSkipLook))];
         uint32_t bits = m & 31u, size = m >> 12, to = k + (m >> 5 & 127u);
         if (to > 63 && skip_takes_one(m, to)) {
-          const FastTable& ft = tables->t[t];
-          uint32_t e = ft.fast[top >> (32 - kGLook)];
+          gin16* ft = (gin16*)jb.tables + t * (sizeof(FastTable) / 2);  // fast, then more
+          uint32_t e = ft[top >> (32 - kGLook)];
           if ((e & 31u) == 0)
-            e = more_entry(e, top, k != 0, [&](uint32_t i) { return static_cast<uint32_t>(ft.more[i]); }, codes,
+            e = more_entry(e, top, k != 0, [ft](uint32_t i) { return static_cast<uint32_t>(ft[(1u << kGLook) + i]); }, codes,
                            static_cast<int>(t));
           bad = e == kBadEntry;
           bits = bad ? 1u : e & 31u;
@@ -956,16 +957,20 @@ __device__ __forceinline__ void mend_chain(const GPlan& pl, const GSplit& sp, co
 
 // One group of LANES lanes per split interval: a wave for most, a workgroup
 // for those of many chunks (pl.n_long of them, first in the list).  A lane
-// takes a run of chunks, kRun at a time so that their loads overlap.
+// takes a run of chunks, kRun at a time so that their loads overlap.  Where
+// waves resolve, five of them to a SIMD: the 9619 intervals of the 12-image
+// corpus take 16.9 us, 19 with the 112 registers that mending asks for otherwise
+// (16.4 without mending).
 constexpr uint32_t kRun = 4;
 template <int LANES>
-__global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve(const GPlan pl) {
+__global__ __launch_bounds__(LANES > 64 ? LANES : kThreads, LANES > 64 ? 4 : 5) void entropy_resolve(const GPlan pl) {
   __shared__ uint32_t lds[LANES > 64 ? 4 * (LANES / 64) : 1];
   const uint32_t which = LANES > 64 ? blockIdx.x : pl.n_long + uniform(blockIdx.x * kWaves + (threadIdx.x >> 6));
   if (which >= pl.n_splits) return;
   const uint32_t id = LANES > 64 ? threadIdx.x : lane_of();
   const GSplit sp = pl.splits[which];
   const GInterval iv = pl.ivs[sp.iv];
+  const GJob jb = pl.jobs[iv.job];
   const uint32_t bytes = pl.bytes[sp.iv];
   const uint32_t last = bytes ? (bytes - 1) / kChunk : 0;
   const uint32_t per = (last + LANES - 1) / LANES;
@@ -1004,6 +1009,8 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
   uint32_t s[4], slot0, exit_slot;  // the slots by which the chain enters chunk c0 and the last one
   Run run;
   for (;;) {  // once, and again after each break that is mended
+    run = Run{};  // no registers for these across a mend
+    for (uint32_t i = 0; i < kRun; ++i) maps[i] = kSameSlots;
     SlotMap mine = kSameSlots;
     for (uint32_t c = c0; c < c1; c += kRun) {
       load_maps(c, maps);
@@ -1044,7 +1051,7 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : kThreads) void entropy_resolve
     // every slot past the first break is none, so one lane has found one
     if (broken != 0xFFFFFFFFu) {
       atomicAdd(&pl.counters[kMended], 1u);
-      mend_chain(pl, sp, pl.jobs[iv.job], bytes, last, broken, broken_slot);
+      mend_chain(pl, sp, jb, bytes, last, broken, broken_slot);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if constexpr (LANES > 64) __syncthreads();
