@@ -470,10 +470,10 @@ typedef struct mjd_entropy_batch mjd_entropy_batch;
  * An invalid job fails the whole call, naming the job.  The device buffers
  * are only recorded, not accessed.
  * Device memory of a batch: 13 KB a job, 40 bytes a restart interval, a copy
- * of the entropy-coded bytes (1 GiB at most, or the longest interval; a
- * larger batch is decoded in passes that share it), and where intervals are
- * cut into chunks 3.8 bytes for each of their bytes and 16 KB a job, 1 GiB at
- * most.  Where the device has less left, the intervals stay whole and the
+ * of the entropy-coded bytes with about 56 more for each interval (1 GiB at
+ * most, or the longest interval; a larger batch is decoded in passes that
+ * share it), and where intervals are cut into chunks 3.8 bytes for each of
+ * their bytes and 16 KB a job, 1 GiB at most.  Where the device has less left, the intervals stay whole and the
  * passes get smaller, down to the longest interval; with less than that the
  * call returns MJD_ENOMEM. */
 int mjd_entropy_batch_create(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entropy_batch** out);
