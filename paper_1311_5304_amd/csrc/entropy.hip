@@ -1617,7 +1617,7 @@ static int build(mjd_ctx* ctx, const mjd_entropy_job* jobs, size_t n, mjd_entrop
     b->d_mem = nullptr;
     (void)hipGetLastError();  // the launches ask for it
     if (split_over != 0xFFFFFFFFu) split_over = 0xFFFFFFFFu;
-    else if (pass_bytes > longest) pass_bytes /= 4;
+    else if (pass_bytes > std::max<uint64_t>(longest, 1u << 16)) pass_bytes /= 4;
     else return fail(MJD_ENOMEM, "device allocation for the entropy batch failed");
   }
   b->passes = sc.passes;

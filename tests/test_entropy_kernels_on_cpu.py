@@ -5,6 +5,7 @@ says what each stream holds: every coefficient of a valid one is equal, and a
 damaged one is reported, whatever its bytes.  Coefficients are whole numbers:
 no tolerance."""
 import os
+import platform
 import random
 import shutil
 import subprocess
@@ -21,6 +22,8 @@ CHUNK = 128  # bytes of a chunk of a split interval
 
 
 def clang():
+    if platform.machine() != "x86_64":
+        pytest.skip("the lanes' stacks are switched by x86-64 code")
     for cand in ("/opt/rocm/llvm/bin/clang++", shutil.which("clang++")):
         if cand and os.path.exists(cand):
             return cand
